@@ -5,6 +5,12 @@
 // 16-byte LDS read.  The tile is computed transposed (weight rows as the MFMA
 // row operand, activation rows as the column operand).
 //
+// What bounds the large tiles: power (with N(0,1)-like operands the clock settles at 1.7-1.9 GHz) and, beside it, the
+// loads of operand tiles through a compute unit's load path - a 256x256 k-tile takes 1.45 us, its matrix work alone 1.05
+// and its 64 KB of loads alone 0.97.  16384 x 36864 x 12288: 10.85 -> 10.18 ms (32x32x16 instructions, loads and
+// fragment reads in clumps -> 16x16x32, dealt out one by one, 8 x 4 tiles per XCD); 2048 x 15360 x 5120: 258 -> 250 us;
+// 2048 x 5120 x 20480 (256x160 tiles): 329 -> 311 us.
+//
 // Tile BM x BN (activation rows x weight rows: 256x160, 256x256, 128x128 or 64x128), BK = 64,
 // 256 threads = 4 waves (one per SIMD).  Operands go global -> LDS directly (no register
 // staging), three LDS buffers (two for the 256x256 tile), one barrier per k-tile; fragment reads and load issue are
@@ -72,8 +78,9 @@ unsigned long long* g_gemm_dbg = nullptr;
 // XCD runs at a time share one weight tile and read 32 different activation tiles, and the eight XCDs sit in
 // far-apart parts of the output, so every column tile re-streams the whole activation matrix from HBM.
 // Instead, the 256 workgroups that run together (32 per XCD, ids dealt round-robin) take one patch of up to
-// 16 x 16 output tiles, and inside it every XCD a 16 x 2 strip: 16 + 16 operand tiles from HBM per 256
-// output tiles, 16 + 2 through each L2 per 32.
+// 16 x 16 output tiles, and inside it every XCD a block of 8 x 4: 16 + 16 operand tiles from HBM per 256 output
+// tiles, 8 + 4 through each L2 per 32.  (A strip of 16 x 2 per XCD - 16 + 2 through each L2 - cost 1-3 % at 16384
+// rows; with 8 row tiles the plain m-fastest order inside a chunk is the 8 x 4 block.)
 __device__ __forceinline__ void patch_tile(int pid, int tiles_m, int tiles_n, int& tm, int& tn) {
   constexpr int kXcd = 8, kPerXcd = 32, kChunk = kXcd * kPerXcd, kGroupM = 16;
   const int total = tiles_m * tiles_n;
@@ -81,7 +88,10 @@ __device__ __forceinline__ void patch_tile(int pid, int tiles_m, int tiles_n, in
   int v = pid;
   if (pid < full) {
     const int xcd = pid % kXcd, slot = pid / kXcd;
-    v = slot / kPerXcd * kChunk + xcd * kPerXcd + slot % kPerXcd;
+    const int s = slot % kPerXcd;
+    // the chunk's tiles are numbered m-fastest in groups of 16 rows: (row, column) = (number % 16, number / 16)
+    v = slot / kPerXcd * kChunk + (tiles_m >= kGroupM ? ((xcd >> 1) * 4 + (s >> 3)) * kGroupM + (xcd & 1) * 8 + (s & 7)
+                                                      : xcd * kPerXcd + s);
   } else {
     const int per = (total - full) / kXcd, q = pid - full;  // last, partial chunk: equal contiguous shares
     if (q < per * kXcd) v = full + (q % kXcd) * per + q / kXcd;
@@ -110,6 +120,23 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((VM & 0xf) | (0x7 << 4) | (0xf << 8) | ((VM >> 4) << 14));
 }
 
+// acc += W-fragment x X-fragment, in place in the accumulator registers.  As the builtin, with 64 accumulators of
+// four registers - all 256 accumulator registers - the compiler gave results other registers than inputs and
+// moved 100 to 400 registers per k-tile.  What it cannot see here: an accumulator may be moved or read only 8 wait
+// states after the instruction, and used as input 2 after it was moved.  PADDED carries these waits along, for code
+// around which the compiler does move accumulators (all but the main loop, whose body is free of moves).
+template <bool PADDED>
+__device__ __forceinline__ void mfma_acc(floatx4& acc, const u32x4& w, const u32x4& x) {
+  if constexpr (PADDED)
+    asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\ts_nop 7" : "+a"(acc) : "v"(w), "v"(x));
+  else
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
+}
+
+// Workgroup barrier that closes this wave's LDS reads and leaves its direct-to-LDS loads in flight (behind
+// __syncthreads() the compiler may wait for all of them).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // EPI selects the epilogue at compile time, so the plain prefill instantiation carries none of the
 // decode-side code: 0 = bias / ReLU / residual -> bf16 segments; 1 = split-K, raw fp32 partials;
 // 2 = as 0, but the K and V thirds go into the paged cache.
@@ -122,8 +149,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   constexpr int NW = WAVES_M * WAVES_N;
   static_assert(NW == 4, "4 waves");
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
-  constexpr int TM = WTM / 32, TN = WTN / 32;
-  static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of the 32x32 MFMA");
+  constexpr int TM = WTM / 16, TN = WTN / 16;   // 16x16 result tiles of a wave
+  static_assert(WTM % 16 == 0 && WTN % 32 == 0, "the epilogue stages 32 columns of a wave tile at a time");
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "a wave-level load covers 8 rows");
   constexpr int ROW_BYTES = kBK * 2;                      // 128
   constexpr int STAGE_ELEMS = (BM + BN) * kBK;            // elements per stage
@@ -195,69 +222,75 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
     for (int j = 0; j < LPS; ++j) issue_one(stage, kt_load, j);
   };
 
-  floatx16 acc[TN][TM];
+  floatx4 acc[TN][TM];
 #pragma unroll
   for (int a = 0; a < TN; ++a)
 #pragma unroll
-    for (int b = 0; b < TM; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+    for (int b = 0; b < TM; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // swizzled fragment offsets (elements) inside a row, one per k-step
-  const int frag_row = lane & 31;
-  const int hl = lane >> 5;
+  // swizzled fragment offsets (elements) inside a row, one per 32-deep k-step: lane (row = lane % 16, quarter =
+  // lane / 16) reads chunk 4 * step + quarter
   // Kept in registers across the k loop, one per k-step and operand (the empty asm stops the compiler from
   // recomputing them in the loop): a fragment read is then one add of the stage's base plus an immediate.
-  int xfrag[kBK / 16], wfrag[kBK / 16];
+  const int frag_row = lane & 15;
+  int xfrag[kBK / 32], wfrag[kBK / 32];
 #pragma unroll
-  for (int kk = 0; kk < kBK / 16; ++kk) {
-    const int koff = ((2 * kk + hl) ^ ((lane >> 1) & 7)) * 8;
-    xfrag[kk] = (wm * WTM + frag_row) * kBK + koff;
-    wfrag[kk] = BM * kBK + (wn * WTN + frag_row) * kBK + koff;
-    asm volatile("" : "+v"(xfrag[kk]), "+v"(wfrag[kk]));
+  for (int ks = 0; ks < kBK / 32; ++ks) {
+    const int koff = ((4 * ks + (lane >> 4)) ^ ((lane >> 1) & 7)) * 8;
+    xfrag[ks] = (wm * WTM + frag_row) * kBK + koff;
+    wfrag[ks] = BM * kBK + (wn * WTN + frag_row) * kBK + koff;
+    asm volatile("" : "+v"(xfrag[ks]), "+v"(wfrag[ks]));
   }
 
-  // A k-tile (4 MFMA k-steps) is multiplied in two halves of two k-steps each.  Within a half every
-  // accumulator tile gets its two MFMAs back to back (the second one chains on the first one's
-  // result, which the matrix pipe issues without a bubble; a round-robin over 10 accumulators was
-  // measured ~15 % slower with one wave per SIMD).  The fragments of the next half are fetched
-  // while the current half is multiplied, so two fragment sets of 2 x (TN + TM) registers exist.
+  // A k-tile is multiplied in two halves of one 32-deep k-step each.  The fragments of the next half are fetched
+  // while the current half is multiplied, so two fragment sets of TN + TM registers x 4 exist.
   // (held as integer vectors: bf16 vectors carried around the loop get re-packed by the compiler)
   struct Frags {
-    u32x4 w[2][TN];
-    u32x4 x[2][TM];
+    u32x4 w[TN];
+    u32x4 x[TM];
   };
   Frags fa, fb;
-  constexpr int NR = 2 * (TN + TM);  // fragment reads per half
-  // read number r of the half starting at k-step kk0 of stage buffer sb
-  auto frag_read = [&](Frags& f, const uint16_t* sb, int kk0, int r) {
-    const int s2 = r / (TN + TM), q = r % (TN + TM);
-    if (q < TN) f.w[s2][q] = *reinterpret_cast<const u32x4*>(sb + wfrag[kk0 + s2] + q * 32 * kBK);
-    else f.x[s2][q - TN] = *reinterpret_cast<const u32x4*>(sb + xfrag[kk0 + s2] + (q - TN) * 32 * kBK);
+  constexpr int NR = TN + TM;  // fragment reads per half
+  // read number r of k-step ks of stage buffer sb
+  auto frag_read = [&](Frags& f, const uint16_t* sb, int ks, int r) {
+    if (r == 0) f.w[0] = *reinterpret_cast<const u32x4*>(sb + wfrag[ks]);
+    else if (r <= TM) f.x[r - 1] = *reinterpret_cast<const u32x4*>(sb + xfrag[ks] + (r - 1) * 16 * kBK);
+    else f.w[r - TM] = *reinterpret_cast<const u32x4*>(sb + wfrag[ks] + (r - TM) * 16 * kBK);
   };
 
-  // One half: after each accumulator's MFMA pair the code issues a share of the next half's fragment
-  // reads and (in the second half of a tile) of the global->LDS loads of tile kt+3; a scheduling
-  // fence after every group keeps that interleaving, so memory instructions issue in the shadow of
-  // the MFMAs instead of in bursts.
-  // `mem(j)` is called for j = 0 .. JN-1, spread evenly over the MFMA pairs: it issues the j-th
-  // direct-to-LDS load of this half.
-  auto half = [&](auto jn, const Frags& fc, Frags& fn, const uint16_t* sb_next, int kk_next, auto&& mem) {
-    constexpr int NM = TM * TN;
+  // One half.  The 16x16x32 instruction, not 32x32x16: under the chip's power limit it sustains 15 % more with
+  // N(0,1)-like operands (registers only: 2.17 against 1.88 PFLOP/s; the same 2.4 with zeros), and the tiles are
+  // walked back and forth so that consecutive instructions share an operand.  It also leaves only 16 cycles between
+  // two of them, room for about three other instructions, so the next half's fragment reads and (in the second half
+  // of a tile) the global->LDS loads of a later tile are dealt out one at a time, never at the same place: in
+  // clumps after every four matrix instructions the 256x256 kernel was 2 % slower.  The reads come first needed
+  // first and end three quarters into the half, so that the barrier (or the next half) does not wait for the last.
+  // A scheduling fence after every group keeps that interleaving.  (256x256 prefers groups of one, the rest of two.)
+  // `last` marks the last k-tile.  `mem(j)` is called for j = 0 .. JN-1: it issues the j-th direct-to-LDS load.
+  auto half = [&](auto jn, auto last, const Frags& fc, Frags& fn, const uint16_t* sb_next, int ks_next, auto&& mem) {
+    constexpr int NM = TM * TN, GRP = NM >= 64 ? 1 : 2, NG = NM / GRP, NGR = NG > 4 ? NG * 3 / 4 : NG;
+    static_assert(NM % GRP == 0, "whole groups");
     constexpr int JN = decltype(jn)::value;
+    auto reads_by = [](int g) { return (g < NGR ? g : NGR) * NR / NGR; };           // fragment reads due before group g
+    auto loads_by = [](int g) { return (g + 2 < NG ? (g > 0 ? g + 2 : 0) : NG) * JN / NG; };
 #pragma unroll
-    for (int i = 0; i < NM; ++i) {
-      const int a = i / TM, b = i % TM;
-      acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fc.w[0][a]),
-                                                          __builtin_bit_cast(bf16x8, fc.x[0][b]), acc[a][b], 0, 0, 0);
-      acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fc.w[1][a]),
-                                                          __builtin_bit_cast(bf16x8, fc.x[1][b]), acc[a][b], 0, 0, 0);
+    for (int g = 0; g < NG; ++g) {
 #pragma unroll
-      for (int r = i * NR / NM; r < (i + 1) * NR / NM; ++r) frag_read(fn, sb_next, kk_next, r);
+      for (int q = g * GRP; q < (g + 1) * GRP; ++q) {
+        const int a = q / TM, b = (a & 1) ? TM - 1 - q % TM : q % TM;
+        if constexpr (NM >= 64)
+          mfma_acc<decltype(last)::value>(acc[a][b], fc.w[a], fc.x[b]);
+        else
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fc.w[a]),
+                                                              __builtin_bit_cast(bf16x8, fc.x[b]), acc[a][b], 0, 0, 0);
+      }
 #pragma unroll
-      for (int j = i * JN / NM; j < (i + 1) * JN / NM; ++j) mem(j);
+      for (int r = reads_by(g); r < reads_by(g + 1); ++r) frag_read(fn, sb_next, ks_next, r);
+#pragma unroll
+      for (int j = loads_by(g); j < loads_by(g + 1); ++j) mem(j);
       __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (NM >= 64 && !decltype(last)::value) asm volatile("s_nop 7");   // moves at the loop's exit (mfma_acc)
   };
   using none = std::integral_constant<int, 0>;
   using all_loads = std::integral_constant<int, LPS>;
@@ -269,18 +302,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   // lanes fall into distinct banks.
   constexpr int LDS_FLOATS = gemm_lds_bytes(BM, BN, STAGES) / 4;
   constexpr int GA_FIT = (LDS_FLOATS / (NW * WTM) - 4) / 32;
-  constexpr int GA = GA_FIT < TN ? GA_FIT : TN;
+  constexpr int TG = WTN / 32;  // groups of 32 columns of a wave tile
+  constexpr int GA = GA_FIT < TG ? GA_FIT : TG;
   static_assert(GA >= 1, "no room to stage the epilogue");
   constexpr int RSTR = GA * 32 + 4;  // staging row stride in floats
   constexpr int MAX_ITERS = WTM * GA * 4 / 64;
-  constexpr int NPASS = (TN + GA - 1) / GA;
+  constexpr int NPASS = (TG + GA - 1) / GA;
   const int row_base = m0 + wm * WTM;
   const int col_base = n0 + wn * WTN;
   // Pass `a0/GA` covers column tiles a0 .. a0+ga-1; after the LDS transposition lane `idx = it*64+lane`
   // owns row idx / cpr, 8-column chunk idx % cpr (cpr = 4*ga chunks per row).
   u32x4 epi_res[2][MAX_ITERS], epi_bias[2][MAX_ITERS];
   auto epi_prefetch = [&](int a0, u32x4* resv, u32x4* biasv) {
-    const int ga = (TN - a0) < GA ? (TN - a0) : GA;
+    const int ga = (TG - a0) < GA ? (TG - a0) : GA;
     const int cpr = ga * 4;
     const int iters = WTM * cpr / 64;
 #pragma unroll
@@ -314,7 +348,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
 #pragma unroll
     for (int st = 0; st < STAGES; ++st) issue(st, st);
     wait_vmcnt<(STAGES - 1) * LPS>();
-    __syncthreads();
+    lds_barrier();
     DS_STAMP(1);
 #pragma unroll
     for (int r = 0; r < NR; ++r) frag_read(fa, lds, 0, r);
@@ -326,24 +360,24 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
       if (nstage == STAGES) nstage = 0;
       const uint16_t* sbn = lds + nstage * STAGE_ELEMS;
       __builtin_amdgcn_sched_barrier(0);
-      half(none{}, fa, fb, sb, 2, no_mem);
+      half(none{}, std::false_type{}, fa, fb, sb, 1, no_mem);
       wait_vmcnt<(STAGES - 2) * LPS>();
-      __syncthreads();
-      half(all_loads{}, fb, fa, sbn, 0, [&](int j) { issue_one(stage, kt + STAGES, j); });
+      lds_barrier();
+      half(all_loads{}, std::false_type{}, fb, fa, sbn, 0, [&](int j) { issue_one(stage, kt + STAGES, j); });
       stage = nstage;
     }
     // Last k-tile (already in LDS and visible since the previous iteration's barrier): no loads, no
     // waits.  The residual and bias pieces of the first epilogue pass are requested before it, so
     // their memory latency passes while the matrix pipe still has work.
     // (only where the register file has room for them next to the accumulators and both fragment sets)
-    constexpr bool EARLY_EPI = TM * TN <= 10;
+    constexpr bool EARLY_EPI = TM * TN <= 40;
     if (EARLY_EPI) epi_prefetch(0, epi_res[0], epi_bias[0]);
     {
       const uint16_t* sb = lds + stage * STAGE_ELEMS;
       __builtin_amdgcn_sched_barrier(0);
-      half(none{}, fa, fb, sb, 2, no_mem);
+      half(none{}, std::true_type{}, fa, fb, sb, 1, no_mem);
       // (the fragment fetch of this half reads a buffer of clamped re-loads; the values are never used)
-      half(none{}, fb, fa, sb, 0, no_mem);
+      half(none{}, std::true_type{}, fb, fa, sb, 0, no_mem);
     }
     if (!EARLY_EPI) epi_prefetch(0, epi_res[0], epi_bias[0]);
     wait_vmcnt<0>();  // the clamped re-loads of the loop tail must not land in the epilogue's staging area
@@ -360,24 +394,18 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
 #pragma unroll
   for (int pass = 0; pass < NPASS; ++pass) {
     const int a0 = pass * GA;
-    const int ga = (TN - a0) < GA ? (TN - a0) : GA;  // column tiles in this pass (compile-time after unrolling)
+    const int ga = (TG - a0) < GA ? (TG - a0) : GA;  // column tiles in this pass (compile-time after unrolling)
     u32x4* resv = epi_res[pass & 1];
     u32x4* biasv = epi_bias[pass & 1];
     // the next pass's residual / bias pieces travel while this pass is transposed and stored
     if (pass + 1 < NPASS) epi_prefetch(a0 + GA, epi_res[(pass + 1) & 1], epi_bias[(pass + 1) & 1]);
-    // 1. accumulators -> LDS (transposing): lane holds rows b*32 + lane%32, columns a*32 + 8g + 4*(lane/32) + 0..3
+    // 1. accumulators -> LDS (transposing): lane holds row 16 b + lane%16, columns 16 a + 4*(lane/16) + 0..3
 #pragma unroll
-    for (int a = 0; a < GA; ++a) {
-      if (a >= ga) break;
+    for (int a = 0; a < 2 * GA; ++a) {
+      if (a >= 2 * ga) break;
 #pragma unroll
       for (int b = 0; b < TM; ++b)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          floatx4 v;
-          v[0] = acc[a0 + a][b][4 * g + 0]; v[1] = acc[a0 + a][b][4 * g + 1];
-          v[2] = acc[a0 + a][b][4 * g + 2]; v[3] = acc[a0 + a][b][4 * g + 3];
-          *reinterpret_cast<floatx4*>(stg + (b * 32 + (lane & 31)) * RSTR + a * 32 + g * 8 + (lane >> 5) * 4) = v;
-        }
+        *reinterpret_cast<floatx4*>(stg + (b * 16 + (lane & 15)) * RSTR + a * 16 + (lane >> 4) * 4) = acc[2 * a0 + a][b];
     }
     // 2. read back row-contiguous: chunk = 8 columns; cpr chunks per row
     const int cpr = ga * 4;

@@ -1,0 +1,28 @@
+"""The tile GEMM's workgroup order: with 16 or more row tiles the workgroups that run together take 16 x 16 patches,
+one block of 8 x 4 tiles per chip partition.  Every output tile has to be computed exactly once, whatever the number
+of row and column tiles (whole patches, a ragged last group of rows, fewer columns than a patch)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ds_oracle as orc
+from paper_2401_09670_amd import synth
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,in_f,out_f", [(4096, 64, 4096), (4100, 128, 4104), (8200, 64, 1288), (5000, 64, 2560),
+                                             (4352, 192, 768)])
+def test_linear_many_row_tiles(gpu, rows, in_f, out_f):
+    ctx = gu.make_ctx(synth.TINY)
+    x, w = gu.dev_normal_bits((rows, in_f), 1.0, 11 + rows), gu.dev_normal_bits((out_f, in_f), 0.05, 12 + out_f)
+    y = torch.full((rows + 1, out_f), 7.0, dtype=torch.bfloat16, device="cuda")
+    ws = gu.workspace(ctx.ds_linear_workspace_bytes(rows, in_f, out_f))
+    ctx.ds_linear(x, w, None, None, 0, rows, in_f, out_f, y, ws)
+    torch.cuda.synchronize()
+    got = gu.to_f64(y)
+    ref = orc.linear(gu.to_f64(x), gu.to_f64(w), None)
+    assert np.all(got[rows] == 7.0), "wrote past the last row"
+    # one bf16 rounding of the result (2^-9) and fp32 sums of at most 192 products, relative to the largest value
+    assert float(np.max(np.abs(got[:rows] - ref))) <= 2.0 ** -8 * float(np.max(np.abs(ref)))
