@@ -59,4 +59,8 @@ __device__ __forceinline__ float wave_max(float v) {
 __device__ __forceinline__ u32x4 ld16(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
 __device__ __forceinline__ void st16(void* p, u32x4 v) { *reinterpret_cast<u32x4*>(p) = v; }
 
+// Workgroup barrier that closes this wave's LDS reads and leaves its direct-to-LDS loads in flight (behind
+// __syncthreads() the compiler may wait for all of them).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 }  // namespace ds

@@ -133,10 +133,6 @@ __device__ __forceinline__ void mfma_acc(floatx4& acc, const u32x4& w, const u32
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
 }
 
-// Workgroup barrier that closes this wave's LDS reads and leaves its direct-to-LDS loads in flight (behind
-// __syncthreads() the compiler may wait for all of them).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // EPI selects the epilogue at compile time, so the plain prefill instantiation carries none of the
 // decode-side code: 0 = bias / ReLU / residual -> bf16 segments; 1 = split-K, raw fp32 partials;
 // 2 = as 0, but the K and V thirds go into the paged cache.

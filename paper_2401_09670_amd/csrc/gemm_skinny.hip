@@ -21,11 +21,11 @@
 // bytes.
 //
 // grid = (N/BN, KSPLIT).  Workgroup = 8 waves: wave w owns the column tiles
-// (16 weight rows each) of column group w & 3 and, of every 128-wide k slab,
-// the two 32-wide MFMA k-steps 2*(w>>2), 2*(w>>2)+1; the two k-halves are
+// (16 weight rows each) of column group w & 3 and, of every 64-wide k slab,
+// the 32-wide MFMA k-step w >> 2; the two k-halves are
 // added through LDS at the end.  Both operands go global -> LDS directly (no
 // registers, no ds_write) into a ring of S stages; a wave-level load fetches
-// 4 rows x 256 contiguous bytes.  The tile is computed transposed (weights
+// 8 rows x 128 contiguous bytes.  The tile is computed transposed (weights
 // as MFMA row operand), so a lane ends up with 4 consecutive output columns
 // of one row.  With KSPLIT > 1 each split writes fp32 partial sums and a
 // second kernel adds them in a fixed order and applies the epilogue.
@@ -40,7 +40,7 @@ namespace ds {
 constexpr int kWeightAux = 2;
 constexpr int kSkThreads = 512;
 constexpr int kSkWaves = kSkThreads / 64;
-constexpr int kSkKS = 128;  // k elements per slab
+constexpr int kSkKS = 64;  // k elements per slab
 
 struct SkinnyParams {
   const uint16_t* X;
@@ -72,24 +72,43 @@ __device__ __forceinline__ void sk_wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((VM & 0xf) | (0x7 << 4) | (0xf << 8) | ((VM >> 4) << 14));
 }
 
+// Which of its ns slabs (slab_stride elements apart) a workgroup starts with; it goes round from there.  Where the row
+// stride is a multiple of 4 KB, the pieces that all rows have at one position of K lie on few memory channels, and
+// workgroups in lockstep wait for these (32768 x 8192, 48 rows: 123 us, 91 with this; 49152 x 12288, 64 rows: 218 and
+// 214).  So each XCD (id % 8) starts at an eighth of its own, and its 32 workgroups are spread over as many slabs as
+// their activations keep in the XCD's L2 (spread over all of K, 128 rows of 5120 x 20480 take 65 us, not 56).  Other
+// strides spread by themselves, and rows in step share DRAM pages (5120 x 5120, 64 rows: 18.8 us in step, 20 spread).
+__device__ __forceinline__ int start_slab(unsigned id, int ns, int slab_stride, int rows, int K) {
+  if (K % 2048 != 0) return 0;
+  const int in_l2 = (1 << 20) / (rows * slab_stride);  // slabs whose activations take 2 MB
+  const int window = in_l2 < ns ? in_l2 : ns;
+  return (int)(((id & 7) * (unsigned)ns / 8 + ((id >> 3) & 31) * (unsigned)window / 32) % (unsigned)ns);
+}
+
 // MT = activation row tiles of 16 (4, 8, 16); NTW = column tiles per wave (1, 2, 4: BN = 64 * NTW);
 // S = LDS stages (prefetch distance D = S - 1).
 //
-// Stage layout: [MP rows of X | BN rows of W], every row 128 k-elements = 256 B = 16 chunks of
-// 16 B, unpadded; chunk c of row r sits at position c ^ (r & 15), so the 16 consecutive rows a
-// fragment read touches fall into 16 different bank groups.  The swizzle is applied on the global
-// side: lane l of a wave-level load fetches row 4g + l/16, chunk (l%16) ^ (row & 15).
+// Stage layout: [MP rows of X | BN rows of W], every row 64 k-elements = 128 B = 8 chunks of
+// 16 B, unpadded; chunk c of row r sits at position c ^ ((r >> 1) & 7), so the 16 consecutive rows a
+// fragment read touches spread over all banks.  The swizzle is applied on the global
+// side: lane l of a wave-level load fetches row 8g + l/8, chunk (l%8) ^ ((row >> 1) & 7).
+//
+// What bounds it: bytes on their way from HBM, so the ring holds as many small stages as the LDS has room for (160 KB of
+// 16 to 40 KB each) and the loop never drains it - behind __syncthreads() the compiler waits for every load in
+// flight, which with 128-element slabs in two or three stages left a gap per slab.  Per product, reduce pass
+// included: 5120 x 5120 at 1 row 18.5 -> 14.3 us, at 64 rows 20.5 -> 18.9; 5120 x 20480 at 1 row 45.7 -> 39.5, at 64
+// rows 51.4 -> 47; 32768 x 8192 at 48 rows 127 -> 91 (5.9 TB/s of weights); 12288 x 49152 at 128 rows 326 -> 302.
 template <int MT, int NTW, int S>
 __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyParams p) {
   constexpr int MP = MT * 16;   // padded activation rows held in LDS
   constexpr int BN = 64 * NTW;  // weight rows per workgroup
   constexpr int D = S - 1;      // slabs in flight ahead of the one being multiplied
   constexpr int STAGE_ELEMS = (MP + BN) * kSkKS;
-  constexpr int GROUPS = (MP + BN) / 4;  // wave-level loads (4 rows each) per slab
-  static_assert(GROUPS % kSkWaves == 0, "every wave issues the same number of loads");
+  constexpr int GROUPS = (MP + BN) / 8;  // wave-level loads (8 rows each) per slab
+  static_assert(GROUPS % kSkWaves == 0 && MP % (8 * kSkWaves) == 0, "every wave issues the same number of loads");
   constexpr int G = GROUPS / kSkWaves;  // loads per wave per slab
   static_assert(D >= 1 && (D - 1) * G < 64, "vmcnt range");
-  extern __shared__ __attribute__((aligned(1024))) uint16_t lds[];  // [S][MP + BN][128]
+  extern __shared__ __attribute__((aligned(1024))) uint16_t lds[];  // [S][MP + BN][64]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
@@ -97,28 +116,39 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
   const int n0 = blockIdx.x * BN;
   const int split = blockIdx.y;
   const int n_splits = gridDim.y;
-  // The K axis is dealt to the splits slab by slab (split s takes slabs s, s + KSPLIT, ...).
+  // The K axis is dealt to the splits slab by slab: split s takes number s of every group of n_splits slabs.  With a
+  // multiple of 4 splits it takes number (s + i) % n_splits of group i instead, or it would meet only every fourth
+  // 128-byte piece of a row, a fraction of the memory channels (8192 x 32768, 48 rows, 8 splits: 118 -> 93 us; other
+  // split counts meet all of them anyway and lose up to 10 % by the turning).
   const int slabs_total = p.K / kSkKS;
-  const int ns = (slabs_total - split + n_splits - 1) / n_splits;  // >= 1: n_splits <= slabs_total
+  const int whole = slabs_total / n_splits;  // >= 1: n_splits <= slabs_total
+  const int turn_by = (n_splits & 3) == 0 ? 1 : 0;
+  const int ns = whole + ((split + whole * turn_by) % n_splits < slabs_total - whole * n_splits ? 1 : 0);
   const int K = p.K;
+  const int rot = start_slab(blockIdx.x + gridDim.x * split, ns, n_splits * kSkKS, p.M, K);
 
-  // load j of this wave is row group g = j*8 + wave of the stage (4 rows): X rows first, then W rows
-  const int lr = lane >> 4;
+  // load j of this wave is row group g = j*8 + wave of the stage (8 rows): X rows first, then W rows
+  const int lr = lane >> 3;
   const uint16_t* src[G];
 #pragma unroll
   for (int j = 0; j < G; ++j) {
-    const int r = 4 * (j * kSkWaves + wave) + lr;  // stage row
-    const int sw = ((lane & 15) ^ (r & 15)) * 8;
-    if (r < MP) src[j] = p.X + (size_t)min(r, p.M - 1) * K + (size_t)split * kSkKS + sw;
-    else src[j] = p.W + (size_t)min(n0 + r - MP, p.N - 1) * K + (size_t)split * kSkKS + sw;
+    const int r = 8 * (j * kSkWaves + wave) + lr;  // stage row
+    const int sw = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+    if (r < MP) src[j] = p.X + (size_t)min(r, p.M - 1) * K + sw;
+    else src[j] = p.W + (size_t)min(n0 + r - MP, p.N - 1) * K + sw;
   }
-  // requests slab i (clamped to the last real slab: a harmless re-load) into stage `st`
-  auto request = [&](int i, int st) {
-    const int ofs = min(i, ns - 1) * n_splits * kSkKS;
-    uint16_t* dst = lds + st * STAGE_ELEMS + wave_s * 512;  // one wave-load = 4 rows = 1 KB = 512 elements
+  // requests the next slab of this split (the last one again when none is left: a harmless re-load) into stage `st`
+  int group = rot, turn = (split + rot * turn_by) % n_splits, left = ns;
+  auto request = [&](int st) {
+    const int ofs = (group * n_splits + turn) * kSkKS;
+    if (--left > 0) {
+      turn = turn + turn_by == n_splits ? 0 : turn + turn_by;
+      if (++group == ns) group = 0, turn = split;
+    }
+    uint16_t* dst = lds + st * STAGE_ELEMS + wave_s * 512;  // one wave-load = 8 rows = 1 KB = 512 elements
 #pragma unroll
     for (int j = 0; j < G; ++j) {
-      if (j < MP / (4 * kSkWaves))  // activation rows
+      if (j < MP / (8 * kSkWaves))  // activation rows
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[j] + ofs),
                                          (__attribute__((address_space(3))) void*)(dst + j * kSkWaves * 512), 16,
                                          0, 0);
@@ -135,37 +165,30 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
 #pragma unroll
     for (int t = 0; t < MT; ++t) acc[a][t] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-  // fragment read offsets of this wave's two k-steps: lane (row = lane%16, kq = lane/16) reads
-  // chunk 4*step + kq of its row
-  int fo[2];
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
-    fo[s] = (lane & 15) * kSkKS + (((4 * (2 * kh + s) + (lane >> 4)) ^ (lane & 15)) * 8);
+  // fragment read offset of this wave's k-step: lane (row = lane%16, kq = lane/16) reads chunk 4*step + kq of its row
+  const int fo = (lane & 15) * kSkKS + (((4 * kh + (lane >> 4)) ^ (((lane & 15) >> 1) & 7)) * 8);
   const int wfrag0 = (MP + ng * NTW * 16) * kSkKS;
 
 #pragma unroll
-  for (int d = 0; d < D; ++d) request(d, d);
+  for (int d = 0; d < D; ++d) request(d);
 
   int st = 0;      // stage of slab i
   int st_req = D;  // stage slab i+D goes to (= the stage slab i-1 used)
   for (int i = 0; i < ns; ++i) {
     sk_wait_vmcnt<(D - 1) * G>();  // this wave's part of slab i has landed
-    __syncthreads();               // slab i visible to all waves; everyone is done with slab i-1
-    request(i + D, st_req);
+    lds_barrier();                 // slab i visible to all waves; everyone is done with slab i-1
+    request(st_req);
     const uint16_t* sb = lds + st * STAGE_ELEMS;
+    u32x4 xf[MT];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      u32x4 xf[MT];
+    for (int t = 0; t < MT; ++t) xf[t] = *reinterpret_cast<const u32x4*>(sb + t * 16 * kSkKS + fo);
 #pragma unroll
-      for (int t = 0; t < MT; ++t) xf[t] = *reinterpret_cast<const u32x4*>(sb + t * 16 * kSkKS + fo[s]);
+    for (int a = 0; a < NTW; ++a) {
+      const u32x4 wf = *reinterpret_cast<const u32x4*>(sb + wfrag0 + a * 16 * kSkKS + fo);
 #pragma unroll
-      for (int a = 0; a < NTW; ++a) {
-        const u32x4 wf = *reinterpret_cast<const u32x4*>(sb + wfrag0 + a * 16 * kSkKS + fo[s]);
-#pragma unroll
-        for (int t = 0; t < MT; ++t)
-          acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf),
-                                                              __builtin_bit_cast(bf16x8, xf[t]), acc[a][t], 0, 0, 0);
-      }
+      for (int t = 0; t < MT; ++t)
+        acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf),
+                                                            __builtin_bit_cast(bf16x8, xf[t]), acc[a][t], 0, 0, 0);
     }
     st_req = st;
     st = (st + 1 == S) ? 0 : st + 1;
@@ -320,6 +343,7 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
   const int K = p.K;
   const int slabs_total = K / kWrKS;
   const int ns = (slabs_total - wave + NW - 1) / NW;  // this wave's slabs: wave, wave + NW, ...  (>= 1: K >= 256)
+  const int rot = start_slab(blockIdx.x, ns, NW * kWrKS, p.M, K);
 
   // load j of a slab covers stage rows 8j .. 8j+7 (rows 0..BM-1 = X, then W); lane: row 8j + lane/8,
   // 16-byte chunk (lane%8) ^ ((row >> 1) & 7) - the swizzle that makes the fragment reads conflict-free
@@ -333,7 +357,8 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
   }
   uint16_t* ring = lds + wave * S * kWrStageElems;
   auto request = [&](int i, int st) {  // this wave's slab i (clamped: a harmless re-load) into its stage st
-    const int ofs = min(i, ns - 1) * NW * kWrKS;
+    const int at = min(i, ns - 1) + rot;
+    const int ofs = (at < ns ? at : at - ns) * NW * kWrKS;
     uint16_t* dst = ring + st * kWrStageElems;
 #pragma unroll
     for (int j = 0; j < kWrLoads; ++j) {
@@ -658,7 +683,7 @@ struct SkinnyPlan {
 //   weights + (N/BN) * X (each column block re-reads the activations) + partial sums written and
 //   read back.
 static SkinnyPlan skinny_plan(int M, int N, int K, bool allow_split = true, double* cost_out = nullptr) {
-  const int slabs = K / kSkKS;
+  const int slabs = K / 128;
   const int mp = M <= 64 ? 64 : (M <= 128 ? 128 : 256);
   SkinnyPlan best{1, 1};
   double best_cost = 1e300;
@@ -694,7 +719,7 @@ static SkinnyPlan skinny_plan(int M, int N, int K, bool allow_split = true, doub
 }
 
 size_t skinny_workspace_bytes(int M, int N, int K) {
-  if (K % kSkKS != 0 || M > 256) return 0;
+  if (K % 128 != 0 || M > 256) return 0;
   const SkinnyPlan pl = skinny_plan(M, N, K);  // (also covers the shapes the unsplit kernel takes)
   return pl.splits > 1 ? (size_t)pl.splits * M * N * sizeof(float) : 0;
 }
@@ -757,8 +782,11 @@ static int wring_tiles(int M, int N, int K) {
   // its bytes (in skinny_plan's terms, reduce launch included) are clearly fewer.  Measured at 64 rows: FFN-in of
   // OPT-175B 245 -> 214 us, QKV of OPT-66B 107 -> 98 us; QKV of OPT-175B and FFN-in of OPT-66B (two rounds of 80
   // columns against 144 workgroups of 256) stay here, 6-9 % ahead.
+  // A single round that leaves a fifth of the chip idle is compared the same way (64 rows: 12288 x 49152 on 192
+  // workgroups 278 us, 48 x 5 split 205; 12288 x 12288 76 and 61; 48 rows of 10240 x 8192 on 160 42.3 and 36.0; but
+  // 15360 x 5120 on 240 34.8 and 38).
   const int rounds = nt == 5 ? r5 : r4;
-  if (rounds > 1 && M > 16 && g_skinny_wring != 2) {
+  if ((rounds > 1 || tiles < 208) && M > 16 && g_skinny_wring != 2) {
     const double rows = M <= 32 ? 32 : (M <= 64 ? 64 : 128);
     const double wring_cost = rounds * 256.0 * (16.0 * nt + rows) * K * 2.0;
     double ring_cost;
@@ -771,22 +799,22 @@ static int wring_tiles(int M, int N, int K) {
 static hipError_t dispatch_skinny(const SkinnyParams& p, const SkinnyPlan& pl, hipStream_t stream) {
   // fewer than 64 rows run as 64 (clamped duplicates; the matrix cores are idle anyway)
   if (p.M <= 64) {
-    if (pl.ntw == 4) return launch_skinny_cfg<4, 4, 2>(p, pl.splits, stream);  // 160 KB
-    if (pl.ntw == 2) return launch_skinny_cfg<4, 2, 3>(p, pl.splits, stream);  // 144 KB
-    return launch_skinny_cfg<4, 1, 2>(p, pl.splits, stream);                   //  64 KB
+    if (pl.ntw == 4) return launch_skinny_cfg<4, 4, 4>(p, pl.splits, stream);  // 160 KB
+    if (pl.ntw == 2) return launch_skinny_cfg<4, 2, 6>(p, pl.splits, stream);  // 144 KB
+    return launch_skinny_cfg<4, 1, 8>(p, pl.splits, stream);                   // 128 KB
   }
   if (p.M <= 128) {
-    if (pl.ntw == 2) return launch_skinny_cfg<8, 2, 2>(p, pl.splits, stream);  // 128 KB
-    return launch_skinny_cfg<8, 1, 3>(p, pl.splits, stream);                   // 144 KB
+    if (pl.ntw == 2) return launch_skinny_cfg<8, 2, 5>(p, pl.splits, stream);  // 160 KB
+    return launch_skinny_cfg<8, 1, 6>(p, pl.splits, stream);                   // 144 KB
   }
-  return launch_skinny_cfg<16, 1, 2>(p, pl.splits, stream);                    // 160 KB
+  return launch_skinny_cfg<16, 1, 4>(p, pl.splits, stream);                    // 160 KB
 }
 
 hipError_t launch_argmax_merge(const float* part_val, const int32_t* part_idx, int n_blocks, int M,
                                int32_t* next_token, float* best_logit, hipStream_t stream);
 
 size_t skinny_argmax_workspace_bytes(int M, int N, int K) {
-  if (K % kSkKS != 0 || M > 256 || M <= 0 || N <= 0) return 0;
+  if (K % 128 != 0 || M > 256 || M <= 0 || N <= 0) return 0;
   const SkinnyPlan pl = skinny_plan(M, N, K, false);
   const size_t blocks = (size_t)(N + 64 * pl.ntw - 1) / (64 * pl.ntw);
   return blocks * M * (sizeof(float) + sizeof(int32_t));
@@ -794,7 +822,7 @@ size_t skinny_argmax_workspace_bytes(int M, int N, int K) {
 
 hipError_t launch_skinny_argmax(const void* X, const void* W, int M, int N, int K, void* workspace,
                                 int32_t* next_token, float* best_logit, hipStream_t stream) {
-  if (M <= 0 || M > 256 || N <= 0 || K % kSkKS != 0 || !workspace || !next_token) return hipErrorInvalidValue;
+  if (M <= 0 || M > 256 || N <= 0 || K % 128 != 0 || !workspace || !next_token) return hipErrorInvalidValue;
   const SkinnyPlan pl = skinny_plan(M, N, K, false);
   const int blocks = (N + 64 * pl.ntw - 1) / (64 * pl.ntw);
   SkinnyParams p;
@@ -875,7 +903,7 @@ hipError_t launch_skinny_gemm(const void* X, const void* W, int M, int N, int K,
                               void* workspace, hipStream_t stream, const SkinnyFused* fused, bool* fused_done) {
   if (fused_done) *fused_done = false;
   if (M <= 0 || N <= 0) return hipSuccess;
-  if (M > 256 || K % kSkKS != 0 || N % 8 != 0 || ep.seg_cols <= 0 || ep.seg_cols % 8 != 0 || ep.seg_cols_kv < 0 ||
+  if (M > 256 || K % 128 != 0 || N % 8 != 0 || ep.seg_cols <= 0 || ep.seg_cols % 8 != 0 || ep.seg_cols_kv < 0 ||
       ep.seg_cols_kv % 8 != 0)
     return hipErrorInvalidValue;
   if (ep.residual && ep.seg_cols != N) return hipErrorInvalidValue;
