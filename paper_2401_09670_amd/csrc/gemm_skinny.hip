@@ -467,21 +467,24 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
   }
 }
 
-// Sum of the split partials of 8 consecutive columns of row m, added in split order; the loads of four
-// splits are issued together (the reduce passes are latency-bound).
-__device__ __forceinline__ void sum_partials8(const SkinnyParams& p, int n_splits, int m, int n, float v[8]) {
+// Sum of the split partials of 8 consecutive columns of row m, added in split order.  The reduce passes are bound by
+// latency, one round trip after another: the loads of up to U splits are issued together, and what the epilogue needs
+// besides is requested before them (epi_load) instead of after the sum.  64 rows of 5120: 4.7 -> 4.5 us, with
+// LayerNorm 5.7 -> 5.2; decode step of OPT-13B at 1 row 130.7 -> 129.8, at 64 rows 268.9 -> 267.3.
+template <int U>
+__device__ __forceinline__ void sum_partials8_by(const SkinnyParams& p, int n_splits, int m, int n, float v[8]) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) v[j] = 0.f;
-  for (int s0 = 0; s0 < n_splits; s0 += 4) {
-    floatx4 a[4], b[4];
+  for (int s0 = 0; s0 < n_splits; s0 += U) {
+    floatx4 a[U], b[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < U; ++u) {
       const float* src = p.partial + ((size_t)min(s0 + u, n_splits - 1) * p.M + m) * p.N + n;
       a[u] = *reinterpret_cast<const floatx4*>(src);
       b[u] = *reinterpret_cast<const floatx4*>(src + 4);
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < U; ++u) {
       if (s0 + u < n_splits) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -493,21 +496,29 @@ __device__ __forceinline__ void sum_partials8(const SkinnyParams& p, int n_split
   }
 }
 
-// Sum the split partials in split order, then bias / ReLU / residual, 8 columns per thread.
-__global__ __launch_bounds__(256) void skinny_reduce_kernel(const SkinnyParams p, int n_splits) {
-  const int chunks_per_row = p.N >> 3;
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (long)p.M * chunks_per_row) return;
-  const int m = (int)(idx / chunks_per_row);
-  const int n = (int)(idx % chunks_per_row) * 8;
-  float v[8];
-  sum_partials8(p, n_splits, m, n, v);
+__device__ __forceinline__ void sum_partials8(const SkinnyParams& p, int n_splits, int m, int n, float v[8]) {
+  if (n_splits <= 4) sum_partials8_by<4>(p, n_splits, m, n, v);
+  else sum_partials8_by<8>(p, n_splits, m, n, v);
+}
+
+// Bias and residual of 8 columns.  An absent operand is read from the partials instead and not used: a branch around
+// the load would end in a wait for it.
+struct EpiPieces {
+  u32x4 bias, res;
+};
+__device__ __forceinline__ EpiPieces epi_load(const SkinnyParams& p, int m, int n) {
+  const uint16_t* any = reinterpret_cast<const uint16_t*>(p.partial);
+  EpiPieces e;
+  e.bias = ld16((p.bias ? p.bias : any) + n);
+  e.res = ld16((p.residual ? p.residual : any) + (size_t)m * p.N + n);
+  return e;
+}
+__device__ __forceinline__ void epi_apply(const SkinnyParams& p, const EpiPieces& e, float v[8]) {
   if (p.bias) {
-    const u32x4 bb = ld16(p.bias + n);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      v[2 * j] += bf16_lo(bb[j]);
-      v[2 * j + 1] += bf16_hi(bb[j]);
+      v[2 * j] += bf16_lo(e.bias[j]);
+      v[2 * j + 1] += bf16_hi(e.bias[j]);
     }
   }
   if (p.relu) {
@@ -515,13 +526,25 @@ __global__ __launch_bounds__(256) void skinny_reduce_kernel(const SkinnyParams p
     for (int j = 0; j < 8; ++j) v[j] = fmaxf(v[j], 0.f);
   }
   if (p.residual) {
-    const u32x4 rr = ld16(p.residual + (size_t)m * p.N + n);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      v[2 * j] += bf16_lo(rr[j]);
-      v[2 * j + 1] += bf16_hi(rr[j]);
+      v[2 * j] += bf16_lo(e.res[j]);
+      v[2 * j + 1] += bf16_hi(e.res[j]);
     }
   }
+}
+
+// Sum the split partials in split order, then bias / ReLU / residual, 8 columns per thread.
+__global__ __launch_bounds__(256) void skinny_reduce_kernel(const SkinnyParams p, int n_splits) {
+  const int chunks_per_row = p.N >> 3;
+  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= (long)p.M * chunks_per_row) return;
+  const int m = (int)(idx / chunks_per_row);
+  const int n = (int)(idx % chunks_per_row) * 8;
+  const EpiPieces e = epi_load(p, m, n);
+  float v[8];
+  sum_partials8(p, n_splits, m, n, v);
+  epi_apply(p, e, v);
   const int seg = (n >= p.seg_cols) + (n >= p.seg_cols + p.seg_cols_kv);
   const int ld = seg == 0 ? p.seg_cols : p.seg_cols_kv;
   const int first = seg == 0 ? 0 : p.seg_cols + (seg - 1) * p.seg_cols_kv;
@@ -546,6 +569,15 @@ __global__ __launch_bounds__(kRedLnThreads) void skinny_reduce_ln_kernel(const S
   __shared__ float red[kRedLnThreads / 64];
   const int m = blockIdx.x;
   const int nchunk = p.N >> 3;
+  EpiPieces e[NCH];
+  u32x4 gam[NCH], bet[NCH];
+#pragma unroll
+  for (int i = 0; i < NCH; ++i) {
+    const int c = min((int)threadIdx.x + i * kRedLnThreads, nchunk - 1);
+    e[i] = epi_load(p, m, c * 8);
+    gam[i] = ld16(gamma + c * 8);
+    bet[i] = ld16(beta + c * 8);
+  }
   float vals[NCH][8];
   float sum = 0.f;
 #pragma unroll
@@ -555,26 +587,7 @@ __global__ __launch_bounds__(kRedLnThreads) void skinny_reduce_ln_kernel(const S
       const int n = c * 8;
       float v[8];
       sum_partials8(p, n_splits, m, n, v);
-      if (p.bias) {
-        const u32x4 bb = ld16(p.bias + n);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          v[2 * j] += bf16_lo(bb[j]);
-          v[2 * j + 1] += bf16_hi(bb[j]);
-        }
-      }
-      if (p.relu) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = fmaxf(v[j], 0.f);
-      }
-      if (p.residual) {
-        const u32x4 rr = ld16(p.residual + (size_t)m * p.N + n);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          v[2 * j] += bf16_lo(rr[j]);
-          v[2 * j + 1] += bf16_hi(rr[j]);
-        }
-      }
+      epi_apply(p, e[i], v);
       u32x4 ov;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -614,13 +627,11 @@ __global__ __launch_bounds__(kRedLnThreads) void skinny_reduce_ln_kernel(const S
   for (int i = 0; i < NCH; ++i) {
     const int c = threadIdx.x + i * kRedLnThreads;
     if (c < nchunk) {
-      const u32x4 g = ld16(gamma + c * 8);
-      const u32x4 b = ld16(beta + c * 8);
       u32x4 o;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float lo = (vals[i][2 * j] - mean) * rstd * bf16_lo(g[j]) + bf16_lo(b[j]);
-        const float hi = (vals[i][2 * j + 1] - mean) * rstd * bf16_hi(g[j]) + bf16_hi(b[j]);
+        const float lo = (vals[i][2 * j] - mean) * rstd * bf16_lo(gam[i][j]) + bf16_lo(bet[i][j]);
+        const float hi = (vals[i][2 * j + 1] - mean) * rstd * bf16_hi(gam[i][j]) + bf16_hi(bet[i][j]);
         o[j] = pack_bf16(lo, hi);
       }
       st16(ln_out + (size_t)m * p.N + c * 8, o);
@@ -642,16 +653,12 @@ __global__ __launch_bounds__(256) void skinny_reduce_kv_kernel(const SkinnyParam
   if (idx >= (long)p.M * chunks_per_row) return;
   const int m = (int)(idx / chunks_per_row);
   const int n = (int)(idx % chunks_per_row) * 8;
+  const EpiPieces e = epi_load(p, m, n);
+  const int pos = ctx_lens[m];
+  const int blk = block_tables[(size_t)m * max_blocks + pos / 16];
   float v[8];
   sum_partials8(p, n_splits, m, n, v);
-  if (p.bias) {
-    const u32x4 bb = ld16(p.bias + n);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      v[2 * j] += bf16_lo(bb[j]);
-      v[2 * j + 1] += bf16_hi(bb[j]);
-    }
-  }
+  epi_apply(p, e, v);
   u32x4 ov;
 #pragma unroll
   for (int j = 0; j < 4; ++j) ov[j] = pack_bf16(v[2 * j], v[2 * j + 1]);
@@ -663,8 +670,6 @@ __global__ __launch_bounds__(256) void skinny_reduce_kv_kernel(const SkinnyParam
   const int which = n >= h + hkv;
   const int col = n - h - which * hkv;
   const int head = col / head_dim, d = col - head * head_dim;
-  const int pos = ctx_lens[m];
-  const int blk = block_tables[(size_t)m * max_blocks + pos / 16];
   uint16_t* dst = (which ? v_cache : k_cache) + (((size_t)blk * n_kv_heads + head) * 16 + (pos % 16)) * head_dim + d;
   st16(dst, ov);
 }

@@ -210,6 +210,17 @@ def test_tensor_parallel_shard_shapes(gpu, name, hidden, n_heads, ffn):
     _decode_and_check(shape, lw, w32, ctxs, seed, [0, int(np.argmax(ctxs)), int(np.argmin(ctxs))], steps=2)
 
 
+def test_decode_step_row_of_two_pieces(gpu):
+    """The reduce pass with LayerNorm-2 gives a thread two pieces of a row wider than 8192; here the second piece is
+    there for 16 of the 1024 threads only."""
+    shape = synth.ModelShape(hidden=8320, n_heads=65, head_dim=128, ffn=1024)
+    lw, wdev = gu.dev_layer_weights(shape, 8320)
+    assert gu.make_ctx(shape).ds_linear_plan(5, shape.hidden, shape.hidden)["splits"] > 1
+    w32 = orc.weights_from_bits(gu.host_weights(wdev), np.float32)
+    ctxs = synth.uniform_lengths(5, 1, 300, 8320, stream=3)
+    _decode_and_check(shape, lw, w32, ctxs, 8320, [0, 2, 4], steps=1)
+
+
 @pytest.mark.parametrize("hidden,n_heads,ffn,B", [
     (1024, 8, 4096, 200),     # QKV / FFN-in split over K on the tile kernel: K,V arrive through the reduce pass
     (256, 2, 1024, 150),      # too few k-tiles to split: K,V scattered by the tile kernel's own epilogue

@@ -109,6 +109,21 @@ def test_linear_tile_path(gpu, rows, in_f, out_f, bias, relu, residual):
     _linear_case(ctx, rows, in_f, out_f, bias, relu, residual, seed=rows)
 
 
+@pytest.mark.parametrize("bias,residual", [(False, False), (True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("rows,in_f,out_f,splits", [
+    (512, 5120, 5120, 3),     # up to four splits are summed in one group of loads
+    (3, 1024, 1032, 8),       # one whole group of eight, rows that end inside a workgroup
+    (1, 2048, 136, 16),       # two groups; fewer columns than a workgroup's
+    (64, 2048, 1032, 15),     # a last group that is not full
+])
+def test_split_reduction_with_and_without_each_operand(gpu, rows, in_f, out_f, splits, bias, residual):
+    """The reduce pass requests bias and residual before the partial sums and reads other memory where there is none:
+    what it reads there must not reach the result."""
+    ctx = gu.make_ctx(synth.TINY)
+    assert ctx.ds_linear_plan(rows, in_f, out_f)["splits"] == splits
+    _linear_case(ctx, rows, in_f, out_f, bias, False, residual, seed=rows + splits)
+
+
 def test_linear_tile_path_cases_cover_every_plan_kind(gpu):
     """The cases above are there for the plans they take: this pins which ones (host-side planning only)."""
     ctx = gu.make_ctx(synth.TINY)
