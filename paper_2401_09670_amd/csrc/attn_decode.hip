@@ -3,13 +3,12 @@
 // (16 tokens x s elements, contiguous) exactly once with 16-byte loads.
 //
 // grid = (heads, sequences, splits).  A workgroup of 4 waves takes one split
-// of the sequence's pages (splits are equally long; a sequence may have fewer
-// than the launch); wave w takes pages w, w+4, ... of that split.  In
+// of the sequence's pages; wave w takes pages w, w+4, ... of that split.  In
 // a wave, s/8 lanes cover one token row (8 elements each), so one load
 // instruction covers 64/(s/8) tokens.  Scores are reduced across the lanes
 // of a token with xor-shuffles, softmax runs online in fp32, and the four
-// waves' (max, sum, acc) states are merged through LDS.  A sequence of one split has its
-// result written as bf16; of several, fp32 partial states go to the
+// waves' (max, sum, acc) states are merged through LDS.  With one split the
+// result is written as bf16; with several, fp32 partial states go to the
 // workspace and a second kernel merges them (fixed order: deterministic).
 #include "common.h"
 #include "kernels.h"
@@ -39,12 +38,6 @@ __device__ __forceinline__ float dot8(const u32x4 a, const u32x4 b) {
   return acc;
 }
 
-// Splits of a sequence's pages that hold any: the others leave at once, and a sequence with a single one has its
-// result written by it.  (1 for a sequence without keys, whose result is defined as 0.)
-__device__ __forceinline__ int seq_splits(int n_pages, int pages_per_split) {
-  return min((int)gridDim.z, max(1, (n_pages + pages_per_split - 1) / pages_per_split));
-}
-
 // partial state layout in the workspace, per (seq, head, split): [0]=max, [1]=sum, [2..2+HD) = acc
 template <int HD>
 __global__ __launch_bounds__(kDecThreads) void decode_attention_kernel(
@@ -65,13 +58,12 @@ __global__ __launch_bounds__(kDecThreads) void decode_attention_kernel(
   const int kv_head = blockIdx.x % n_kv_heads;
   const int head = kv_head * kv_group + blockIdx.x / n_kv_heads;
   const int seq = blockIdx.y, split = blockIdx.z;
+  const int n_splits = gridDim.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tg = lane / LPT, dc = lane % LPT;
 
   const int kv_len = kv_lens[seq] + kv_len_add;
   const int n_pages = (kv_len + kDecPage - 1) / kDecPage;
-  const int n_splits = seq_splits(n_pages, pages_per_split);
-  if (split >= n_splits) return;
   const int page_lo = split * pages_per_split;
   const int page_hi = min(n_pages, page_lo + pages_per_split);
 
@@ -184,7 +176,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_attention_kernel(
     if (n_splits == 1) {
       reinterpret_cast<__bf16*>(o)[((size_t)seq * n_heads + head) * HD + tid] = (__bf16)(l > 0.f ? a / l : 0.f);  // no key at all (kv_len = 0): defined as 0
     } else {
-      float* dst = partial + (((size_t)seq * n_heads + head) * gridDim.z + split) * (HD + 2);
+      float* dst = partial + (((size_t)seq * n_heads + head) * n_splits + split) * (HD + 2);
       if (tid == 0) {
         dst[0] = m;
         dst[1] = l;
@@ -194,17 +186,11 @@ __global__ __launch_bounds__(kDecThreads) void decode_attention_kernel(
   }
 }
 
-// grid = (heads, sequences); z = max_splits of the launch that left the partial states, for their stride.
 template <int HD>
-__global__ __launch_bounds__(HD) void decode_combine_kernel(const float* __restrict__ partial, int max_splits,
-                                                            const int32_t* __restrict__ kv_lens, int kv_len_add,
-                                                            int pages_per_split, float scale_log2e,
-                                                            uint16_t* __restrict__ o) {
-  const int n_pages = (kv_lens[blockIdx.y] + kv_len_add + kDecPage - 1) / kDecPage;
-  const int n_splits = min(max_splits, (n_pages + pages_per_split - 1) / pages_per_split);
-  if (n_splits <= 1) return;  // the attention kernel has written the result
-  const size_t item = (size_t)blockIdx.y * gridDim.x + blockIdx.x;  // seq * n_heads + head
-  const float* src = partial + item * max_splits * (HD + 2);
+__global__ __launch_bounds__(HD) void decode_combine_kernel(const float* __restrict__ partial, int n_splits,
+                                                            float scale_log2e, uint16_t* __restrict__ o) {
+  const size_t item = blockIdx.x;  // seq * n_heads + head
+  const float* src = partial + item * n_splits * (HD + 2);
   const int tid = threadIdx.x;
   float m = -INFINITY;
   for (int s = 0; s < n_splits; ++s) m = fmaxf(m, src[s * (HD + 2)]);
@@ -217,7 +203,7 @@ __global__ __launch_bounds__(HD) void decode_combine_kernel(const float* __restr
       a += src[s * (HD + 2) + 2 + tid] * f;
     }
   }
-  reinterpret_cast<__bf16*>(o)[item * HD + tid] = (__bf16)(l > 0.f ? a / l : 0.f);
+  reinterpret_cast<__bf16*>(o)[item * HD + tid] = (__bf16)(l > 0.f ? a / l : 0.f);  // no key at all (kv_len = 0): defined as 0
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -256,14 +242,13 @@ __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(2))
 
   const int G = n_heads / n_kv_heads;  // 2..16 query heads share this key/value head
   const int kv_head = blockIdx.x, seq = blockIdx.y, split = blockIdx.z;
+  const int n_splits = gridDim.z;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hl = lane & 15, g = lane >> 4;  // head (or key, or d) index inside a tile; lane group
 
   const int kv_len = kv_lens[seq] + kv_len_add;
   const int n_pages = (kv_len + kDecPage - 1) / kDecPage;
-  const int n_splits = seq_splits(n_pages, pages_per_split);
-  if (split >= n_splits) return;
   const int page_lo = split * pages_per_split;
   const int page_hi = min(n_pages, page_lo + pages_per_split);
   const int32_t* bt = block_tables + (size_t)seq * max_blocks;
@@ -444,7 +429,7 @@ __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(2))
       for (int j = 0; j < 4; ++j) ov[j] = pack_bf16(a[2 * j] * inv, a[2 * j + 1] * inv);
       st16(o + item * HD + d0, ov);
     } else {
-      float* dst = partial + (item * gridDim.z + split) * (HD + 2);
+      float* dst = partial + (item * n_splits + split) * (HD + 2);
       if ((tid & 15) == 0) {
         dst[0] = m;
         dst[1] = l;
@@ -462,10 +447,9 @@ static bool gqa_kernel_serves(int n_heads, int n_kv_heads, int head_dim) {
   return head_dim == kGqaHD && G >= 2 && G <= 16;
 }
 
-// Splits that the workspace has to have room for: enough workgroups to cover the chip about twice, but never less
-// than 8 pages per split.  A workgroup serves one (sequence, head), or one (sequence, key/value head) in the
-// grouped-query kernel.
-static int needed_splits(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len) {
+// Enough workgroups to cover the chip about twice, but never less than 8 pages per split.  A workgroup
+// serves one (sequence, head), or one (sequence, key/value head) in the grouped-query kernel.
+int decode_attention_splits(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len) {
   const int pages = (max_kv_len + kDecPage - 1) / kDecPage;
   const long items = (long)B * (gqa_kernel_serves(n_heads, n_kv_heads, head_dim) ? n_kv_heads : n_heads);
   int splits = (int)((2 * 256 + items - 1) / items);
@@ -475,62 +459,49 @@ static int needed_splits(int B, int n_heads, int n_kv_heads, int head_dim, int m
   return splits;
 }
 
-static size_t split_bytes(int B, int n_heads, int head_dim) {
-  return (size_t)B * n_heads * (head_dim + 2) * sizeof(float);
-}
-
 size_t decode_attention_workspace_bytes(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len) {
-  const int splits = needed_splits(B, n_heads, n_kv_heads, head_dim, max_kv_len);
-  return splits == 1 ? 0 : splits * split_bytes(B, n_heads, head_dim);
-}
-
-// Pages per split.  The host knows the longest sequence only.  While the launch is no more than about six rounds of
-// the workgroups that are resident together (four to five per compute unit), a sequence much longer than the others
-// ends it alone on its unit, at what latency allows one workgroup: such a launch is cut into splits of at least 24 to
-// 48 pages, the more workgroups there are the longer, and only where two fit the longest sequence (what a shorter
-// one does not reach leaves at once, and a sequence of one split writes its result itself).  Measured, OPT-13B heads,
-// ragged contexts of median 384: 32 sequences up to 2224 tokens 84 -> 75 us, 64 up to 1872 122 -> 118, 128 up to 3088
-// 249 -> 241; 8 key/value heads for 64, 48 sequences up to 4064 tokens 107 -> 100.  Equal lengths gain nothing (64 of
-// 545 tokens: 119 whole, 122 in two), nor do larger launches (256 sequences 453 and 462, 256 of OPT-175B 2021 and 2151).
-static int plan_pages_per_split(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len,
-                                size_t workspace_bytes) {
-  const int pages = (max_kv_len + kDecPage - 1) / kDecPage;
-  const int needed = needed_splits(B, n_heads, n_kv_heads, head_dim, max_kv_len);
-  const bool gqa = gqa_kernel_serves(n_heads, n_kv_heads, head_dim);
-  const long items = (long)B * (gqa ? n_kv_heads : n_heads);
-  long splits = needed;
-  if (items <= 6144) {
-    const long least = gqa ? 48 : (items / 64 < 24 ? 24 : (items / 64 > 48 ? 48 : items / 64));
-    if (pages / least > splits) splits = pages / least;
-  }
-  const size_t room = workspace_bytes / split_bytes(B, n_heads, head_dim);
-  if (splits > needed && (size_t)splits > room) splits = room > (size_t)needed ? (long)room : needed;
-  return (int)((pages + splits - 1) / splits);
+  const int splits = decode_attention_splits(B, n_heads, n_kv_heads, head_dim, max_kv_len);
+  if (splits == 1) return 0;
+  return (size_t)B * n_heads * splits * (head_dim + 2) * sizeof(float);
 }
 
 hipError_t launch_decode_attention(const void* q, int q_stride, const int32_t* kv_lens, int kv_len_add,
                                    const int32_t* block_tables, int B, int max_blocks, int max_kv_len,
                                    const void* k_cache, const void* v_cache, int n_heads, int n_kv_heads,
-                                   int head_dim, void* o, void* workspace, size_t workspace_bytes, hipStream_t stream) {
+                                   int head_dim, void* o, void* workspace, hipStream_t stream) {
   if (B <= 0) return hipSuccess;
   if (n_kv_heads <= 0 || n_heads % n_kv_heads != 0) return hipErrorInvalidValue;
   if (B > 65535) return hipErrorInvalidValue;
-  if (head_dim != 64 && head_dim != 128) return hipErrorInvalidValue;
+  const int splits = decode_attention_splits(B, n_heads, n_kv_heads, head_dim, max_kv_len);
   const int pages = (max_kv_len + kDecPage - 1) / kDecPage;
-  const int pps = plan_pages_per_split(B, n_heads, n_kv_heads, head_dim, max_kv_len, workspace ? workspace_bytes : 0);
-  const int splits = (pages + pps - 1) / pps;
+  const int pps = (pages + splits - 1) / splits;
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)head_dim);
-  const bool gqa = gqa_kernel_serves(n_heads, n_kv_heads, head_dim);
-  const auto kern = gqa ? decode_attention_gqa_kernel
-                        : (head_dim == 128 ? decode_attention_kernel<128> : decode_attention_kernel<64>);
-  hipLaunchKernelGGL(kern, dim3(gqa ? n_kv_heads : n_heads, B, splits), dim3(kDecThreads), 0, stream,
-                     (const uint16_t*)q, q_stride, kv_lens, kv_len_add, block_tables, max_blocks,
-                     (const uint16_t*)k_cache, (const uint16_t*)v_cache, n_heads, n_kv_heads, pps, scale_log2e,
-                     (uint16_t*)o, (float*)workspace);
-  if (splits > 1)
-    hipLaunchKernelGGL(head_dim == 128 ? decode_combine_kernel<128> : decode_combine_kernel<64>, dim3(n_heads, B),
-                       dim3(head_dim), 0, stream, (const float*)workspace, splits, kv_lens, kv_len_add, pps,
-                       scale_log2e, (uint16_t*)o);
+  const dim3 grid(n_heads, B, splits);
+  if (gqa_kernel_serves(n_heads, n_kv_heads, head_dim)) {
+    hipLaunchKernelGGL(decode_attention_gqa_kernel, dim3(n_kv_heads, B, splits), dim3(kDecThreads), 0, stream,
+                       (const uint16_t*)q, q_stride, kv_lens, kv_len_add, block_tables, max_blocks,
+                       (const uint16_t*)k_cache, (const uint16_t*)v_cache, n_heads, n_kv_heads, pps, scale_log2e,
+                       (uint16_t*)o, (float*)workspace);
+    if (splits > 1)
+      hipLaunchKernelGGL(decode_combine_kernel<128>, dim3(B * n_heads), dim3(128), 0, stream,
+                         (const float*)workspace, splits, scale_log2e, (uint16_t*)o);
+  } else if (head_dim == 128) {
+    hipLaunchKernelGGL(decode_attention_kernel<128>, grid, dim3(kDecThreads), 0, stream, (const uint16_t*)q,
+                       q_stride, kv_lens, kv_len_add, block_tables, max_blocks, (const uint16_t*)k_cache,
+                       (const uint16_t*)v_cache, n_heads, n_kv_heads, pps, scale_log2e, (uint16_t*)o, (float*)workspace);
+    if (splits > 1)
+      hipLaunchKernelGGL(decode_combine_kernel<128>, dim3(B * n_heads), dim3(128), 0, stream,
+                         (const float*)workspace, splits, scale_log2e, (uint16_t*)o);
+  } else if (head_dim == 64) {
+    hipLaunchKernelGGL(decode_attention_kernel<64>, grid, dim3(kDecThreads), 0, stream, (const uint16_t*)q,
+                       q_stride, kv_lens, kv_len_add, block_tables, max_blocks, (const uint16_t*)k_cache,
+                       (const uint16_t*)v_cache, n_heads, n_kv_heads, pps, scale_log2e, (uint16_t*)o, (float*)workspace);
+    if (splits > 1)
+      hipLaunchKernelGGL(decode_combine_kernel<64>, dim3(B * n_heads), dim3(64), 0, stream,
+                         (const float*)workspace, splits, scale_log2e, (uint16_t*)o);
+  } else {
+    return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

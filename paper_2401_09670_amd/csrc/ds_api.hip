@@ -696,8 +696,7 @@ ds_status ds_decode_attention(ds_ctx* ctx, const void* q, const int32_t* kv_lens
   }
   DS_LAUNCH(ctx, s, DS_K_DECODE_ATTN,
             ds::launch_decode_attention(q, c.hidden, kv_lens, 0, block_tables, B, max_blocks_per_seq, max_kv_len,
-                                        k_cache, v_cache, c.n_heads, c.n_kv_heads, c.head_dim, o, workspace,
-                                        workspace_bytes, s));
+                                        k_cache, v_cache, c.n_heads, c.n_kv_heads, c.head_dim, o, workspace, s));
   return DS_OK;
 }
 
@@ -752,13 +751,8 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
   void* x1 = ws.take((size_t)B * h * 2);
   const int hkv = kv_width(c), wqkv = qkv_width(c);
   void* qkv = ws.take((size_t)B * wqkv * 2);
-  // The attention's partial sums may lie over everything behind them: u is written after they are read, and the
-  // products on either side use the split-K partials before and after.  (Counted from what this step asks for, not
-  // from what the caller's buffer holds, so that the plan - and the rounding - does not depend on the buffer.)
-  void* att = ws.take(0);
-  const size_t att_bytes = need - ws.off;
   void* u = ws.take((size_t)B * m * 2);
-  ws.take(ds::decode_attention_workspace_bytes(B, c.n_heads, c.n_kv_heads, c.head_dim, max_ctx));
+  void* att = ws.take(ds::decode_attention_workspace_bytes(B, c.n_heads, c.n_kv_heads, c.head_dim, max_ctx));
   void* sk = ws.take(0);
 
   DS_LAUNCH(ctx, s, DS_K_LAYERNORM, ds::launch_layernorm(x, w->ln1_g, w->ln1_b, a, B, h, c.ln_eps, s));
@@ -783,7 +777,7 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
   }
   DS_LAUNCH(ctx, s, DS_K_DECODE_ATTN,
             ds::launch_decode_attention(qkv, wqkv, ctx_lens, 1, block_tables, B, max_blocks_per_seq, max_ctx,
-                                        k_cache, v_cache, c.n_heads, c.n_kv_heads, c.head_dim, o, att, att_bytes, s));
+                                        k_cache, v_cache, c.n_heads, c.n_kv_heads, c.head_dim, o, att, s));
   {
     // x1 = x + o W_o^T + b_o, and f = LN2(x1) in the same reduction pass
     ds::Epilogue ep;

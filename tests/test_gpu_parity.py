@@ -306,47 +306,6 @@ def test_decode_attention_grouped_query(gpu, n_heads, n_kv, kv_lens):
         assert gu.rel_err(got[i], ref[i]) < TOL, (i, kv_lens[i])
 
 
-@pytest.mark.parametrize("head_dim,n_heads,n_kv,batch,edge", [
-    (128, 4, 4, 32, 432),                    # 188 pages in 7 splits of 27
-    (64, 4, 4, 32, 432),
-    (128, 4, 2, 128, 1008),                  # grouped queries: 3 splits of 63
-])
-def test_decode_attention_ragged_splits(gpu, head_dim, n_heads, n_kv, batch, edge):
-    """One sequence much longer than the others, which cuts the launch into more splits than it needs to fill the
-    chip: lengths around the ends of splits, sequences of a single split and without any key, a buffer that was
-    never written, and one with room for the needed splits only."""
-    lens = [3000, 0, 1, 16, edge - 1, edge, edge + 1, 2 * edge, 2 * edge + 1, 2 * edge + 16]
-    lens = [min(l, 3000) for l in lens] + [5 + 3 * i for i in range(batch - len(lens))]
-    shape = synth.ModelShape(hidden=n_heads * head_dim, n_heads=n_heads, head_dim=head_dim, ffn=256, n_kv_heads=n_kv)
-    ctx = gu.make_ctx(shape)
-    h = shape.hidden
-    bt, nblk = synth.make_block_tables([max(l, 1) for l in lens], 16, seed=61)
-    kf, vf = synth.make_kv_fill(sum(lens), shape, seed=62)
-    kc = np.full((nblk, n_kv, 16, head_dim), 0x7FC0, dtype=np.uint16)     # unowned slots: NaN / -Inf
-    vc = np.full_like(kc, 0xFF80)
-    orc.kv_migrate(kf, vf, lens, bt, kc, vc)
-    qb = synth.make_activations(batch, h, seed=63)
-    q = orc.from_bf16_bits(qb).reshape(batch, n_heads, head_dim)
-    cu = synth.cu_seqlens(lens)
-    ref = np.zeros_like(q)
-    for i, l in enumerate(lens):
-        if l:
-            ref[i] = orc.attention_rows(q[i:i + 1], np.array([l - 1]), orc.from_bf16_bits(kf[cu[i]:cu[i] + l]),
-                                        orc.from_bf16_bits(vf[cu[i]:cu[i] + l]))[0]
-    needed = -(-512 // (batch * n_kv)) * batch * n_heads * (head_dim + 2) * 4
-    for nbytes in (64 << 20, needed):
-        ws = torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda")  # NaN where nothing is written
-        o = torch.full((batch, h), 7.0, dtype=torch.bfloat16, device="cuda")
-        ctx.ds_decode_attention(gu.to_dev(qb), gu.i32_dev(lens), gu.i32_dev(bt), batch, bt.shape[1], max(lens),
-                                gu.to_dev(kc), gu.to_dev(vc), nblk, o, ws)
-        torch.cuda.synchronize()
-        got = gu.to_f64(o).reshape(batch, n_heads, head_dim)
-        assert np.all(got[1] == 0)
-        for i, l in enumerate(lens):
-            if l:
-                assert gu.rel_err(got[i], ref[i]) < TOL, (i, l, nbytes)
-
-
 # ------------------------------------------------------------------ whole path, config 1 (tiny), every element
 def run_path(shape, wbits, xbits, lens, steps, seed, decode_x):
     """prefill -> migrate -> `steps` decode steps on the GPU; returns device results as numpy."""
