@@ -125,7 +125,9 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
   const int turn_by = (n_splits & 3) == 0 ? 1 : 0;
   const int ns = whole + ((split + whole * turn_by) % n_splits < slabs_total - whole * n_splits ? 1 : 0);
   const int K = p.K;
-  const int rot = start_slab(blockIdx.x + gridDim.x * split, ns, n_splits * kSkKS, p.M, K);
+  // Greedy choice: one order for all column blocks, so that equal vocabulary rows get equal logits, bit for bit, and the
+  // tie goes to the lowest id.
+  const int rot = p.amax_val ? 0 : start_slab(blockIdx.x + gridDim.x * split, ns, n_splits * kSkKS, p.M, K);
 
   // load j of this wave is row group g = j*8 + wave of the stage (8 rows): X rows first, then W rows
   const int lr = lane >> 3;

@@ -132,6 +132,41 @@ def test_next_token_ties_go_to_lowest_id():
     assert np.any(expect != first)          # some twin really sat below its original
 
 
+@pytest.mark.parametrize("h,rows", [(2048, 16), (2048, 65), (8192, 3), (8192, 64), (12288, 64), (4096, 200)])
+def test_next_token_ties_between_column_blocks(h, rows):
+    """Rows of K whose stride is a multiple of 4 KB (h a multiple of 2048): equal vocabulary rows that lie in different
+    column blocks have to get equal logits, bit for bit, or the larger rounding error would win instead of the lowest
+    id.  Every row's winner gets a twin below and a twin above it, 3 and 5 column blocks away or more."""
+    vocab = 4096
+    ctx = _ctx(h, h // 128, 128, 4 * h)
+    x = gu.dev_normal_bits((rows, h), 1.0, 51)
+    g, b = gu.dev_normal_bits((h,), 0.05, 52, 1.0), gu.dev_normal_bits((h,), 0.05, 53)
+    w = gu.dev_normal_bits((vocab, h), 0.05, 54)
+    ws = gu.workspace(ctx.ds_next_token_workspace_bytes(rows, vocab))
+    tok = torch.empty(rows, dtype=torch.int32, device="cuda")
+    best = torch.empty(rows, dtype=torch.float32, device="cuda")
+    ctx.ds_next_token(x, None, rows, g, b, w, vocab, tok, best, ws)
+    torch.cuda.synchronize()
+    first = tok.cpu().numpy().copy()
+    w2, expect, taken, planted = w.clone(), {}, set(int(t) for t in first), 0
+    for r, t in enumerate(int(t) for t in first):
+        if t in expect:
+            continue                        # another row's winner, with its twins already there
+        expect[t] = t
+        for twin in (t - 3 * 256 - 5 * r % 64, t + 5 * 256 + 3 * r % 64):
+            if 0 <= twin < vocab and twin not in taken:
+                taken.add(twin)
+                w2[twin] = w[t]
+                expect[t] = min(expect[t], twin)
+                planted += 1
+    tok2, best2 = torch.empty_like(tok), torch.empty_like(best)
+    ctx.ds_next_token(x, None, rows, g, b, w2, vocab, tok2, best2, ws)
+    torch.cuda.synchronize()
+    assert planted >= len(expect)           # about one and a half twins each
+    assert np.array_equal(tok2.cpu().numpy(), [expect[int(t)] for t in first])
+    assert torch.equal(best2, best)
+
+
 def test_next_token_opt13b_vocab_after_prefill_rows():
     """OPT-13B width and OPT's vocabulary (50272 ids, Sec. 6.1), rows picked like the last positions of a
     packed prefill batch, and a 64-wide decode batch."""
