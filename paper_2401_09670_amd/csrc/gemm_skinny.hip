@@ -78,9 +78,13 @@ __device__ __forceinline__ void sk_wait_vmcnt() {
 // 214).  So each XCD (id % 8) starts at an eighth of its own, and its 32 workgroups are spread over as many slabs as
 // their activations keep in the XCD's L2 (spread over all of K, 128 rows of 5120 x 20480 take 65 us, not 56).  Other
 // strides spread by themselves, and rows in step share DRAM pages (5120 x 5120, 64 rows: 18.8 us in step, 20 spread).
+// `rows` is the most rows the kernel takes (64, 128 or 256), never the batch's own: the start decides in which order K
+// is added, and a sequence's result must not depend on how many others are in its step.  So a small batch is spread as a
+// full one, and the window is all of the L2's 4 MB (half of it: 8192 x 32768 at 1 row 92.6 us, not 87.2, at 128 rows
+// 112.4, not 107.2).
 __device__ __forceinline__ int start_slab(unsigned id, int ns, int slab_stride, int rows, int K) {
   if (K % 2048 != 0) return 0;
-  const int in_l2 = (1 << 20) / (rows * slab_stride);  // slabs whose activations take 2 MB
+  const int in_l2 = (1 << 21) / (rows * slab_stride);  // slabs whose activations take 4 MB
   const int window = in_l2 < ns ? in_l2 : ns;
   return (int)(((id & 7) * (unsigned)ns / 8 + ((id >> 3) & 31) * (unsigned)window / 32) % (unsigned)ns);
 }
@@ -127,7 +131,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
   const int K = p.K;
   // Greedy choice: one order for all column blocks, so that equal vocabulary rows get equal logits, bit for bit, and the
   // tie goes to the lowest id.
-  const int rot = p.amax_val ? 0 : start_slab(blockIdx.x + gridDim.x * split, ns, n_splits * kSkKS, p.M, K);
+  const int rot = p.amax_val ? 0 : start_slab(blockIdx.x + gridDim.x * split, ns, n_splits * kSkKS, MP, K);
 
   // load j of this wave is row group g = j*8 + wave of the stage (8 rows): X rows first, then W rows
   const int lr = lane >> 3;
@@ -345,7 +349,7 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
   const int K = p.K;
   const int slabs_total = K / kWrKS;
   const int ns = (slabs_total - wave + NW - 1) / NW;  // this wave's slabs: wave, wave + NW, ...  (>= 1: K >= 256)
-  const int rot = start_slab(blockIdx.x, ns, NW * kWrKS, p.M, K);
+  const int rot = start_slab(blockIdx.x, ns, NW * kWrKS, MT <= 4 ? 64 : 128, K);
 
   // load j of a slab covers stage rows 8j .. 8j+7 (rows 0..BM-1 = X, then W); lane: row 8j + lane/8,
   // 16-byte chunk (lane%8) ^ ((row >> 1) & 7) - the swizzle that makes the fragment reads conflict-free

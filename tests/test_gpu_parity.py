@@ -124,6 +124,33 @@ def test_split_reduction_with_and_without_each_operand(gpu, rows, in_f, out_f, s
     _linear_case(ctx, rows, in_f, out_f, bias, False, residual, seed=rows + splits)
 
 
+@pytest.mark.parametrize("small,large,in_f,out_f,tile_cols,splits", [
+    (1, 64, 32768, 1032, 128, 28),
+    (33, 64, 32768, 8200, 256, 7),
+    (47, 48, 32768, 8192, 256, 8),
+    (65, 128, 16384, 8200, 128, 3),
+    (17, 64, 32768, 13320, 64, 1),    # wave-private rings, 32 and 64 activation rows
+    (1, 64, 4096, 13320, 64, 1),      # ... 16 and 64
+    (65, 128, 16384, 16648, 80, 1),   # ... of 128 activation rows
+])
+def test_streaming_rows_do_not_depend_on_the_rows_beside_them(gpu, small, large, in_f, out_f, tile_cols, splits):
+    """Up to 64 rows, and from 65 to 128, a product of one plan adds K in one order: a sequence's row has the same
+    bits whatever the batch it is in."""
+    ctx = gu.make_ctx(synth.TINY)
+    x = gu.dev_normal_bits((large, in_f), 1.0, 61)
+    w = gu.dev_normal_bits((out_f, in_f), 0.02, 62)
+    got = []
+    for rows in (small, large):
+        plan = ctx.ds_linear_plan(rows, in_f, out_f)
+        assert plan["streaming"] and (plan["tile_cols"], plan["splits"]) == (tile_cols, splits), (rows, plan)
+        y = torch.empty(rows, out_f, dtype=torch.bfloat16, device="cuda")
+        ws = gu.workspace(ctx.ds_linear_workspace_bytes(rows, in_f, out_f))
+        ctx.ds_linear(x, w, None, None, 0, rows, in_f, out_f, y, ws)
+        got.append(y)
+    torch.cuda.synchronize()
+    assert torch.equal(got[1][:small].view(torch.int16), got[0].view(torch.int16))
+
+
 def test_linear_tile_path_cases_cover_every_plan_kind(gpu):
     """The cases above are there for the plans they take: this pins which ones (host-side planning only)."""
     ctx = gu.make_ctx(synth.TINY)
