@@ -72,6 +72,17 @@ __device__ __forceinline__ void sk_wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((VM & 0xf) | (0x7 << 4) | (0xf << 8) | ((VM >> 4) << 14));
 }
 
+// Waits until at most `slabs` (0 .. MOST) slabs of G loads are in flight.
+template <int MOST, int G>
+__device__ __forceinline__ void sk_wait_slabs(int slabs) {
+  if constexpr (MOST == 0) {
+    sk_wait_vmcnt<0>();
+  } else {
+    if (slabs >= MOST) sk_wait_vmcnt<MOST * G>();
+    else sk_wait_slabs<MOST - 1, G>(slabs);
+  }
+}
+
 // Which of its ns slabs (slab_stride elements apart) a workgroup starts with; it goes round from there.  Where the row
 // stride is a multiple of 4 KB, the pieces that all rows have at one position of K lie on few memory channels, and
 // workgroups in lockstep wait for these (32768 x 8192, 48 rows: 123 us, 91 with this; 49152 x 12288, 64 rows: 218 and
@@ -99,9 +110,12 @@ __device__ __forceinline__ int start_slab(unsigned id, int ns, int slab_stride, 
 //
 // What bounds it: bytes on their way from HBM, so the ring holds as many small stages as the LDS has room for (160 KB of
 // 16 to 40 KB each) and the loop never drains it - behind __syncthreads() the compiler waits for every load in
-// flight, which with 128-element slabs in two or three stages left a gap per slab.  Per product, reduce pass
-// included: 5120 x 5120 at 1 row 18.5 -> 14.3 us, at 64 rows 20.5 -> 18.9; 5120 x 20480 at 1 row 45.7 -> 39.5, at 64
-// rows 51.4 -> 47; 32768 x 8192 at 48 rows 127 -> 91 (5.9 TB/s of weights); 12288 x 49152 at 128 rows 326 -> 302.
+// flight, which with 128-element slabs in two or three stages left a gap per slab.  Nor does it ask for more slabs than
+// there are: with the last one loaded again and again, so that the count of loads in flight stays the same, 512 x 128
+// brought in nine slabs for two (1 row: 3.6 us, 3.2 without) and long products were 1-5 % slower.  Per product, reduce
+// pass included, from 128-element slabs: 5120 x 5120 at 1 row 18.3 -> 14.0 us, at 64 rows 21.0 -> 19.5; 5120 x 20480 at
+// 1 row 47.7 -> 39.5, at 64 rows 53.8 -> 46.4; 32768 x 8192 at 48 rows 128 -> 89 (6.0 TB/s of weights); 12288 x 49152 at
+// 128 rows 301 -> 296.
 template <int MT, int NTW, int S>
 __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyParams p) {
   constexpr int MP = MT * 16;   // padded activation rows held in LDS
@@ -124,10 +138,15 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
   // multiple of 4 splits it takes number (s + i) % n_splits of group i instead, or it would meet only every fourth
   // 128-byte piece of a row, a fraction of the memory channels (8192 x 32768, 48 rows, 8 splits: 118 -> 93 us; other
   // split counts meet all of them anyway and lose up to 10 % by the turning).
+  // (The divisions are left out where there is nothing to divide: they are a tenth of a launch over few slabs.)
   const int slabs_total = p.K / kSkKS;
-  const int whole = slabs_total / n_splits;  // >= 1: n_splits <= slabs_total
-  const int turn_by = (n_splits & 3) == 0 ? 1 : 0;
-  const int ns = whole + ((split + whole * turn_by) % n_splits < slabs_total - whole * n_splits ? 1 : 0);
+  const int turn_by = n_splits > 1 && (n_splits & 3) == 0 ? 1 : 0;
+  int ns = slabs_total;  // >= 1: n_splits <= slabs_total
+  if (n_splits > 1) {
+    const int whole = slabs_total / n_splits;
+    const int number = turn_by ? (split + whole) % n_splits : split;  // of this split in a last, partial group
+    ns = whole + (number < slabs_total - whole * n_splits ? 1 : 0);
+  }
   const int K = p.K;
   // Greedy choice: one order for all column blocks, so that equal vocabulary rows get equal logits, bit for bit, and the
   // tie goes to the lowest id.
@@ -143,14 +162,12 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
     if (r < MP) src[j] = p.X + (size_t)min(r, p.M - 1) * K + sw;
     else src[j] = p.W + (size_t)min(n0 + r - MP, p.N - 1) * K + sw;
   }
-  // requests the next slab of this split (the last one again when none is left: a harmless re-load) into stage `st`
-  int group = rot, turn = (split + rot * turn_by) % n_splits, left = ns;
+  // requests the next slab of this split into stage `st`
+  int group = rot, turn = turn_by && rot ? (split + rot) % n_splits : split;
   auto request = [&](int st) {
     const int ofs = (group * n_splits + turn) * kSkKS;
-    if (--left > 0) {
-      turn = turn + turn_by == n_splits ? 0 : turn + turn_by;
-      if (++group == ns) group = 0, turn = split;
-    }
+    turn = turn + turn_by == n_splits ? 0 : turn + turn_by;
+    if (++group == ns) group = 0, turn = split;
     uint16_t* dst = lds + st * STAGE_ELEMS + wave_s * 512;  // one wave-load = 8 rows = 1 KB = 512 elements
 #pragma unroll
     for (int j = 0; j < G; ++j) {
@@ -174,16 +191,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
   // fragment read offset of this wave's k-step: lane (row = lane%16, kq = lane/16) reads chunk 4*step + kq of its row
   const int fo = (lane & 15) * kSkKS + (((4 * kh + (lane >> 4)) ^ (((lane & 15) >> 1) & 7)) * 8);
   const int wfrag0 = (MP + ng * NTW * 16) * kSkKS;
-
-#pragma unroll
-  for (int d = 0; d < D; ++d) request(d);
-
-  int st = 0;      // stage of slab i
-  int st_req = D;  // stage slab i+D goes to (= the stage slab i-1 used)
-  for (int i = 0; i < ns; ++i) {
-    sk_wait_vmcnt<(D - 1) * G>();  // this wave's part of slab i has landed
-    lds_barrier();                 // slab i visible to all waves; everyone is done with slab i-1
-    request(st_req);
+  auto multiply = [&](int st) {
     const uint16_t* sb = lds + st * STAGE_ELEMS;
     u32x4 xf[MT];
 #pragma unroll
@@ -196,7 +204,28 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
         acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf),
                                                             __builtin_bit_cast(bf16x8, xf[t]), acc[a][t], 0, 0, 0);
     }
+  };
+
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (d < ns) request(d);
+
+  int st = 0;      // stage of slab i
+  int st_req = D;  // stage slab i+D goes to (= the stage slab i-1 used)
+  int i = 0;
+  for (; i + D < ns; ++i) {
+    sk_wait_vmcnt<(D - 1) * G>();  // this wave's part of slab i has landed
+    lds_barrier();                 // slab i visible to all waves; everyone is done with slab i-1
+    request(st_req);
+    multiply(st);
     st_req = st;
+    st = (st + 1 == S) ? 0 : st + 1;
+  }
+  // The last D slabs, all requested: ns - 1 - i younger ones may still be in flight.
+  for (; i < ns; ++i) {
+    sk_wait_slabs<D - 1, G>(ns - 1 - i);
+    lds_barrier();
+    multiply(st);
     st = (st + 1 == S) ? 0 : st + 1;
   }
   sk_wait_vmcnt<0>();  // no global->LDS write of this workgroup may still be in flight ...

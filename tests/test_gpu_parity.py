@@ -124,6 +124,28 @@ def test_split_reduction_with_and_without_each_operand(gpu, rows, in_f, out_f, s
     _linear_case(ctx, rows, in_f, out_f, bias, False, residual, seed=rows + splits)
 
 
+@pytest.mark.parametrize("rows,in_f,out_f,tile_cols,splits", [
+    (3, 128, 136, 64, 1),         # 2 slabs in a ring of 8 stages
+    (17, 384, 264, 64, 1),        # 6: one less than the ring keeps in flight
+    (64, 1792, 4096, 64, 4),      # 7 per split: as many, so the main loop has nothing to do
+    (64, 512, 1032, 64, 1),       # 8: one more
+    (40, 1792, 3080, 64, 5),      # 5 or 6 per split
+    (5, 384, 16392, 128, 1),      # 6 in 6 stages
+    (64, 128, 40008, 256, 1),     # 2 in 4 stages
+    (65, 128, 40008, 128, 1),     # 128 activation rows: 2 in 5 stages
+    (128, 256, 520, 64, 1),       # ... 4 in 6
+    (100, 384, 136, 64, 1),       # ... 6 in 6
+    (65, 1152, 520, 64, 9),       # ... 2 per split
+])
+def test_streaming_rings_deeper_than_the_product(gpu, rows, in_f, out_f, tile_cols, splits):
+    """Few 64-wide slabs of K for a workgroup: the ring asks for no slab that is not there and waits for exactly those
+    that are."""
+    ctx = gu.make_ctx(synth.TINY)
+    plan = ctx.ds_linear_plan(rows, in_f, out_f)
+    assert plan["streaming"] and (plan["tile_cols"], plan["splits"]) == (tile_cols, splits)
+    _linear_case(ctx, rows, in_f, out_f, True, True, False, seed=rows + in_f)
+
+
 @pytest.mark.parametrize("small,large,in_f,out_f,tile_cols,splits", [
     (1, 64, 32768, 1032, 128, 28),
     (33, 64, 32768, 8200, 256, 7),
