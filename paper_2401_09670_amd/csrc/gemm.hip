@@ -124,7 +124,8 @@ __device__ __forceinline__ void wait_vmcnt() {
 // four registers - all 256 accumulator registers - the compiler gave results other registers than inputs and
 // moved 100 to 400 registers per k-tile.  What it cannot see here: an accumulator may be moved or read only 8 wait
 // states after the instruction, and used as input 2 after it was moved.  PADDED carries these waits along, for code
-// around which the compiler does move accumulators (all but the main loop, whose body is free of moves).
+// around which the compiler does move accumulators (all but the main loop, whose body is free of moves: that is the
+// register allocator's choice, and tests/test_gemm_wait_states_cpu.py reads it off the compiled kernels).
 template <bool PADDED>
 __device__ __forceinline__ void mfma_acc(floatx4& acc, const u32x4& w, const u32x4& x) {
   if constexpr (PADDED)
