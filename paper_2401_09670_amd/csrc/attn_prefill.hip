@@ -20,7 +20,7 @@ constexpr int kAttQ = 128;    // queries per workgroup
 constexpr int kAttKV = 64;    // keys per tile
 constexpr float kSlack = 8.f;   // exponent headroom before the softmax reference point is moved
 
-#ifdef DS_DEV_SWITCHES
+#ifdef DS_DEV_STAMPS
 // timing harness builds only: 16 wall-clock stamps (100 MHz) per workgroup - entry, first tile landed, the end
 // of each of the first 12 tiles, exit - and the tile count
 unsigned long long* g_attn_dbg = nullptr;
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kAttThreads) __attribute__((amdgpu_waves_per_eu(2))
   auto wait_loads = [] {  // s_waitcnt vmcnt(0) only: vmcnt[3:0] | expcnt=7 | lgkmcnt=15 | vmcnt[5:4] in bits 15:14
     __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xf << 8));
   };
-#ifdef DS_DEV_SWITCHES
+#ifdef DS_DEV_STAMPS
   int dbg_tiles = 0;
 #endif
   for (;;) {   // one query tile, or two
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kAttThreads) __attribute__((amdgpu_waves_per_eu(2))
 
     const int kv_end = min(len, q0 + kAttQ);  // keys any query of this workgroup may see
     const int n_tiles = (kv_end + kAttKV - 1) / kAttKV;
-#ifdef DS_DEV_SWITCHES
+#ifdef DS_DEV_STAMPS
     dbg_tiles += n_tiles;
 #endif
 
@@ -331,7 +331,7 @@ __global__ __launch_bounds__(kAttThreads) __attribute__((amdgpu_waves_per_eu(2))
     qt_next = -1;
   }
   DS_ATT_STAMP(14);
-#ifdef DS_DEV_SWITCHES
+#ifdef DS_DEV_STAMPS
   if (dbg && threadIdx.x == 0) dbg[(size_t)blockIdx.x * 16 + 15] = (unsigned long long)dbg_tiles;
 #endif
 }

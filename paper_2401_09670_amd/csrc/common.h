@@ -6,7 +6,8 @@
 
 // Development switches (force a tile shape, a split count, a kernel choice): plain constants in the library
 // build, so the choice logic they sit in folds away; the timing harnesses compile the sources with
-// -DDS_DEV_SWITCHES and flip them at run time.
+// -DDS_DEV_SWITCHES and flip them at run time.  The kernels are the same in both builds; wall-clock stamps inside them
+// need -DDS_DEV_STAMPS and give other code (the 256x160 GEMM loop: 279 vector instructions per k-tile, not 4).
 #ifdef DS_DEV_SWITCHES
 namespace ds {
 struct SwitchReg {  // makes a switch settable by name through ds_dev_switch (development builds only)

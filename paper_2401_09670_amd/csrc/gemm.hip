@@ -58,12 +58,12 @@ struct GemmParams {
   uint16_t* k_cache;
   uint16_t* v_cache;
   int n_heads, n_kv_heads, head_dim;
-#ifdef DS_DEV_SWITCHES
+#ifdef DS_DEV_STAMPS
   unsigned long long* dbg;  // timing harness builds only: 4 wall-clock stamps per workgroup
 #endif
 };
 
-#ifdef DS_DEV_SWITCHES
+#ifdef DS_DEV_STAMPS
 unsigned long long* g_gemm_dbg = nullptr;
 #define DS_STAMP(i)                                                                         \
   do {                                                                                      \
@@ -696,7 +696,7 @@ hipError_t launch_gemm(const void* X, const void* W, int M, int N, int K, const 
   p.partial = nullptr;
   p.ctx_lens = nullptr; p.block_tables = nullptr; p.max_blocks = 0;
   p.k_cache = nullptr; p.v_cache = nullptr; p.n_heads = 0; p.n_kv_heads = 0; p.head_dim = 0;
-#ifdef DS_DEV_SWITCHES
+#ifdef DS_DEV_STAMPS
   p.dbg = g_gemm_dbg;
 #endif
   GemmPlan pl = gemm_plan(M, N, K);

@@ -1,5 +1,11 @@
 """Host-side pieces of the plan sweep harness (the sweep itself needs a GPU and the development build)."""
-from paper_2401_09670_amd import plan_sweep
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2401_09670_amd import build, plan_sweep
 
 
 def test_plan_text_names_what_the_plan_does():
@@ -27,3 +33,29 @@ def test_markdown_reports_the_worst_ratio_and_every_row():
 
 def test_shapes_are_the_three_opt_models():
     assert plan_sweep.SHAPES == {"opt13b": (5120, 20480), "opt66b": (9216, 36864), "opt175b": (12288, 49152)}
+
+
+@pytest.mark.parametrize("source", ["gemm.hip", "gemm_skinny.hip", "attn_prefill.hip"])
+def test_development_build_has_the_library_s_kernels(source, tmp_path):
+    """What the sweep times is what the library runs: the switches are host code and change no instruction.  (A store
+    added to a kernel for its timeline is enough for other registers in the main loop.)"""
+    runs = []
+    for extra in ([], ["-DDS_DEV_SWITCHES"]):
+        out = str(tmp_path / f"{len(runs)}.s")
+        runs.append((out, subprocess.Popen([build.HIPCC, *build.FLAGS, *extra, "--cuda-device-only", "-S",
+                                            os.path.join(build.CSRC, source), "-o", out], stderr=subprocess.DEVNULL)))
+    kernels = []
+    for out, process in runs:
+        assert process.wait() == 0
+        found, name = {}, None
+        for line in open(out):
+            begin = re.match(r"(_Z\w+):", line)
+            if begin:
+                name = begin.group(1)
+                found[name] = []
+            elif line.startswith(".Lfunc_end"):
+                name = None
+            elif name:
+                found[name].append(line.split(";")[0].rstrip())
+        kernels.append(found)
+    assert kernels[0] and kernels[0] == kernels[1]
