@@ -125,6 +125,24 @@ def test_split_reduction_with_and_without_each_operand(gpu, rows, in_f, out_f, s
 
 
 @pytest.mark.parametrize("rows,in_f,out_f,tile_cols,splits", [
+    (2, 3200, 1288, 64, 12),      # 50 slabs of K for 12 splits: the last group has two
+    (5, 2048, 1288, 64, 12),      # 32 for 12, and every workgroup starts elsewhere
+    (64, 4096, 520, 64, 28),      # 64 for 28: eight slabs left for a third group
+    (100, 10240, 136, 64, 64),    # 160 for 64, 128 activation rows per slab
+    (40, 8192, 1032, 64, 15),     # a split count that does not turn, spread starts
+    (70, 2048, 2568, 64, 6),      # the same with two groups of starts per column block
+])
+def test_streaming_starts_and_turns_meet_every_slab_once(gpu, rows, in_f, out_f, tile_cols, splits):
+    """A split takes one 64-wide slab of K out of every group of `splits`; a multiple of four splits moves on by one
+    from group to group, and where in_f is a multiple of 2048 a workgroup starts in the middle and goes round.  A slab
+    left out or taken twice shows in every output."""
+    ctx = gu.make_ctx(synth.TINY)
+    plan = ctx.ds_linear_plan(rows, in_f, out_f)
+    assert plan["streaming"] and (plan["tile_cols"], plan["splits"]) == (tile_cols, splits)
+    _linear_case(ctx, rows, in_f, out_f, True, False, False, seed=rows + splits)
+
+
+@pytest.mark.parametrize("rows,in_f,out_f,tile_cols,splits", [
     (3, 128, 136, 64, 1),         # 2 slabs in a ring of 8 stages
     (17, 384, 264, 64, 1),        # 6: one less than the ring keeps in flight
     (64, 1792, 4096, 64, 4),      # 7 per split: as many, so the main loop has nothing to do

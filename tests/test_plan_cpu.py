@@ -92,3 +92,18 @@ def test_wide_decode_products_leave_the_unsplit_kernel_when_it_would_need_severa
         assert ctx.ds_linear_plan(16, k, n) == dict(streaming=True, tile_rows=0, tile_cols=64, splits=1, cut_cols=0)
     # the OPT-13B products fit one round unsplit: 64 and 80 columns per workgroup
     assert ctx.ds_linear_plan(64, 5120, 15360)["tile_cols"] == 64 and ctx.ds_linear_plan(64, 5120, 20480)["tile_cols"] == 80
+
+
+def test_unsplit_products_that_leave_a_fifth_of_the_chip_idle_are_compared_with_split_ones(ctx):
+    """More than 16 rows on fewer than 208 workgroups of 64 columns: split where that moves clearly fewer bytes (17 rows
+    of 49152 -> 12288 200 us unsplit, 185 split five ways; 64 rows of 12288 -> 12288 76 and 58, of 8192 -> 10240 48 and
+    37), unsplit where it does not, at 16 rows, and from 208 workgroups on."""
+    unsplit = dict(streaming=True, tile_rows=0, tile_cols=64, splits=1, cut_cols=0)
+    for rows in (17, 32, 64):
+        assert ctx.ds_linear_plan(rows, 49152, 12288) == dict(unsplit, tile_cols=256, splits=5)
+    assert ctx.ds_linear_plan(16, 49152, 12288) == unsplit
+    assert ctx.ds_linear_plan(33, 12288, 12288)["splits"] == 5 and ctx.ds_linear_plan(64, 8192, 10240)["splits"] == 3
+    assert ctx.ds_linear_plan(32, 12288, 12288) == unsplit and ctx.ds_linear_plan(32, 8192, 10240) == unsplit
+    # 207 workgroups are compared, 208 are not
+    assert ctx.ds_linear_plan(64, 49152, 207 * 64)["splits"] > 1
+    assert ctx.ds_linear_plan(64, 49152, 208 * 64) == unsplit
