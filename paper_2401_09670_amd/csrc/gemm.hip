@@ -6,10 +6,11 @@
 // row operand, activation rows as the column operand).
 //
 // What bounds the large tiles: power (with N(0,1)-like operands the clock settles at 1.7-1.9 GHz) and, beside it, the
-// loads of operand tiles through a compute unit's load path - a 256x256 k-tile takes 1.45 us, its matrix work alone 1.05
-// and its 64 KB of loads alone 0.97.  16384 x 36864 x 12288: 10.85 -> 10.18 ms (32x32x16 instructions, loads and
-// fragment reads in clumps -> 16x16x32, dealt out one by one, 8 x 4 tiles per XCD); 2048 x 15360 x 5120: 258 -> 250 us;
-// 2048 x 5120 x 20480 (256x160 tiles): 329 -> 311 us.
+// loads of operand tiles through a compute unit's load path - a 256x256 k-tile of 16384 x 36864 x 12288 takes 1.42 us
+// (1.53 with the loop before this one), 1.19 without its 64 KB of loads and 1.30 without its matrix instructions; in a
+// launch of one round (4096 x 4096) the loads alone take all of its 1.55 us.  16384 x 36864 x 12288: 10.85 -> 10.18 ms
+// (32x32x16 instructions, loads and fragment reads in clumps -> 16x16x32, dealt out one by one, 8 x 4 tiles per XCD);
+// 2048 x 15360 x 5120: 258 -> 250 us; 2048 x 5120 x 20480 (256x160 tiles): 329 -> 311 us.
 //
 // Tile BM x BN (activation rows x weight rows: 256x160, 256x256, 128x128 or 64x128), BK = 64,
 // 256 threads = 4 waves (one per SIMD).  Operands go global -> LDS directly (no register
@@ -255,8 +256,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
     else f.w[r - TM] = *reinterpret_cast<const u32x4*>(sb + wfrag[ks] + (r - TM) * 16 * kBK);
   };
 
-  // One half.  The 16x16x32 instruction, not 32x32x16: under the chip's power limit it sustains 15 % more with
-  // N(0,1)-like operands (registers only: 2.17 against 1.88 PFLOP/s; the same 2.4 with zeros), and the tiles are
+  // One half.  The 16x16x32 instruction, not 32x32x16: under the chip's power limit it sustains 13 % more with
+  // N(0,1)-like operands (registers only: 1.98 against 1.75 PFLOP/s; with zeros 2.43 and 2.47), and the tiles are
   // walked back and forth so that consecutive instructions share an operand.  It also leaves only 16 cycles between
   // two of them, room for about three other instructions, so the next half's fragment reads and (in the second half
   // of a tile) the global->LDS loads of a later tile are dealt out one at a time, never at the same place: in
@@ -553,6 +554,9 @@ static GemmPlan decode_plan(int M, int N, int K) {
 //    the large tile in whole rounds, the rest runs as a second launch on 256x160 or 128x128 tiles (bias,
 //    residual and output pointers follow the cut).  FFN-in of OPT-13B at 2048 rows: 383 us whole, 348 us as
 //    two rounds of 256x256 tiles plus one of 256x160.
+// The constants were fitted to the loop with 32x32x16 instructions; the present one takes 3 to 6 % less on every tile.
+// Against every forced tile and split count (512, 1024 and 2048 rows of the OPT-13B, 66B and 175B products) the plans
+// are still within 3 % of the fastest, but for one: 512 x 12288 x 12288, 181 us planned, 167 on 128x256 tiles.
 struct TileModel {
   int variant, bm, bn;
   double us_per_kk, t0;

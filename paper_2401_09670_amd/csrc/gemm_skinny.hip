@@ -41,6 +41,9 @@ constexpr int kWeightAux = 2;
 constexpr int kSkThreads = 512;
 constexpr int kSkWaves = kSkThreads / 64;
 constexpr int kSkKS = 64;  // k elements per slab
+// Granularity of K in plans and in the shapes these kernels are given.  Two slabs: the plan's constants were fitted to
+// split counts of that grain, and other multiples of 64 go to the tile kernel.
+constexpr int kSkPlanK = 128;
 
 struct SkinnyParams {
   const uint16_t* X;
@@ -723,14 +726,16 @@ struct SkinnyPlan {
 //   weights + (N/BN) * X (each column block re-reads the activations) + partial sums written and
 //   read back.
 static SkinnyPlan skinny_plan(int M, int N, int K, bool allow_split = true, double* cost_out = nullptr) {
-  const int slabs = K / 128;
+  const int slabs = K / kSkPlanK;
   const int mp = M <= 64 ? 64 : (M <= 128 ? 128 : 256);
   SkinnyPlan best{1, 1};
   double best_cost = 1e300;
   for (int ntw = 1; ntw <= 4; ntw *= 2) {
     if (g_skinny_force_ntw > 0 && ntw != g_skinny_force_ntw) continue;
     const int bn = 64 * ntw;
-    if (mp == 256 && ntw > 1) continue;  // (256 + 128) * 256 B * 2 stages does not fit the LDS
+    // Wider tiles than these are not instantiated: four stages of 256 + 128 or of 128 + 256 rows do not fit the LDS.
+    // (Three do, 144 KB; not tried.  More than 128 rows come here for the greedy choice only.)
+    if (mp == 256 && ntw > 1) continue;
     if (mp == 128 && ntw > 2) continue;
     const int wgs_n = (N + bn - 1) / bn;
     for (int splits = 1; splits <= slabs && splits <= 64; ++splits) {
@@ -759,7 +764,7 @@ static SkinnyPlan skinny_plan(int M, int N, int K, bool allow_split = true, doub
 }
 
 size_t skinny_workspace_bytes(int M, int N, int K) {
-  if (K % 128 != 0 || M > 256) return 0;
+  if (K % kSkPlanK != 0 || M > 256) return 0;
   const SkinnyPlan pl = skinny_plan(M, N, K);  // (also covers the shapes the unsplit kernel takes)
   return pl.splits > 1 ? (size_t)pl.splits * M * N * sizeof(float) : 0;
 }
@@ -805,8 +810,8 @@ static hipError_t launch_wring(int nt, const SkinnyParams& p, hipStream_t stream
 // Column-tile width (in 16-row tiles) for the wave-private-ring kernel, or 0 if the shape is not one it
 // is good at: K a multiple of 256 and enough column tiles to occupy most of the chip without splitting K.
 // Up to 64 rows it takes both widths; for 65..128 rows only the 80-column one, where a workgroup re-reads 1.6
-// activation bytes per weight byte rather than 2 (measured at 128 rows: FFN-in of OPT-13B / 66B and QKV of
-// OPT-175B 18-27 % faster than the split-K ring kernel, every 64-column shape equal or up to 20 % slower).
+// activation bytes per weight byte rather than 2 (measured at 128 rows against the ring kernel: FFN-in of OPT-13B 55 us
+// and 64, of OPT-66B 166 and 201, QKV of OPT-175B 217 and 268; every 64-column shape was equal or up to 20 % slower).
 DS_SWITCH(g_skinny_wring, 1);  // 0 = never use the wave-private-ring kernel, 2 = also where it needs several rounds
 static int wring_tiles(int M, int N, int K) {
   if (!g_skinny_wring || M > 128 || K < 256 || K % 256 != 0) return 0;
@@ -820,11 +825,12 @@ static int wring_tiles(int M, int N, int K) {
   // rows, and from 32 rows up that is as many bytes through a compute unit's load path as the weights.  The
   // split-K ring kernel with 256-column tiles reads a quarter of that and stays within one round; it wins where
   // its bytes (in skinny_plan's terms, reduce launch included) are clearly fewer.  Measured at 64 rows: FFN-in of
-  // OPT-175B 245 -> 214 us, QKV of OPT-66B 107 -> 98 us; QKV of OPT-175B and FFN-in of OPT-66B (two rounds of 80
-  // columns against 144 workgroups of 256) stay here, 6-9 % ahead.
-  // A single round that leaves a fifth of the chip idle is compared the same way (64 rows: 12288 x 49152 on 192
-  // workgroups 278 us, 48 x 5 split 205; 12288 x 12288 76 and 61; 48 rows of 10240 x 8192 on 160 42.3 and 36.0; but
-  // 15360 x 5120 on 240 34.8 and 38).
+  // OPT-175B 219 -> 203 us, QKV of OPT-66B 107 -> 93 us; QKV of OPT-175B and FFN-in of OPT-66B (two rounds of 80
+  // columns against 144 workgroups of 256) stay here, 171 against 184 and 134 against 137.
+  // A single round that leaves a fifth of the chip idle is compared the same way: 12288 x 49152 on 192 workgroups at
+  // 17, 32 and 64 rows 200, 218 and 260 us, 48 x 5 split 185, 187 and 194; 12288 x 12288 at 48 and 64 rows 71 and 76,
+  // split 58 and 58; 10240 x 8192 on 160 at 48 and 64 rows 46 and 48, split 37 and 37.5.  15360 x 5120 on 240 is not:
+  // 32.5 and 34.9 at 48 rows, 34.6 and 37.4 at 64.
   const int rounds = nt == 5 ? r5 : r4;
   if ((rounds > 1 || tiles < 208) && M > 16 && g_skinny_wring != 2) {
     const double rows = M <= 32 ? 32 : (M <= 64 ? 64 : 128);
@@ -854,7 +860,7 @@ hipError_t launch_argmax_merge(const float* part_val, const int32_t* part_idx, i
                                int32_t* next_token, float* best_logit, hipStream_t stream);
 
 size_t skinny_argmax_workspace_bytes(int M, int N, int K) {
-  if (K % 128 != 0 || M > 256 || M <= 0 || N <= 0) return 0;
+  if (K % kSkPlanK != 0 || M > 256 || M <= 0 || N <= 0) return 0;
   const SkinnyPlan pl = skinny_plan(M, N, K, false);
   const size_t blocks = (size_t)(N + 64 * pl.ntw - 1) / (64 * pl.ntw);
   return blocks * M * (sizeof(float) + sizeof(int32_t));
@@ -862,7 +868,7 @@ size_t skinny_argmax_workspace_bytes(int M, int N, int K) {
 
 hipError_t launch_skinny_argmax(const void* X, const void* W, int M, int N, int K, void* workspace,
                                 int32_t* next_token, float* best_logit, hipStream_t stream) {
-  if (M <= 0 || M > 256 || N <= 0 || K % 128 != 0 || !workspace || !next_token) return hipErrorInvalidValue;
+  if (M <= 0 || M > 256 || N <= 0 || K % kSkPlanK != 0 || !workspace || !next_token) return hipErrorInvalidValue;
   const SkinnyPlan pl = skinny_plan(M, N, K, false);
   const int blocks = (N + 64 * pl.ntw - 1) / (64 * pl.ntw);
   SkinnyParams p;
@@ -943,7 +949,7 @@ hipError_t launch_skinny_gemm(const void* X, const void* W, int M, int N, int K,
                               void* workspace, hipStream_t stream, const SkinnyFused* fused, bool* fused_done) {
   if (fused_done) *fused_done = false;
   if (M <= 0 || N <= 0) return hipSuccess;
-  if (M > 256 || K % 128 != 0 || N % 8 != 0 || ep.seg_cols <= 0 || ep.seg_cols % 8 != 0 || ep.seg_cols_kv < 0 ||
+  if (M > 256 || K % kSkPlanK != 0 || N % 8 != 0 || ep.seg_cols <= 0 || ep.seg_cols % 8 != 0 || ep.seg_cols_kv < 0 ||
       ep.seg_cols_kv % 8 != 0)
     return hipErrorInvalidValue;
   if (ep.residual && ep.seg_cols != N) return hipErrorInvalidValue;
