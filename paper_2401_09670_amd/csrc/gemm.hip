@@ -554,7 +554,8 @@ static GemmPlan decode_plan(int M, int N, int K) {
 //    the large tile in whole rounds, the rest runs as a second launch on 256x160 or 128x128 tiles (bias,
 //    residual and output pointers follow the cut).  FFN-in of OPT-13B at 2048 rows: 383 us whole, 348 us as
 //    two rounds of 256x256 tiles plus one of 256x160.
-// The constants were fitted to the loop with 32x32x16 instructions; the present one takes 3 to 6 % less on every tile.
+// The constants were fitted to the loop with 32x32x16 instructions; from 512 rows up the present one takes 5 % less on
+// 256x160 tiles, 4 % on 256x256 and 128x256 (nothing where 256x256 tiles are split), 2 % on 128x128.
 // Against every forced tile and split count (512, 1024 and 2048 rows of the OPT-13B, 66B and 175B products) the plans
 // are still within 3 % of the fastest, but for one: 512 x 12288 x 12288, 181 us planned, 167 on 128x256 tiles.
 struct TileModel {
