@@ -14,7 +14,8 @@
 //
 // Tile BM x BN (activation rows x weight rows: 256x160, 256x256, 128x128 or 64x128), BK = 64,
 // 256 threads = 4 waves (one per SIMD).  Operands go global -> LDS directly (no register
-// staging), three LDS buffers (two for the 256x256 tile), one barrier per k-tile; fragment reads and load issue are
+// staging) into two LDS rings, one per operand (three stages each; two of activations and three of weights for the
+// 256x256 tile), one barrier per k-tile; fragment reads and load issue are
 // interleaved with the MFMAs by hand (scheduling fences); the epilogue is
 // staged through LDS so bias / residual / output move as 16-byte row pieces.
 #include <type_traits>
@@ -29,8 +30,8 @@ constexpr int kBK = 64;
 // LDS a workgroup asks for: its ring of operand stages - or the whole 160 KB of the compute unit once the ring
 // alone is more than half of it (a second workgroup could not move in anyway), which gives the epilogue a
 // larger staging area: more columns per pass, longer contiguous row pieces in the output stores.
-constexpr int gemm_lds_bytes(int BM, int BN, int STAGES) {
-  const int ring = STAGES * (BM + BN) * kBK * 2;
+constexpr int gemm_lds_bytes(int BM, int BN, int XS, int WS) {
+  const int ring = (XS * BM + WS * BN) * kBK * 2;
   return ring > 80 * 1024 ? 160 * 1024 : ring;
 }
 
@@ -112,8 +113,8 @@ __device__ __forceinline__ void patch_tile(int pid, int tiles_m, int tiles_n, in
 // avoided by an XOR swizzle applied on the *global* side: LDS row r holds
 // 16-byte chunk c at position c ^ ((r >> 1) & 7).  Rows are 128 bytes = half
 // of the 64 banks, so even/odd rows use different halves and any 16
-// consecutive rows read at the same chunk index cover all 64 banks once.  STAGES LDS buffers; the load of k-tile
-// kt+STAGES-1 is in flight while k-tile kt is multiplied.
+// consecutive rows read at the same chunk index cover all 64 banks once.  The operands have rings of their own, of
+// XS and WS >= XS stages: the loads of X k-tile kt+XS and W k-tile kt+WS are issued while k-tile kt is multiplied.
 // ---------------------------------------------------------------------------
 template <int VM>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -140,7 +141,7 @@ __device__ __forceinline__ void mfma_acc(floatx4& acc, const u32x4& w, const u32
 // 2 = as 0, but the K and V thirds go into the paged cache.
 enum { kEpiPlain = 0, kEpiPartial = 1, kEpiKvScatter = 2 };
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int EPI>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int XS, int WS, int EPI>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const GemmParams p) {
   // One wave per SIMD.  (Eight waves - two per SIMD, 128 accumulator registers each - were measured on the
   // 256x256 tile: equal as 4x2 waves of 64x128, 7 % slower as 2x4 of 128x64; the loop is not latency-bound.)
@@ -151,11 +152,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   static_assert(WTM % 16 == 0 && WTN % 32 == 0, "the epilogue stages 32 columns of a wave tile at a time");
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "a wave-level load covers 8 rows");
   constexpr int ROW_BYTES = kBK * 2;                      // 128
-  constexpr int STAGE_ELEMS = (BM + BN) * kBK;            // elements per stage
+  constexpr int W_RING = XS * BM * kBK;                   // the weight ring starts behind the activation ring (elements)
   constexpr int XL = BM / (8 * NW);                       // X loads per wave per stage
   constexpr int WL = BN / (8 * NW);                       // W loads per wave per stage
   constexpr int LPS = XL + WL;
-  static_assert((STAGES - 1) * LPS < 64, "vmcnt range");
+  static_assert(XS >= 2 && WS >= XS && (XS - 1) * LPS + WL < 64, "rings, vmcnt range");
 
   extern __shared__ __attribute__((aligned(1024))) uint16_t lds[];
 
@@ -196,28 +197,20 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
     woff[j] = ((uint32_t)row * (uint32_t)K + lchunk * 8) * 2u;
   }
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);  // keep LDS destinations in scalar registers
-  // Loads k-tile `kt_load` into buffer `stage`.  Tiles past the end are clamped to the last one (a
-  // harmless re-load into a buffer nobody reads again): this keeps the main loop free of branches, so
-  // the loads can be interleaved with MFMAs by the scheduler.
-  auto issue_one = [&](int stage, int kt_load, int j) {   // j in [0, LPS): X loads first, then W loads
-    const size_t kofs = (size_t)((kt_first + min(kt_load, KT - 1) * kt_step) * kBK) * 2;   // bytes
-    uint16_t* xb = lds + stage * STAGE_ELEMS + wave_s * 512;     // 512 elements = 1 KB per wave-load
+  // Load number j of iteration kt, in [0, LPS): of X tile kt + XS first, into X stage `xst`, then of W tile kt + WS, into
+  // W stage `wst`.  Tiles past the end are clamped to the last one (a harmless re-load into a buffer nobody reads
+  // again): this keeps the main loop free of branches, so the loads can be interleaved with MFMAs by the scheduler.
+  auto issue_one = [&](int xst, int wst, int kt, int j) {
     // (the empty asm keeps the 32-bit lane offset a value of this basic block: hoisted out of the loop as a
     // 64-bit pair it costs a 64-bit vector add per load instead of riding in the instruction's offset operand)
     uint32_t& off = j < XL ? xoff[j < XL ? j : 0] : woff[j < XL ? 0 : j - XL];
     asm volatile("" : "+v"(off));
-    if (j < XL) {
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xbase + kofs + off),
-                                       (__attribute__((address_space(3))) void*)(xb + j * NW * 512), 16, 0, 0);
-    } else {
-      __builtin_amdgcn_global_load_lds(
-          (const __attribute__((address_space(1))) void*)(wbase + kofs + off),
-          (__attribute__((address_space(3))) void*)(xb + BM * kBK + (j - XL) * NW * 512), 16, 0, 0);
-    }
-  };
-  auto issue = [&](int stage, int kt_load) {
-#pragma unroll
-    for (int j = 0; j < LPS; ++j) issue_one(stage, kt_load, j);
+    const bool of_x = j < XL;
+    const size_t kofs = (size_t)((kt_first + min(kt + (of_x ? XS : WS), KT - 1) * kt_step) * kBK) * 2;   // bytes
+    uint16_t* dst = lds + (of_x ? xst * BM * kBK + j * NW * 512 : W_RING + wst * BN * kBK + (j - XL) * NW * 512) +
+                    wave_s * 512;   // 512 elements = 1 KB per wave-load
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((of_x ? xbase : wbase) + kofs + off),
+                                     (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
   };
 
   floatx4 acc[TN][TM];
@@ -236,7 +229,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   for (int ks = 0; ks < kBK / 32; ++ks) {
     const int koff = ((4 * ks + (lane >> 4)) ^ ((lane >> 1) & 7)) * 8;
     xfrag[ks] = (wm * WTM + frag_row) * kBK + koff;
-    wfrag[ks] = BM * kBK + (wn * WTN + frag_row) * kBK + koff;
+    wfrag[ks] = W_RING + (wn * WTN + frag_row) * kBK + koff;
     asm volatile("" : "+v"(xfrag[ks]), "+v"(wfrag[ks]));
   }
 
@@ -249,11 +242,15 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   };
   Frags fa, fb;
   constexpr int NR = TN + TM;  // fragment reads per half
-  // read number r of k-step ks of stage buffer sb
-  auto frag_read = [&](Frags& f, const uint16_t* sb, int ks, int r) {
-    if (r == 0) f.w[0] = *reinterpret_cast<const u32x4*>(sb + wfrag[ks]);
-    else if (r <= TM) f.x[r - 1] = *reinterpret_cast<const u32x4*>(sb + xfrag[ks] + (r - 1) * 16 * kBK);
-    else f.w[r - TM] = *reinterpret_cast<const u32x4*>(sb + wfrag[ks] + (r - TM) * 16 * kBK);
+  // read number r of k-step ks of the stage buffers sb
+  struct Bufs {
+    const uint16_t *x, *w;
+  };
+  auto bufs = [&](int xst, int wst) { return Bufs{lds + xst * BM * kBK, lds + wst * BN * kBK}; };
+  auto frag_read = [&](Frags& f, const Bufs& sb, int ks, int r) {
+    if (r == 0) f.w[0] = *reinterpret_cast<const u32x4*>(sb.w + wfrag[ks]);
+    else if (r <= TM) f.x[r - 1] = *reinterpret_cast<const u32x4*>(sb.x + xfrag[ks] + (r - 1) * 16 * kBK);
+    else f.w[r - TM] = *reinterpret_cast<const u32x4*>(sb.w + wfrag[ks] + (r - TM) * 16 * kBK);
   };
 
   // One half.  The 16x16x32 instruction, not 32x32x16: under the chip's power limit it sustains 13 % more with
@@ -265,7 +262,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   // first and end three quarters into the half, so that the barrier (or the next half) does not wait for the last.
   // A scheduling fence after every group keeps that interleaving.  (256x256 prefers groups of one, the rest of two.)
   // `last` marks the last k-tile.  `mem(j)` is called for j = 0 .. JN-1: it issues the j-th direct-to-LDS load.
-  auto half = [&](auto jn, auto last, const Frags& fc, Frags& fn, const uint16_t* sb_next, int ks_next, auto&& mem) {
+  auto half = [&](auto jn, auto last, const Frags& fc, Frags& fn, const Bufs& sb_next, int ks_next, auto&& mem) {
     constexpr int NM = TM * TN, GRP = NM >= 64 ? 1 : 2, NG = NM / GRP, NGR = NG > 4 ? NG * 3 / 4 : NG;
     static_assert(NM % GRP == 0, "whole groups");
     constexpr int JN = decltype(jn)::value;
@@ -298,7 +295,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   // Each wave stages its own WTM x (GA*32) fp32 block (GA column tiles per pass) in LDS that the
   // k-loop no longer needs; rows are padded by 4 floats so the 16-byte transposing writes of 16
   // lanes fall into distinct banks.
-  constexpr int LDS_FLOATS = gemm_lds_bytes(BM, BN, STAGES) / 4;
+  constexpr int LDS_FLOATS = gemm_lds_bytes(BM, BN, XS, WS) / 4;
   constexpr int GA_FIT = (LDS_FLOATS / (NW * WTM) - 4) / 32;
   constexpr int TG = WTN / 32;  // groups of 32 columns of a wave tile
   constexpr int GA = GA_FIT < TG ? GA_FIT : TG;
@@ -332,37 +329,45 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   };
 
   {
-    // Direct-to-LDS schedule (3 LDS buffers, ONE barrier per k-tile, two k-tiles of flight time):
-    //   (written for STAGES = 3; see below for 2)
+    // Direct-to-LDS schedule (one ring per operand, ONE barrier per k-tile):
     //   iteration kt:  first half of tile kt (fetching the fragments of its second half)
-    //                  wait until this wave's part of tile kt+1 has landed (tile kt+2 may still fly)
-    //                  barrier: tile kt+1 is visible to all, and nobody reads buffer kt%3 any more
+    //                  wait until this wave's part of tile kt+1 has landed (later ones may still fly)
+    //                  barrier: tile kt+1 is visible to all, and nobody reads the buffers of tile kt any more
     //                           (the second half's fragments are already in registers)
-    //                  second half of tile kt, issuing the loads of tile kt+3 into buffer kt%3 and
-    //                  fetching the first-half fragments of tile kt+1
-    // With two buffers the same schedule holds with one k-tile of flight time: at the barrier tile
-    // kt+1 (requested during the second half of tile kt-1) must have landed completely.
-    static_assert(STAGES == 2 || STAGES == 3, "ring of 2 or 3 buffers");
+    //                  second half of tile kt, issuing the loads of X tile kt+XS, then of W tile kt+WS, into the
+    //                  buffers of tile kt, and fetching the first-half fragments of tile kt+1
+    // Loads land in the order of their issue, so with WS > XS the weights asked for right behind X tile kt+1 may still
+    // fly at iteration kt's barrier: they have a k-tile longer than with WS = XS.  256x256 has room for two stages of
+    // both (128 KB) or for a third one of weights (160 KB), which the kernels that wait for weights need most.  From two
+    // stages each: 4096 x 12288 x 49152 4.05 -> 3.37 ms (rows of X 96 KB apart), 256 x 49152 x 12288 371 -> 350 us,
+    // 1536 x 20480 x 5120 254 -> 232, 2985 x 15360 x 5120 371 -> 357, 16384 x 12288 x 12288 3.36 -> 3.32 ms.  (256x160
+    // and 128x256 tiles with two and four stages instead of three each: some 1-4 % faster, as many as much slower.)
+    // the loads of iterations -WS to -1, as far as they are of tiles from 0 on
 #pragma unroll
-    for (int st = 0; st < STAGES; ++st) issue(st, st);
-    wait_vmcnt<(STAGES - 1) * LPS>();
+    for (int i = -WS; i < 0; ++i) {
+#pragma unroll
+      for (int j = 0; j < LPS; ++j)
+        if (j >= XL || i >= -XS) issue_one(i + XS, i + WS, i, j);
+    }
+    constexpr int IN_FLIGHT = (XS - 2) * LPS + (WS > XS ? WL : 0);  // loads issued after the last of tile kt+1
+    wait_vmcnt<IN_FLIGHT + LPS>();
     lds_barrier();
     DS_STAMP(1);
 #pragma unroll
-    for (int r = 0; r < NR; ++r) frag_read(fa, lds, 0, r);
+    for (int r = 0; r < NR; ++r) frag_read(fa, bufs(0, 0), 0, r);
 
-    int stage = 0;  // buffer of tile kt
+    int xst = 0, wst = 0;  // buffers of tile kt
     for (int kt = 0; kt < KT - 1; ++kt) {
-      const uint16_t* sb = lds + stage * STAGE_ELEMS;
-      int nstage = stage + 1;
-      if (nstage == STAGES) nstage = 0;
-      const uint16_t* sbn = lds + nstage * STAGE_ELEMS;
+      const Bufs sb = bufs(xst, wst);
+      const int nx = xst + 1 == XS ? 0 : xst + 1, nw = wst + 1 == WS ? 0 : wst + 1;
+      const Bufs sbn = bufs(nx, nw);
       __builtin_amdgcn_sched_barrier(0);
       half(none{}, std::false_type{}, fa, fb, sb, 1, no_mem);
-      wait_vmcnt<(STAGES - 2) * LPS>();
+      wait_vmcnt<IN_FLIGHT>();
       lds_barrier();
-      half(all_loads{}, std::false_type{}, fb, fa, sbn, 0, [&](int j) { issue_one(stage, kt + STAGES, j); });
-      stage = nstage;
+      half(all_loads{}, std::false_type{}, fb, fa, sbn, 0, [&](int j) { issue_one(xst, wst, kt, j); });
+      xst = nx;
+      wst = nw;
     }
     // Last k-tile (already in LDS and visible since the previous iteration's barrier): no loads, no
     // waits.  The residual and bias pieces of the first epilogue pass are requested before it, so
@@ -371,7 +376,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
     constexpr bool EARLY_EPI = TM * TN <= 40;
     if (EARLY_EPI) epi_prefetch(0, epi_res[0], epi_bias[0]);
     {
-      const uint16_t* sb = lds + stage * STAGE_ELEMS;
+      const Bufs sb = bufs(xst, wst);
       __builtin_amdgcn_sched_barrier(0);
       half(none{}, std::true_type{}, fa, fb, sb, 1, no_mem);
       // (the fragment fetch of this half reads a buffer of clamped re-loads; the values are never used)
@@ -460,23 +465,23 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   DS_STAMP(3);
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, int EPI>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int XS, int WS, int EPI>
 static hipError_t launch_dl_epi(GemmParams p, int splits, hipStream_t stream) {
   p.tiles_m = (p.M + BM - 1) / BM;
   p.tiles_n = (p.N - p.n_base + BN - 1) / BN;
-  constexpr size_t lds_bytes = gemm_lds_bytes(BM, BN, STAGES);
-  static_assert((size_t)STAGES * (BM + BN) * kBK * sizeof(uint16_t) <= lds_bytes && lds_bytes <= 160 * 1024, "LDS");
-  constexpr auto kern = gemm_dl_kernel<BM, BN, WAVES_M, WAVES_N, STAGES, EPI>;
+  constexpr size_t lds_bytes = gemm_lds_bytes(BM, BN, XS, WS);
+  static_assert((size_t)(XS * BM + WS * BN) * kBK * sizeof(uint16_t) <= lds_bytes && lds_bytes <= 160 * 1024, "LDS");
+  constexpr auto kern = gemm_dl_kernel<BM, BN, WAVES_M, WAVES_N, XS, WS, EPI>;
   (void)KernelAttrReg<kern, (int)lds_bytes>::done;
   hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n, splits), dim3(64 * WAVES_M * WAVES_N), lds_bytes, stream, p);
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int STAGES, bool KV_OK>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int XS, int WS, bool KV_OK>
 static hipError_t launch_dl(const GemmParams& p, int splits, hipStream_t stream) {
-  if (splits > 1) return launch_dl_epi<BM, BN, WAVES_M, WAVES_N, STAGES, kEpiPartial>(p, splits, stream);
-  if (KV_OK && p.k_cache) return launch_dl_epi<BM, BN, WAVES_M, WAVES_N, STAGES, kEpiKvScatter>(p, 1, stream);
-  return launch_dl_epi<BM, BN, WAVES_M, WAVES_N, STAGES, kEpiPlain>(p, 1, stream);
+  if (splits > 1) return launch_dl_epi<BM, BN, WAVES_M, WAVES_N, XS, WS, kEpiPartial>(p, splits, stream);
+  if (KV_OK && p.k_cache) return launch_dl_epi<BM, BN, WAVES_M, WAVES_N, XS, WS, kEpiKvScatter>(p, 1, stream);
+  return launch_dl_epi<BM, BN, WAVES_M, WAVES_N, XS, WS, kEpiPlain>(p, 1, stream);
 }
 
 // Cost model used to pick a tile shape: (rounds of workgroups on 256 CUs, one workgroup per CU) x
@@ -727,21 +732,21 @@ hipError_t launch_gemm(const void* X, const void* W, int M, int N, int K, const 
     GemmParams a = p, b = p;
     a.N = pl.cut_cols;
     b.n_base = pl.cut_cols;
-    e = pl.variant == 3 ? launch_dl<256, 256, 2, 2, 2, false>(a, 1, stream)
-                        : launch_dl<256, 160, 4, 1, 3, false>(a, 1, stream);
+    e = pl.variant == 3 ? launch_dl<256, 256, 2, 2, 2, 3, false>(a, 1, stream)
+                        : launch_dl<256, 160, 4, 1, 3, 3, false>(a, 1, stream);
     if (e != hipSuccess) return e;
     switch (pl.tail_variant) {
-      case 1: return launch_dl<256, 160, 4, 1, 3, false>(b, 1, stream);
-      case 7: return launch_dl_epi<256, 128, 4, 1, 3, kEpiPlain>(b, 1, stream);
-      default: return launch_dl<128, 128, 2, 2, 3, true>(b, 1, stream);
+      case 1: return launch_dl<256, 160, 4, 1, 3, 3, false>(b, 1, stream);
+      case 7: return launch_dl_epi<256, 128, 4, 1, 3, 3, kEpiPlain>(b, 1, stream);
+      default: return launch_dl<128, 128, 2, 2, 3, 3, true>(b, 1, stream);
     }
   }
   switch (pl.variant) {
-    case 5: e = launch_dl<128, 256, 2, 2, 3, false>(p, pl.splits, stream); break;
-    case 4: e = launch_dl<64, 128, 1, 4, 3, true>(p, pl.splits, stream); break;
-    case 3: e = launch_dl<256, 256, 2, 2, 2, false>(p, pl.splits, stream); break;
-    case 2: e = launch_dl<128, 128, 2, 2, 3, true>(p, pl.splits, stream); break;
-    default: e = launch_dl<256, 160, 4, 1, 3, false>(p, pl.splits, stream); break;
+    case 5: e = launch_dl<128, 256, 2, 2, 3, 3, false>(p, pl.splits, stream); break;
+    case 4: e = launch_dl<64, 128, 1, 4, 3, 3, true>(p, pl.splits, stream); break;
+    case 3: e = launch_dl<256, 256, 2, 2, 2, 3, false>(p, pl.splits, stream); break;
+    case 2: e = launch_dl<128, 128, 2, 2, 3, 3, true>(p, pl.splits, stream); break;
+    default: e = launch_dl<256, 160, 4, 1, 3, 3, false>(p, pl.splits, stream); break;
   }
   if (e != hipSuccess) return e;
   if (pl.splits > 1) e = launch_splitk_reduce(p.partial, pl.splits, M, N, ep, fused, fused_done, stream);
