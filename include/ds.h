@@ -102,11 +102,13 @@ const char *ds_last_error(const ds_ctx *ctx);
  * ctx_lens[i] + 1 lies in [1, max_ctx] (kv_lens[i] in [0, max_kv_len]). */
 ds_status ds_set_validate(ds_ctx *ctx, int32_t on);
 
-/* Workspace (device bytes) ds_prefill needs for up to max_tokens packed tokens.
+/* Workspace (device bytes) for ds_prefill with up to max_tokens packed tokens.
  * Both sizes are upper bounds over all smaller calls: a workspace sized for the
- * largest batch serves every call with fewer tokens / sequences / cached tokens. */
+ * largest batch serves every call with fewer tokens / sequences / cached tokens.
+ * A call with less still runs, on plans that split less, as long as the activations and the partial
+ * sums of ds_linear's plans for its four products (ds_linear_workspace_bytes) fit. */
 size_t ds_prefill_workspace_bytes(const ds_ctx *ctx, int32_t max_tokens);
-/* Workspace ds_decode_step needs for up to max_batch sequences of up to max_ctx cached tokens. */
+/* The same for ds_decode_step with up to max_batch sequences of up to max_ctx cached tokens. */
 size_t ds_decode_workspace_bytes(const ds_ctx *ctx, int32_t max_batch, int32_t max_ctx);
 
 /*
@@ -198,6 +200,11 @@ size_t ds_linear_workspace_bytes(const ds_ctx *ctx, int32_t rows, int32_t in_f, 
  * to fill the chip (Sec. 3.1). */
 ds_status ds_linear_plan(const ds_ctx *ctx, int32_t rows, int32_t in_f, int32_t out_f, int32_t *streaming,
                          int32_t *tile_rows, int32_t *tile_cols, int32_t *splits, int32_t *cut_cols);
+/* The same for the product as ds_prefill and ds_decode_step run it, given the workspace of ds_*_workspace_bytes: from 65
+ * rows on they choose among more tile shapes and split further than ds_linear, whose plan and workspace stay what
+ * its two queries say. */
+ds_status ds_layer_plan(const ds_ctx *ctx, int32_t rows, int32_t in_f, int32_t out_f, int32_t *streaming,
+                        int32_t *tile_rows, int32_t *tile_cols, int32_t *splits, int32_t *cut_cols);
 ds_status ds_linear(ds_ctx *ctx, const void *x, const void *w, const void *bias,
                     const void *residual, int32_t relu, int32_t rows, int32_t in_f, int32_t out_f,
                     void *y, void *workspace, size_t workspace_bytes, void *stream);

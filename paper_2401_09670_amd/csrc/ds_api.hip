@@ -29,8 +29,11 @@ struct ds_ctx {
   std::vector<hipEvent_t> pool;
   // Workspace sizes already worked out (they walk every smaller row count through the GEMM planners, tens of
   // microseconds; every ds_prefill / ds_decode_step call checks its workspace against them).
-  mutable std::map<int, size_t> prefill_ws;
-  mutable std::map<std::pair<int, int>, size_t> decode_ws;
+  struct Workspace {
+    size_t least, full;  // below `least` a call is refused, from `full` on every product has its fastest plan
+  };
+  mutable std::map<int, Workspace> prefill_ws;
+  mutable std::map<std::pair<int, int>, Workspace> decode_ws;
 };
 
 // ---- per-device set-up: kernel attributes, address of the static scratch array ----
@@ -226,6 +229,38 @@ ds_status linear(ds_ctx* ctx, const void* x, const void* w, int rows, int in_f, 
   return DS_OK;
 }
 
+// One product of ds_prefill or ds_decode_step: as `linear`, but from 65 rows on by the layer's own plans, which may
+// split K as far as `ws_bytes` of partial sums go.
+constexpr int kLayerMinRows = 65, kLayerMaxRows = 4096;
+bool layer_tiles(int rows, int in_f, int out_f, size_t ws_bytes, ds::GemmPlan* plan) {
+  if (rows < kLayerMinRows || rows > kLayerMaxRows) return false;
+  double us;
+  *plan = ds::layer_plan(rows, out_f, in_f, ws_bytes, &us);
+  return !use_skinny(rows, in_f) || us < 0.97 * ds::skinny_us(rows, out_f, in_f);
+}
+
+// How often the tile kernel splits K of such a product; 0 = it runs on the streaming kernels.
+int layer_splits(int rows, int in_f, int out_f, size_t ws_bytes) {
+  ds::GemmPlan plan;
+  if (layer_tiles(rows, in_f, out_f, ws_bytes, &plan)) return plan.splits;
+  return use_skinny(rows, in_f) ? 0 : ds::gemm_splits(rows, out_f, in_f);
+}
+
+ds_status layer_linear(ds_ctx* ctx, const void* x, const void* w, int rows, int in_f, int out_f,
+                       const ds::Epilogue& ep, void* gemm_ws, size_t ws_bytes, hipStream_t stream,
+                       const ds::SkinnyFused* fused = nullptr, bool* fused_done = nullptr) {
+  ds::GemmPlan plan;
+  if (!layer_tiles(rows, in_f, out_f, ws_bytes, &plan))
+    return linear(ctx, x, w, rows, in_f, out_f, ep, gemm_ws, stream, fused, fused_done);
+  hipError_t e;
+  {
+    Timed t(ctx, stream, rows <= kSkinnyMaxRows ? DS_K_SKINNY_GEMM : DS_K_GEMM);
+    e = ds::launch_gemm(x, w, rows, out_f, in_f, ep, plan, stream, gemm_ws, fused, fused_done);
+  }
+  if (e != hipSuccess) return fail(ctx, DS_ERR_HIP, "gemm failed: %s", hipGetErrorString(e));
+  return DS_OK;
+}
+
 // split-K partials of the kernel that `linear` picks for exactly `rows` rows
 size_t linear_ws_exact(int rows, int in_f, int out_f) {
   return use_skinny(rows, in_f) ? ds::skinny_workspace_bytes(rows, out_f, in_f)
@@ -245,14 +280,31 @@ size_t linear_ws(int rows, int in_f, int out_f) {
   return b > need ? b : need;
 }
 
-size_t max_gemm_ws(const ds_model_cfg& c, int rows) {
-  size_t a = linear_ws(rows, c.hidden, qkv_width(c));
-  size_t b = linear_ws(rows, c.hidden, c.hidden);
-  size_t d = linear_ws(rows, c.hidden, c.ffn);
-  size_t e = linear_ws(rows, c.ffn, c.hidden);
-  size_t m = a > b ? a : b;
-  m = m > d ? m : d;
-  return m > e ? m : e;
+// Partial sums of the layer's own plans for any row count up to `rows`: they go by rows in 32s.
+size_t layer_ws(int rows, int in_f, int out_f) {
+  size_t need = 0;
+  const int last = rows < kLayerMaxRows ? rows : kLayerMaxRows;
+  for (int r = (kLayerMinRows + 31) / 32 * 32; r < last + 32; r += 32) {
+    const ds::GemmPlan plan = ds::layer_plan(r, out_f, in_f, ~(size_t)0);
+    const size_t b = plan.splits > 1 ? sizeof(float) * plan.splits * r * (size_t)out_f : 0;
+    if (b > need) need = b;
+  }
+  return need;
+}
+
+// ... of the four products of a layer: what the plans of `linear` need, and what the layer's own would use
+ds_ctx::Workspace max_gemm_ws(const ds_model_cfg& c, int rows) {
+  const int shapes[4][2] = {{c.hidden, qkv_width(c)}, {c.hidden, c.hidden}, {c.hidden, c.ffn}, {c.ffn, c.hidden}};
+  ds_ctx::Workspace ws{0, 0};
+  for (const auto& f : shapes) {
+    const size_t least = linear_ws(rows, f[0], f[1]), full = layer_ws(rows, f[0], f[1]);
+    if (least > ws.least) ws.least = least;
+    if (full > ws.full) ws.full = full;
+  }
+  if (ws.full < ws.least) ws.full = ws.least;
+  ws.least = align_up(ws.least, 256);
+  ws.full = align_up(ws.full, 256);
+  return ws;
 }
 
 // Every call that launches goes through here first: the device's one-time set-up (normally done by ds_create;
@@ -337,6 +389,44 @@ ds_status check_weights(ds_ctx* ctx, const ds_layer_weights* w) {
   return DS_OK;
 }
 
+ds_ctx::Workspace prefill_workspace(const ds_ctx* ctx, int max_tokens) {
+  const auto hit = ctx->prefill_ws.find(max_tokens);
+  if (hit != ctx->prefill_ws.end()) return hit->second;
+  const ds_model_cfg& c = ctx->cfg;
+  const size_t th = align_up((size_t)max_tokens * c.hidden * 2, 256);
+  const size_t tm = align_up((size_t)max_tokens * (c.ffn + kRowPad) * 2, 256);
+  // a (LN out, reused for LN2), q, o, x1, u (rows padded), + split-K partials of the GEMMs
+  ds_ctx::Workspace need = max_gemm_ws(c, max_tokens);
+  need.least += 4 * th + tm;
+  need.full += 4 * th + tm;
+  if (ctx->prefill_ws.size() < 4096) ctx->prefill_ws[max_tokens] = need;
+  return need;
+}
+
+ds_ctx::Workspace decode_workspace(const ds_ctx* ctx, int max_batch, int max_ctx) {
+  // the attention partials depend on max_ctx only through its page count
+  const std::pair<int, int> key(max_batch, (max_ctx + 15) / 16);
+  const auto hit = ctx->decode_ws.find(key);
+  if (hit != ctx->decode_ws.end()) return hit->second;
+  const ds_model_cfg& c = ctx->cfg;
+  const size_t bh = align_up((size_t)max_batch * c.hidden * 2, 256);
+  const size_t b3h = align_up((size_t)max_batch * qkv_width(c) * 2, 256);
+  const size_t bm = align_up((size_t)max_batch * c.ffn * 2, 256);
+  // fewer sequences can mean more splits of the KV axis: size the partials for any batch up to max_batch
+  size_t att = 0;
+  for (int b = 1; b <= max_batch; ++b) {
+    const size_t v = ds::decode_attention_workspace_bytes(b, c.n_heads, c.n_kv_heads, c.head_dim, max_ctx);
+    if (v > att) att = v;
+  }
+  // a, qkv, o, x1, u, attention partials, split-K partials
+  const size_t rest = 3 * bh + b3h + bm + align_up(att, 256);
+  ds_ctx::Workspace need = max_gemm_ws(c, max_batch);
+  need.least += rest;
+  need.full += rest;
+  if (ctx->decode_ws.size() < 4096) ctx->decode_ws[key] = need;
+  return need;
+}
+
 }  // namespace
 
 extern "C" {
@@ -388,40 +478,11 @@ void ds_destroy(ds_ctx* ctx) {
 const char* ds_last_error(const ds_ctx* ctx) { return ctx ? ctx->err : "ctx is NULL"; }
 
 size_t ds_prefill_workspace_bytes(const ds_ctx* ctx, int32_t max_tokens) {
-  if (!ctx || max_tokens <= 0) return 0;
-  const auto hit = ctx->prefill_ws.find(max_tokens);
-  if (hit != ctx->prefill_ws.end()) return hit->second;
-  const ds_model_cfg& c = ctx->cfg;
-  const size_t th = align_up((size_t)max_tokens * c.hidden * 2, 256);
-  const size_t tm = align_up((size_t)max_tokens * (c.ffn + kRowPad) * 2, 256);
-  // a (LN out, reused for LN2), q, o, x1, u (rows padded), + split-K partials of the GEMMs
-  const size_t need = 4 * th + tm + align_up(max_gemm_ws(c, max_tokens), 256);
-  if (ctx->prefill_ws.size() < 4096) ctx->prefill_ws[max_tokens] = need;
-  return need;
+  return ctx && max_tokens > 0 ? prefill_workspace(ctx, max_tokens).full : 0;
 }
 
 size_t ds_decode_workspace_bytes(const ds_ctx* ctx, int32_t max_batch, int32_t max_ctx) {
-  if (!ctx || max_batch <= 0 || max_ctx <= 0) return 0;
-  // the attention partials depend on max_ctx only through its page count
-  const std::pair<int, int> key(max_batch, (max_ctx + 15) / 16);
-  const auto hit = ctx->decode_ws.find(key);
-  if (hit != ctx->decode_ws.end()) return hit->second;
-  const ds_model_cfg& c = ctx->cfg;
-  const size_t bh = align_up((size_t)max_batch * c.hidden * 2, 256);
-  const size_t b3h = align_up((size_t)max_batch * qkv_width(c) * 2, 256);
-  const size_t bm = align_up((size_t)max_batch * c.ffn * 2, 256);
-  // fewer sequences can mean more splits of the KV axis: size the partials for any batch up to max_batch
-  size_t att = 0;
-  for (int b = 1; b <= max_batch; ++b) {
-    const size_t v = ds::decode_attention_workspace_bytes(b, c.n_heads, c.n_kv_heads, c.head_dim, max_ctx);
-    if (v > att) att = v;
-  }
-  att = align_up(att, 256);
-  const size_t sk = align_up(max_gemm_ws(c, max_batch), 256);
-  // a, qkv, o, x1, u, attention partials, split-K partials
-  const size_t need = 3 * bh + b3h + bm + att + sk;
-  if (ctx->decode_ws.size() < 4096) ctx->decode_ws[key] = need;
-  return need;
+  return ctx && max_batch > 0 && max_ctx > 0 ? decode_workspace(ctx, max_batch, max_ctx).full : 0;
 }
 
 ds_status ds_layernorm(ds_ctx* ctx, const void* x, const void* gamma, const void* beta, int32_t rows,
@@ -458,6 +519,18 @@ ds_status ds_linear_plan(const ds_ctx* ctx, int32_t rows, int32_t in_f, int32_t 
     ds::gemm_describe(rows, out_f, in_f, &tr, &tc, &sp, &cut);
     *tile_rows = tr; *tile_cols = tc; *splits = sp; *cut_cols = cut;
   }
+  return DS_OK;
+}
+
+ds_status ds_layer_plan(const ds_ctx* ctx, int32_t rows, int32_t in_f, int32_t out_f, int32_t* streaming,
+                        int32_t* tile_rows, int32_t* tile_cols, int32_t* splits, int32_t* cut_cols) {
+  const ds_status st = ds_linear_plan(ctx, rows, in_f, out_f, streaming, tile_rows, tile_cols, splits, cut_cols);
+  ds::GemmPlan plan;
+  if (st != DS_OK || !layer_tiles(rows, in_f, out_f, ~(size_t)0, &plan)) return st;
+  int tr, tc;
+  ds::gemm_tile_shape(plan.tile, &tr, &tc);
+  *streaming = 0;
+  *tile_rows = tr; *tile_cols = tc; *splits = plan.splits; *cut_cols = plan.cut_cols;
   return DS_OK;
 }
 
@@ -567,7 +640,7 @@ ds_status ds_prefill(ds_ctx* ctx, const ds_layer_weights* w, const void* x, cons
   if (x == y) return fail(ctx, DS_ERR_INVALID_ARG, "ds_prefill: y must not alias x");
   if (!aligned16(x) || !aligned16(y) || !aligned16(k_out) || !aligned16(v_out) || !aligned16(workspace))
     return fail(ctx, DS_ERR_INVALID_ARG, "ds_prefill: pointers must be 16-byte aligned");
-  const size_t need = ds_prefill_workspace_bytes(ctx, t);
+  const size_t need = prefill_workspace(ctx, t).least;
   if (!workspace || workspace_bytes < need)
     return fail(ctx, DS_ERR_WORKSPACE, "ds_prefill: workspace %zu < %zu", workspace_bytes, need);
   if ((st = ensure_device(ctx)) != DS_OK) return st;
@@ -584,14 +657,9 @@ ds_status ds_prefill(ds_ctx* ctx, const ds_layer_weights* w, const void* x, cons
   void* q = ws.take((size_t)t * h * 2);
   void* o = ws.take((size_t)t * h * 2);
   void* x1 = ws.take((size_t)t * h * 2);
-  // The FFN intermediate is written by one tile GEMM and read by the next: give its rows 128 bytes of
-  // padding so that consecutive rows do not start on the same memory channels (m * 2 bytes is a multiple of
-  // 8 KB for every OPT size; at OPT-175B's 96 KB the dense stride costs the second GEMM a quarter of its rate).
-  const bool pad_u = !use_skinny(t, h) && !use_skinny(t, m) && ds::gemm_splits(t, m, h) == 1 &&
-                     ds::gemm_splits(t, h, m) == 1;
-  const int ld_u = pad_u ? m + kRowPad : m;
   void* u = ws.take((size_t)t * (m + kRowPad) * 2);
   void* sk = ws.take(0);
+  const size_t sk_bytes = workspace_bytes - ws.off;
 
   // a = LN1(x)
   DS_LAUNCH(ctx, s, DS_K_LAYERNORM, ds::launch_layernorm(x, w->ln1_g, w->ln1_b, a, t, h, c.ln_eps, s));
@@ -602,7 +670,7 @@ ds_status ds_prefill(ds_ctx* ctx, const ds_layer_weights* w, const void* x, cons
     ep.out[0] = q; ep.out[1] = k_out; ep.out[2] = v_out;
     ep.seg_cols = h;
     ep.seg_cols_kv = kv_width(c);
-    st = linear(ctx, a, w->w_qkv, t, h, qkv_width(c), ep, sk, s);
+    st = layer_linear(ctx, a, w->w_qkv, t, h, qkv_width(c), ep, sk, sk_bytes, s);
     if (st != DS_OK) return st;
   }
   // o = causal attention per request
@@ -614,18 +682,24 @@ ds_status ds_prefill(ds_ctx* ctx, const ds_layer_weights* w, const void* x, cons
     ds::Epilogue ep;
     ep.bias = w->b_o; ep.residual = x;
     ep.out[0] = x1; ep.seg_cols = h;
-    st = linear(ctx, o, w->w_o, t, h, h, ep, sk, s);
+    st = layer_linear(ctx, o, w->w_o, t, h, h, ep, sk, sk_bytes, s);
     if (st != DS_OK) return st;
   }
   // f = LN2(x1) (reuses a)
   DS_LAUNCH(ctx, s, DS_K_LAYERNORM, ds::launch_layernorm(x1, w->ln2_g, w->ln2_b, a, t, h, c.ln_eps, s));
+  // The FFN intermediate is written by one tile GEMM and read by the next: give its rows 128 bytes of
+  // padding so that consecutive rows do not start on the same memory channels (m * 2 bytes is a multiple of
+  // 8 KB for every OPT size; at OPT-175B's 96 KB the dense stride costs the second GEMM a quarter of its rate).
+  // (A reduce pass writes dense rows, the streaming kernels read them.)
+  const bool pad_u = layer_splits(t, h, m, sk_bytes) == 1 && layer_splits(t, m, h, sk_bytes) >= 1;
+  const int ld_u = pad_u ? m + kRowPad : m;
   // u = relu(f W_1^T + b_1)
   {
     ds::Epilogue ep;
     ep.bias = w->b_fc1; ep.relu = 1;
     ep.out[0] = u; ep.seg_cols = m;
     if (pad_u) ep.out_ld = ld_u;
-    st = linear(ctx, a, w->w_fc1, t, h, m, ep, sk, s);
+    st = layer_linear(ctx, a, w->w_fc1, t, h, m, ep, sk, sk_bytes, s);
     if (st != DS_OK) return st;
   }
   // y = x1 + u W_2^T + b_2
@@ -634,7 +708,7 @@ ds_status ds_prefill(ds_ctx* ctx, const ds_layer_weights* w, const void* x, cons
     ep.bias = w->b_fc2; ep.residual = x1;
     ep.out[0] = y; ep.seg_cols = h;
     if (pad_u) ep.x_ld = ld_u;
-    st = linear(ctx, u, w->w_fc2, t, m, h, ep, sk, s);
+    st = layer_linear(ctx, u, w->w_fc2, t, m, h, ep, sk, sk_bytes, s);
     if (st != DS_OK) return st;
   }
   return DS_OK;
@@ -719,7 +793,7 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
   if (x == y) return fail(ctx, DS_ERR_INVALID_ARG, "ds_decode_step: y must not alias x");
   if (!aligned16(x) || !aligned16(y) || !aligned16(k_cache) || !aligned16(v_cache) || !aligned16(workspace))
     return fail(ctx, DS_ERR_INVALID_ARG, "ds_decode_step: pointers must be 16-byte aligned");
-  const size_t need = ds_decode_workspace_bytes(ctx, B, max_ctx);
+  const size_t need = decode_workspace(ctx, B, max_ctx).least;
   const DeviceState* dev = nullptr;
   if (use_static) {
     if (need > (size_t)DS_STATIC_SCRATCH_BYTES)
@@ -754,6 +828,7 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
   void* u = ws.take((size_t)B * m * 2);
   void* att = ws.take(ds::decode_attention_workspace_bytes(B, c.n_heads, c.n_kv_heads, c.head_dim, max_ctx));
   void* sk = ws.take(0);
+  const size_t sk_bytes = workspace_bytes - ws.off;
 
   DS_LAUNCH(ctx, s, DS_K_LAYERNORM, ds::launch_layernorm(x, w->ln1_g, w->ln1_b, a, B, h, c.ln_eps, s));
   const uint16_t* qkv16 = static_cast<const uint16_t*>(qkv);
@@ -768,7 +843,7 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
     fu.k_cache = k_cache; fu.v_cache = v_cache;
     fu.n_heads = c.n_heads; fu.n_kv_heads = c.n_kv_heads; fu.head_dim = c.head_dim;
     bool appended = false;
-    st = linear(ctx, a, w->w_qkv, B, h, wqkv, ep, sk, s, &fu, &appended);
+    st = layer_linear(ctx, a, w->w_qkv, B, h, wqkv, ep, sk, sk_bytes, s, &fu, &appended);
     if (st != DS_OK) return st;
     if (!appended)
       DS_LAUNCH(ctx, s, DS_K_KV_APPEND,
@@ -787,7 +862,7 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
     fu.kind = ds::SkinnyFused::kLayerNorm;
     fu.ln_gamma = w->ln2_g; fu.ln_beta = w->ln2_b; fu.ln_eps = c.ln_eps; fu.ln_out = a;
     bool normed = false;
-    st = linear(ctx, o, w->w_o, B, h, h, ep, sk, s, &fu, &normed);
+    st = layer_linear(ctx, o, w->w_o, B, h, h, ep, sk, sk_bytes, s, &fu, &normed);
     if (st != DS_OK) return st;
     if (!normed)
       DS_LAUNCH(ctx, s, DS_K_LAYERNORM, ds::launch_layernorm(x1, w->ln2_g, w->ln2_b, a, B, h, c.ln_eps, s));
@@ -796,14 +871,14 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
     ds::Epilogue ep;
     ep.bias = w->b_fc1; ep.relu = 1;
     ep.out[0] = u; ep.seg_cols = m;
-    st = linear(ctx, a, w->w_fc1, B, h, m, ep, sk, s);
+    st = layer_linear(ctx, a, w->w_fc1, B, h, m, ep, sk, sk_bytes, s);
     if (st != DS_OK) return st;
   }
   {
     ds::Epilogue ep;
     ep.bias = w->b_fc2; ep.residual = x1;
     ep.out[0] = y; ep.seg_cols = h;
-    st = linear(ctx, u, w->w_fc2, B, m, h, ep, sk, s);
+    st = layer_linear(ctx, u, w->w_fc2, B, m, h, ep, sk, sk_bytes, s);
     if (st != DS_OK) return st;
   }
   return DS_OK;

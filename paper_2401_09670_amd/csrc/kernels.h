@@ -45,6 +45,15 @@ struct Epilogue {
 
 struct SkinnyFused;
 
+// How the MFMA tile kernel takes a product apart: number of the tile, splits of K, and, where cut_cols > 0, a cut at
+// that column: [0, cut_cols) on `tile`, the rest on `tail_tile` as a second launch.
+struct GemmPlan {
+  int tile = 0;
+  int splits = 1;
+  int cut_cols = 0;
+  int tail_tile = 0;
+};
+
 // Y[M,N] = X[M,K] W[N,K]^T (+ epilogue) on the MFMA tile kernel, any M.  Where the tiles alone
 // would not fill the chip (decode-sized M, narrow N) the K axis is split over workgroups: fp32
 // partials in `workspace` (gemm_workspace_bytes) and a second pass that also carries the epilogue.
@@ -55,6 +64,12 @@ void gemm_describe(int M, int N, int K, int* tile_rows, int* tile_cols, int* spl
 hipError_t launch_gemm(const void* X, const void* W, int M, int N, int K, const Epilogue& ep,
                        hipStream_t stream, void* workspace = nullptr, const SkinnyFused* fused = nullptr,
                        bool* fused_done = nullptr);
+// The same by a given plan.  layer_plan is the fastest the time model knows for a product of a layer whose partial sums
+// may take partial_bytes, with the time it expects.
+GemmPlan layer_plan(int M, int N, int K, size_t partial_bytes, double* us = nullptr);
+void gemm_tile_shape(int tile, int* tile_rows, int* tile_cols);
+hipError_t launch_gemm(const void* X, const void* W, int M, int N, int K, const Epilogue& ep, GemmPlan plan,
+                       hipStream_t stream, void* workspace, const SkinnyFused* fused, bool* fused_done);
 
 // Work that the decode GEMM's split-K reduction can absorb (saves a launch each):
 //  kLayerNorm: after out = act(..) + residual is written, also write ln_out = LN(out) (row-wise).
@@ -82,6 +97,7 @@ hipError_t launch_splitk_reduce(const float* partial, int splits, int M, int N, 
 // `*fused_done` tells whether the requested fused work was carried out (it needs the split-K
 // reduction pass); if not, the caller launches the separate kernel.
 size_t skinny_workspace_bytes(int M, int N, int K);
+double skinny_us(int M, int N, int K);  // time launch_skinny_gemm takes for 65 to 128 rows, to be held against layer_plan's
 void skinny_describe(int M, int N, int K, int* tile_cols, int* splits);  // the plan launch_skinny_gemm follows
 hipError_t launch_skinny_gemm(const void* X, const void* W, int M, int N, int K, const Epilogue& ep,
                               void* workspace, hipStream_t stream, const SkinnyFused* fused = nullptr,
