@@ -59,7 +59,7 @@ struct SkinnyParams {
   // accumulator of this workgroup's columns and its column go to amax_val / amax_idx [gridDim.x][M].
   float* amax_val = nullptr;
   int32_t* amax_idx = nullptr;
-  // Wave-private-ring kernel only: with kv_k_cache set (decode QKV projection, N = (n + 2 n_kv) s) the K and V
+  // Unsplit launches only: with kv_k_cache set (decode QKV projection, N = (n + 2 n_kv) s) the K and V
   // parts of row m go to slot kv_ctx_lens[m] of the paged cache [num_blocks, n_kv, 16, s] instead of `out`.
   const int32_t* kv_ctx_lens = nullptr;
   const int32_t* kv_block_tables = nullptr;
@@ -73,6 +73,27 @@ template <int VM>
 __device__ __forceinline__ void sk_wait_vmcnt() {
   // s_waitcnt with only vmcnt set: vmcnt[3:0] | expcnt=7 | lgkmcnt=15 | vmcnt[5:4] in bits 15:14
   __builtin_amdgcn_s_waitcnt((VM & 0xf) | (0x7 << 4) | (0xf << 8) | ((VM >> 4) << 14));
+}
+
+// Four finished outputs of row m, columns n .. n+3: into their output segment, or, in a decode QKV projection, this
+// step's K / V row straight into its page.
+__device__ __forceinline__ void store4(const SkinnyParams& p, int m, int n, u32x2 v) {
+  const int hq = p.kv_n_heads * p.kv_head_dim, hkv = p.kv_n_kv_heads * p.kv_head_dim;
+  if (p.kv_k_cache && n >= hq) {
+    const int which = n >= hq + hkv;
+    const int col = n - hq - which * hkv;
+    const int head = col / p.kv_head_dim, d = col - head * p.kv_head_dim;
+    const int pos = p.kv_ctx_lens[m];
+    const int blk = p.kv_block_tables[(size_t)m * p.kv_max_blocks + pos / 16];
+    uint16_t* dst = (which ? p.kv_v_cache : p.kv_k_cache) +
+                    (((size_t)blk * p.kv_n_kv_heads + head) * 16 + (pos % 16)) * p.kv_head_dim + d;
+    *reinterpret_cast<u32x2*>(dst) = v;
+    return;
+  }
+  const int seg = (n >= p.seg_cols) + (n >= p.seg_cols + p.seg_cols_kv);
+  const int ld = seg == 0 ? p.seg_cols : p.seg_cols_kv;
+  const int first = seg == 0 ? 0 : p.seg_cols + (seg - 1) * p.seg_cols_kv;
+  *reinterpret_cast<u32x2*>(p.out[seg] + (size_t)m * ld + (n - first)) = v;
 }
 
 // Waits until at most `slabs` (0 .. MOST) slabs of G loads are in flight.
@@ -334,13 +355,10 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
         v0 += bf16_lo(rr[0]); v1 += bf16_hi(rr[0]);
         v2 += bf16_lo(rr[1]); v3 += bf16_hi(rr[1]);
       }
-      const int seg = (n >= p.seg_cols) + (n >= p.seg_cols + p.seg_cols_kv);
-      const int ld = seg == 0 ? p.seg_cols : p.seg_cols_kv;
-      const int first = seg == 0 ? 0 : p.seg_cols + (seg - 1) * p.seg_cols_kv;
       u32x2 ov;
       ov[0] = pack_bf16(v0, v1);
       ov[1] = pack_bf16(v2, v3);
-      *reinterpret_cast<u32x2*>(p.out[seg] + (size_t)m * ld + (n - first)) = ov;
+      store4(p, m, n, ov);
     }
   }
 }
@@ -485,22 +503,7 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
       u32x2 ov;
       ov[0] = pack_bf16(v0, v1);
       ov[1] = pack_bf16(v2, v3);
-      const int hq = p.kv_n_heads * p.kv_head_dim, hkv = p.kv_n_kv_heads * p.kv_head_dim;
-      if (p.kv_k_cache && n >= hq) {  // decode QKV projection: this step's K / V row goes straight into its page
-        const int which = n >= hq + hkv;
-        const int col = n - hq - which * hkv;
-        const int head = col / p.kv_head_dim, d = col - head * p.kv_head_dim;
-        const int pos = p.kv_ctx_lens[m];
-        const int blk = p.kv_block_tables[(size_t)m * p.kv_max_blocks + pos / 16];
-        uint16_t* dst = (which ? p.kv_v_cache : p.kv_k_cache) +
-                        (((size_t)blk * p.kv_n_kv_heads + head) * 16 + (pos % 16)) * p.kv_head_dim + d;
-        *reinterpret_cast<u32x2*>(dst) = ov;
-        continue;
-      }
-      const int seg = (n >= p.seg_cols) + (n >= p.seg_cols + p.seg_cols_kv);
-      const int ld = seg == 0 ? p.seg_cols : p.seg_cols_kv;
-      const int first = seg == 0 ? 0 : p.seg_cols + (seg - 1) * p.seg_cols_kv;
-      *reinterpret_cast<u32x2*>(p.out[seg] + (size_t)m * ld + (n - first)) = ov;
+      store4(p, m, n, ov);
     }
   }
 }
@@ -720,6 +723,8 @@ struct SkinnyPlan {
   int splits;  // K splits over workgroups
 };
 
+constexpr double kReduceBytes = 57e6;  // what a reduce launch costs, in bytes of the chip's stream (4 us)
+
 // Measured on MI355X: a CU sustains about one workgroup's worth of streaming whatever the LDS would
 // allow, and a second round of workgroups costs a full round.  So a plan must fit one round
 // (<= 256 workgroups) and should fill it; among such plans take the fewest bytes through the CUs' L1:
@@ -759,8 +764,15 @@ static SkinnyPlan skinny_plan(int M, int N, int K, bool allow_split = true, doub
       }
     }
   }
-  if (cost_out) *cost_out = best_cost + (best.splits > 1 ? 57e6 : 0.0);  // + the reduce launch (6 us of the chip)
+  if (cost_out) *cost_out = best_cost + (best.splits > 1 ? kReduceBytes : 0.0);
   return best;
+}
+
+// What the unsplit ring kernel with 64 columns a workgroup costs, in the same bytes; rows that only repeat the last one
+// are left out (they come from one line).
+static double unsplit_bytes(int M, int N, int K) {
+  const int wgs = (N + 63) / 64, rows = (M + 15) / 16 * 16;
+  return (2.0 * N * K + 2.0 * wgs * rows * (double)K) * (wgs >= 256 ? (wgs + 255) / 256 : 256.0 / wgs);
 }
 
 size_t skinny_workspace_bytes(int M, int N, int K) {
@@ -945,8 +957,8 @@ void skinny_describe(int M, int N, int K, int* tile_cols, int* splits) {
   *splits = pl.splits;
 }
 
-// By the bytes the plans go by, fitted to 16 products at 65, 96 and 128 rows (within 8 % but for 12288 x 49152, where it
-// is a third too long).
+// By the bytes the plans go by, fitted to 16 products at 65, 96 and 128 rows (within 10 %; 12288 x 49152 left out: two
+// rounds of 128 columns, where it is a third too long).
 double skinny_us(int M, int N, int K) {
   const int nt = wring_tiles(M, N, K);
   double bytes;
@@ -956,11 +968,12 @@ double skinny_us(int M, int N, int K) {
   } else {
     skinny_plan(M, N, K, true, &bytes);
   }
-  return 7.6 + (M - 96) * 0.11 + (nt > 0 ? 0.0757e-6 : 0.0709e-6) * bytes;
+  return 7.5 + (nt > 0 ? 0.0760e-6 : 0.0734e-6) * bytes * (1.0 + 0.088 * (M - 96) / 32.0);
 }
 
 hipError_t launch_skinny_gemm(const void* X, const void* W, int M, int N, int K, const Epilogue& ep,
-                              void* workspace, hipStream_t stream, const SkinnyFused* fused, bool* fused_done) {
+                              void* workspace, hipStream_t stream, const SkinnyFused* fused, bool* fused_done,
+                              bool weigh_reduce) {
   if (fused_done) *fused_done = false;
   if (M <= 0 || N <= 0) return hipSuccess;
   if (M > 256 || K % kSkPlanK != 0 || N % 8 != 0 || ep.seg_cols <= 0 || ep.seg_cols % 8 != 0 || ep.seg_cols_kv < 0 ||
@@ -984,17 +997,23 @@ hipError_t launch_skinny_gemm(const void* X, const void* W, int M, int N, int K,
                        !ep.residual && N == (fused->n_heads + 2 * fused->n_kv_heads) * fused->head_dim &&
                        fused->head_dim % 4 == 0;
   const int nt = (plain || want_kv) ? wring_tiles(M, N, K) : 0;
+  SkinnyPlan pl{1, 1};
+  if (nt == 0) {
+    double split;
+    pl = skinny_plan(M, N, K, true, &split);
+    if (weigh_reduce && (plain || want_kv) && pl.splits > 1 && unsplit_bytes(M, N, K) < split - kReduceBytes + 24e6)
+      pl = SkinnyPlan{1, 1};
+  }
+  if (want_kv && pl.splits == 1) {
+    p.kv_ctx_lens = fused->ctx_lens; p.kv_block_tables = fused->block_tables; p.kv_max_blocks = fused->max_blocks;
+    p.kv_k_cache = (uint16_t*)fused->k_cache; p.kv_v_cache = (uint16_t*)fused->v_cache;
+    p.kv_n_heads = fused->n_heads; p.kv_n_kv_heads = fused->n_kv_heads; p.kv_head_dim = fused->head_dim;
+    if (fused_done) *fused_done = true;
+  }
   if (nt > 0) {
-    if (want_kv) {
-      p.kv_ctx_lens = fused->ctx_lens; p.kv_block_tables = fused->block_tables; p.kv_max_blocks = fused->max_blocks;
-      p.kv_k_cache = (uint16_t*)fused->k_cache; p.kv_v_cache = (uint16_t*)fused->v_cache;
-      p.kv_n_heads = fused->n_heads; p.kv_n_kv_heads = fused->n_kv_heads; p.kv_head_dim = fused->head_dim;
-      if (fused_done) *fused_done = true;
-    }
     p.partial = nullptr;
     return launch_wring(nt, p, stream);
   }
-  const SkinnyPlan pl = skinny_plan(M, N, K);
   p.partial = (float*)workspace;
   if (pl.splits > 1 && workspace == nullptr) return hipErrorInvalidValue;
   hipError_t e = dispatch_skinny(p, pl, stream);

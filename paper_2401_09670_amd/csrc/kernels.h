@@ -94,14 +94,16 @@ hipError_t launch_splitk_reduce(const float* partial, int splits, int M, int N, 
                                 const SkinnyFused* fused, bool* fused_done, hipStream_t stream);
 
 // Same contraction for M <= 256 (decode): weights are streamed once from HBM.
-// `*fused_done` tells whether the requested fused work was carried out (it needs the split-K
-// reduction pass); if not, the caller launches the separate kernel.
+// `*fused_done` tells whether the requested fused work was carried out (LayerNorm needs the split-K
+// reduction pass); if not, the caller launches the separate kernel.  With `weigh_reduce` a product stays unsplit where
+// that takes no longer than splitting and the reduce pass together (24e6 of the plans' bytes, 2 us, for a small one): one
+// launch less for the host (2 rows of 1024 -> 256), 3072 x 1024 at 64 rows 3 us.
 size_t skinny_workspace_bytes(int M, int N, int K);
 double skinny_us(int M, int N, int K);  // time launch_skinny_gemm takes for 65 to 128 rows, to be held against layer_plan's
 void skinny_describe(int M, int N, int K, int* tile_cols, int* splits);  // the plan launch_skinny_gemm follows
 hipError_t launch_skinny_gemm(const void* X, const void* W, int M, int N, int K, const Epilogue& ep,
                               void* workspace, hipStream_t stream, const SkinnyFused* fused = nullptr,
-                              bool* fused_done = nullptr);
+                              bool* fused_done = nullptr, bool weigh_reduce = false);
 
 // Greedy token choice over logits = X[M,K] W[N,K]^T (M <= 256, fp32 accumulation, never written out):
 // the weight-streaming kernel keeps, per row and column block, the largest logit and its column; a

@@ -93,28 +93,23 @@ def test_smallest_workspace_runs_on_plans_that_fit_it(gpu):
         _prefill(layer, t, ws[:least - 1])
 
 
-@pytest.mark.parametrize("batch,tile", [(100, (128, 192)), (150, (160, 192)), (180, (192, 192)), (200, (224, 192)),
-                                        (250, (256, 160))])
-def test_decode_step_scatters_k_and_v_from_unsplit_tiles(gpu, batch, tile):
-    """OPT-175B's QKV projection is wide enough to stay unsplit: the tile's own epilogue writes the step's K and V into
-    the pages (each sequence's next slot, and nothing else)."""
-    h, n, s = 12288, 96, 128
-    shape = synth.ModelShape(hidden=h, n_heads=n, head_dim=s, ffn=512)
+def _kv_scatter_case(shape, batch):
+    """One decoding step; its K and V rows against the product in float64, every other slot of the pool untouched."""
+    h, s, n_kv = shape.hidden, shape.head_dim, shape.kv_heads
+    kvw, m = n_kv * s, shape.ffn
     ctx = gu.make_ctx(shape)
-    plan = ctx.ds_layer_plan(batch, h, 3 * h)
-    assert (plan["tile_rows"], plan["tile_cols"], plan["splits"]) == (*tile, 1)
     g = torch.Generator(device="cuda")
     g.manual_seed(batch)
     draw = lambda *size, std=1.0, mean=0.0: torch.empty(size, dtype=torch.bfloat16, device="cuda").normal_(
         mean, std, generator=g)
-    w = {"ln1_g": draw(h, std=0.02, mean=1.0), "ln1_b": draw(h, std=0.02), "w_qkv": draw(3 * h, h, std=0.02),
-         "b_qkv": draw(3 * h, std=0.02), "w_o": draw(h, h, std=0.02), "b_o": draw(h, std=0.02),
-         "ln2_g": draw(h, std=0.02, mean=1.0), "ln2_b": draw(h, std=0.02), "w_fc1": draw(512, h, std=0.02),
-         "b_fc1": draw(512, std=0.02), "w_fc2": draw(h, 512, std=0.02), "b_fc2": draw(h, std=0.02)}
+    w = {"ln1_g": draw(h, std=0.02, mean=1.0), "ln1_b": draw(h, std=0.02), "w_qkv": draw(h + 2 * kvw, h, std=0.02),
+         "b_qkv": draw(h + 2 * kvw, std=0.02), "w_o": draw(h, h, std=0.02), "b_o": draw(h, std=0.02),
+         "ln2_g": draw(h, std=0.02, mean=1.0), "ln2_b": draw(h, std=0.02), "w_fc1": draw(m, h, std=0.02),
+         "b_fc1": draw(m, std=0.02), "w_fc2": draw(h, m, std=0.02), "b_fc2": draw(h, std=0.02)}
     lw, keep = ctx.pack_weights(w)
     lens = [1 + (7 * i) % 40 for i in range(batch)]
     tables, nblk = synth.make_block_tables([l + 1 for l in lens], 16, 5)
-    kc, vc = draw(nblk, n, 16, s), draw(nblk, n, 16, s)
+    kc, vc = draw(nblk, n_kv, 16, s), draw(nblk, n_kv, 16, s)
     want_k, want_v = kc.double(), vc.double()
     x, y = draw(batch, h), torch.empty(batch, h, dtype=torch.bfloat16, device="cuda")
     xd = x.double()
@@ -123,8 +118,8 @@ def test_decode_step_scatters_k_and_v_from_unsplit_tiles(gpu, batch, tile):
     kv = a @ w["w_qkv"][h:].double().T + w["b_qkv"][h:].double()
     for i, l in enumerate(lens):
         blk = int(tables[i][l // 16])
-        want_k[blk, :, l % 16] = kv[i, :h].view(n, s)
-        want_v[blk, :, l % 16] = kv[i, h:].view(n, s)
+        want_k[blk, :, l % 16] = kv[i, :kvw].view(n_kv, s)
+        want_v[blk, :, l % 16] = kv[i, kvw:].view(n_kv, s)
     ws = gu.workspace(ctx.ds_decode_workspace_bytes(batch, max(lens) + 1))
     ctx.ds_decode_step(lw, x, gu.i32_dev(lens), gu.i32_dev(tables), batch, tables.shape[1], max(lens) + 1, kc, vc, nblk,
                        y, ws)
@@ -132,3 +127,22 @@ def test_decode_step_scatters_k_and_v_from_unsplit_tiles(gpu, batch, tile):
     for got, want in ((kc, want_k), (vc, want_v)):
         # one bf16 rounding of the result (2^-9) and of a on the way to it (another LayerNorm order may flip one)
         assert float((got.double() - want).abs().max()) <= 2.0 ** -7 * float(want.abs().max())
+
+
+@pytest.mark.parametrize("batch,tile", [(100, (128, 192)), (150, (160, 192)), (180, (192, 192)), (200, (224, 192)),
+                                        (250, (256, 160))])
+def test_decode_step_scatters_k_and_v_from_unsplit_tiles(gpu, batch, tile):
+    """OPT-175B's QKV projection is wide enough to stay unsplit: the tile's own epilogue writes the step's K and V into
+    the pages (each sequence's next slot, and nothing else)."""
+    shape = synth.ModelShape(hidden=12288, n_heads=96, head_dim=128, ffn=512)
+    plan = gu.make_ctx(shape).ds_layer_plan(batch, 12288, 36864)
+    assert (plan["tile_rows"], plan["tile_cols"], plan["splits"]) == (*tile, 1)
+    _kv_scatter_case(shape, batch)
+
+
+@pytest.mark.parametrize("batch", [1, 15, 16, 33, 64, 67, 129])
+@pytest.mark.parametrize("heads,head_dim,n_kv", [(4, 64, 0), (6, 128, 2), (8, 128, 0)])
+def test_decode_step_scatters_k_and_v_of_small_layers(gpu, heads, head_dim, n_kv, batch):
+    """Projections of a few workgroups: unsplit on the ring kernel, with and without a reduce pass, and on tiles."""
+    _kv_scatter_case(synth.ModelShape(hidden=heads * head_dim, n_heads=heads, head_dim=head_dim, ffn=256,
+                                      n_kv_heads=n_kv), batch)
