@@ -844,7 +844,12 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
   void* sk = ws.take(0);
   const size_t sk_bytes = workspace_bytes - ws.off;
 
-  DS_LAUNCH(ctx, s, DS_K_LAYERNORM, ds::launch_layernorm(x, w->ln1_g, w->ln1_b, a, B, h, c.ln_eps, s));
+  // The attention starts its longest sequences first; their order lies in x1 until the out-projection writes there.
+  ds::LengthOrder by_length;
+  if (ds::decode_attention_wants_order(B, c.n_heads, c.n_kv_heads, c.head_dim, max_ctx))
+    by_length = ds::LengthOrder{ctx_lens, static_cast<int32_t*>(x1), B};
+  DS_LAUNCH(ctx, s, DS_K_LAYERNORM,
+            ds::launch_layernorm(x, w->ln1_g, w->ln1_b, a, B, h, c.ln_eps, s, nullptr, by_length));
   const uint16_t* qkv16 = static_cast<const uint16_t*>(qkv);
   {
     // [q | k | v] = a W_qkv^T + b_qkv; the split-K reduction writes k, v straight into the cache
@@ -866,7 +871,8 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
   }
   DS_LAUNCH(ctx, s, DS_K_DECODE_ATTN,
             ds::launch_decode_attention(qkv, wqkv, ctx_lens, 1, block_tables, B, max_blocks_per_seq, max_ctx,
-                                        k_cache, v_cache, c.n_heads, c.n_kv_heads, c.head_dim, o, att, s));
+                                        k_cache, v_cache, c.n_heads, c.n_kv_heads, c.head_dim, o, att, s,
+                                        by_length.order));
   {
     // x1 = x + o W_o^T + b_o, f = LN2(x1)
     ds::Epilogue ep;

@@ -18,11 +18,20 @@ struct KernelAttrReg {
   static inline const bool done = (register_kernel_attr(reinterpret_cast<const void*>(Kern), LdsBytes), true);
 };
 
+// Sequences by length, longest first (equal ones in their order): order[0 .. count) from lens[0 .. count).
+constexpr int kMaxSorted = 512;
+struct LengthOrder {
+  const int32_t* lens = nullptr;
+  int32_t* order = nullptr;
+  int count = 0;  // <= kMaxSorted; 0 = none wanted
+};
+
 // y = LN(x) * gamma + beta, one workgroup per row.  h % 8 == 0, h <= 16384.
 // With `row_index` (device, `rows` entries) output row r normalises input row row_index[r].
+// With `sort`, a workgroup beside the rows' writes that order.
 hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, void* out,
                             int rows, int h, float eps, hipStream_t stream,
-                            const int32_t* row_index = nullptr);
+                            const int32_t* row_index = nullptr, const LengthOrder& sort = {});
 
 // Epilogue of both GEMM paths: out = act(acc + bias) + residual, written as bf16.
 // The N output columns may be cut into up to three segments that go to
@@ -136,12 +145,15 @@ hipError_t launch_kv_append(const void* k_new, const void* v_new, int src_stride
                             int n_heads, int head_dim, hipStream_t stream);
 
 // One query per (sequence, head) over the paged cache.  kv_len_add is added to
-// kv_lens[i] (1 when kv_lens holds the lengths before this step's append).
+// kv_lens[i] (1 when kv_lens holds the lengths before this step's append).  `order` (device, B entries, or null): which
+// sequence to start first, second, ...; decode_attention_wants_order tells whether one is worth having.
 size_t decode_attention_workspace_bytes(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len);
 int decode_attention_splits(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len);
+bool decode_attention_wants_order(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len);
 hipError_t launch_decode_attention(const void* q, int q_stride, const int32_t* kv_lens, int kv_len_add,
                                    const int32_t* block_tables, int B, int max_blocks, int max_kv_len,
                                    const void* k_cache, const void* v_cache, int n_heads, int n_kv_heads,
-                                   int head_dim, void* o, void* workspace, hipStream_t stream);
+                                   int head_dim, void* o, void* workspace, hipStream_t stream,
+                                   const int32_t* order = nullptr);
 
 }  // namespace ds

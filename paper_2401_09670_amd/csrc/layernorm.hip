@@ -18,6 +18,19 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return red[0] + red[1] + red[2] + red[3];
 }
 
+// Rank of every length by counting: a workgroup of its own in the launch before the one that uses the order.
+__device__ void sort_lengths(const LengthOrder& s) {
+  __shared__ int32_t len[kMaxSorted];
+  for (int i = threadIdx.x; i < s.count; i += kLnThreads) len[i] = s.lens[i];
+  __syncthreads();
+  for (int i = threadIdx.x; i < s.count; i += kLnThreads) {
+    const int32_t mine = len[i];
+    int rank = 0;
+    for (int j = 0; j < s.count; ++j) rank += len[j] > mine || (len[j] == mine && j < i) ? 1 : 0;
+    s.order[rank] = i;
+  }
+}
+
 // NCH = 16-byte pieces per thread (row length <= NCH * 2048 elements): the row buffer is sized to the
 // row, so that short rows leave enough registers for every row of a 2048-row launch to be resident.
 template <int NCH>
@@ -25,8 +38,13 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_kernel(const uint16_t* _
                                                                const uint16_t* __restrict__ gamma,
                                                                const uint16_t* __restrict__ beta,
                                                                uint16_t* __restrict__ out, int h, float eps,
-                                                               const int32_t* __restrict__ row_index) {
+                                                               const int32_t* __restrict__ row_index,
+                                                               const LengthOrder sort) {
   __shared__ float red[4];
+  if (sort.count > 0 && blockIdx.x == gridDim.x - 1) {
+    sort_lengths(sort);
+    return;
+  }
   const int nchunk = h >> 3;
   const size_t row = blockIdx.x;
   // output row `row` normalises input row row_index[row] (all rows in order when there is no index)
@@ -86,13 +104,13 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_kernel(const uint16_t* _
 }
 
 hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, void* out, int rows, int h,
-                            float eps, hipStream_t stream, const int32_t* row_index) {
+                            float eps, hipStream_t stream, const int32_t* row_index, const LengthOrder& sort) {
   if (rows <= 0) return hipSuccess;
-  if (h % 8 != 0 || h > kLnThreads * 8 * kLnMaxChunks) return hipErrorInvalidValue;
+  if (h % 8 != 0 || h > kLnThreads * 8 * kLnMaxChunks || sort.count > kMaxSorted) return hipErrorInvalidValue;
   const int nch = ((h >> 3) + kLnThreads - 1) / kLnThreads;
 #define DS_LN_LAUNCH(N)                                                                                   \
-  hipLaunchKernelGGL(layernorm_kernel<N>, dim3(rows), dim3(kLnThreads), 0, stream, (const uint16_t*)x,   \
-                     (const uint16_t*)gamma, (const uint16_t*)beta, (uint16_t*)out, h, eps, row_index)
+  hipLaunchKernelGGL(layernorm_kernel<N>, dim3(rows + (sort.count > 0 ? 1 : 0)), dim3(kLnThreads), 0, stream, (const uint16_t*)x, \
+                     (const uint16_t*)gamma, (const uint16_t*)beta, (uint16_t*)out, h, eps, row_index, sort)
   if (nch <= 1) DS_LN_LAUNCH(1);
   else if (nch == 2) DS_LN_LAUNCH(2);
   else if (nch == 3) DS_LN_LAUNCH(3);
