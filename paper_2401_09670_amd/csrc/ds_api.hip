@@ -207,7 +207,8 @@ struct Carver {
 // Y = act(X W^T + b) + residual for any row count.  Up to 128 rows the weight-streaming kernel is the
 // faster one (measured with weights that do not sit in the last-level cache: 156 / 204 us against
 // 163 / 212 us for the four OPT-13B GEMMs at 32 / 128 rows); from there on the MFMA tile kernel,
-// split over K where its tiles alone would not fill the chip (287 against 364 us at 256 rows).
+// split over K where its tiles alone would not fill the chip (287 against 364 us at 256 rows).  (The products of a
+// layer have plans of their own from 65 rows on: layer_linear.)
 // Decode-sized calls (<= 256 rows) are timed as their own class whichever kernel runs.
 constexpr int kStreamMaxRows = 128;
 constexpr int kRowPad = 64;  // elements of padding per row of a padded internal buffer (128 bytes)

@@ -8,9 +8,14 @@
 // What bounds the large tiles: power (with N(0,1)-like operands the clock settles at 1.7-1.9 GHz) and, beside it, the
 // loads of operand tiles through a compute unit's load path - a 256x256 k-tile of 16384 x 36864 x 12288 takes 1.42 us
 // (1.53 with the loop before this one), 1.19 without its 64 KB of loads and 1.30 without its matrix instructions; in a
-// launch of one round (4096 x 4096) the loads alone take all of its 1.55 us.  16384 x 36864 x 12288: 10.85 -> 10.18 ms
-// (32x32x16 instructions, loads and fragment reads in clumps -> 16x16x32, dealt out one by one, 8 x 4 tiles per XCD);
-// 2048 x 15360 x 5120: 258 -> 250 us; 2048 x 5120 x 20480 (256x160 tiles): 329 -> 311 us.
+// launch of one round (4096 x 4096) the loads alone took all of its 1.55 us (these with two stages of weights, not three).
+// 32x32x16 instructions, loads and fragment reads in clumps -> 16x16x32, dealt out one by one, 8 x 4 tiles per XCD:
+// 16384 x 36864 x 12288 10.85 -> 10.18 ms, 2048 x 15360 x 5120 258 -> 250 us.
+// The third stage of weights, two against three in turn: K = 5120: 4096 x 15360 502 -> 482 us, 16384 x 20480 2583 -> 2477
+// (3-4 %); K = 9216: 0-1 %; K = 12288: 2048 x 49152 1.3 %, 4096 x 36864 none, and from 8192 rows on, where power bounds the
+// loop, between 0.3 % faster and 1.1 % slower (16384 x 36864 10.15 -> 10.20 ms, x 49152 13.51 -> 13.63; another time
+// 10.04 -> 10.15).  A ring with two stages only for those would be a kernel more for that 1 %.
+// What bounds the others: see layer_plan.
 //
 // Tile BM x BN (activation rows x weight rows, kTiles), BK = 64,
 // 256 threads = 4 waves (one per SIMD).  Operands go global -> LDS directly (no register
@@ -63,7 +68,7 @@ static double tile_cost(int M, int N, int BM, int BN, double factor) {
   return rounds * BM * BN * factor;
 }
 
-DS_SWITCH(g_gemm_variant, 0);     // 0 = cost model, 1..5 force a tile
+DS_SWITCH(g_gemm_variant, 0);     // 0 = plan, > 0: force this tile (kTiles)
 DS_SWITCH(g_gemm_splits, 0);      // 0 = plan, > 0 force the split count
 DS_SWITCH(g_gemm_tail_split, 1);  // 0 = never cut a product at a column
 DS_SWITCH(g_gemm_cut_cols, 0);    // > 0: cut at this column ...
@@ -102,8 +107,8 @@ static GemmPlan decode_plan(int M, int N, int K) {
   return best;
 }
 
-// Prefill-sized products (more than 256 rows): tile shape, split count and column cut together, by a time
-// model fitted to this chip (OPT-13B shapes, 512-2048 rows, weights not resident in any cache).
+// Prefill-sized products (more than 256 rows) of ds_linear, and of a layer from 4097 on: tile shape, split count and
+// column cut together, by a time model fitted to this chip (OPT-13B shapes, 512-2048 rows, weights not resident in any cache).
 //  * A workgroup's k-loop costs us_per_kk microseconds per 1000 elements of K when all 256 compute units are
 //    busy, plus t0 for its prologue and epilogue (the output burst of a whole round of tiles is bound by write
 //    bandwidth: 9 us for 256x256 tiles, 5 us for 256x160).

@@ -1,5 +1,5 @@
 // Decode-phase GEMM: Y[M,N] = act(X[M,K] W[N,K]^T + bias) + residual for a handful of rows
-// (the library routes M <= 128 here; the kernels accept up to 256).
+// (ds_linear routes M <= 128 here, a layer M <= 64 and what is faster here up to 128; the kernels accept up to 256).
 // The weights (N*K*2 bytes) are read once from HBM and dominate the traffic
 // (App. A.3: 4h^2 + 2hm elements per layer), so the kernels are organised
 // around streaming W at HBM rate while the matrix cores do the M x ... work.
