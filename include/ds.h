@@ -158,15 +158,16 @@ ds_status ds_decode_step(ds_ctx *ctx, const ds_layer_weights *w, const void *x,
 
 /*
  * ds_decode_step for callers that cannot allocate device memory or carry a workspace: code under HIP
- * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and
- * same results as ds_decode_step, minus the workspace: the step's scratch (activations between its
+ * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and
+ * kernels as ds_decode_step, minus the workspace: the step's scratch (activations between its
  * kernels, split-K and attention partial sums) lives in a static device array of DS_STATIC_SCRATCH_BYTES
  * that every GPU the library runs on holds until the process ends.  The call allocates and frees nothing.
  * A step that cannot run in it (e.g. batches beyond ~128 sequences of an OPT-13B layer) is rejected with
  * DS_ERR_WORKSPACE before anything is launched.  ds_decode_workspace_bytes may report more than the array holds for a
  * step that is accepted: the reported size lets the products have their fastest plans, and a step with less
  * takes plans that fit.  Such a step adds its partial sums in other groups than ds_decode_step with all of that
- * workspace: equal up to the rounding of the sums, not bit by bit.  All calls on one GPU share that GPU's array: calls that may overlap on one GPU (different
+ * workspace: equal up to the rounding of the sums, not bit by bit.
+ * All calls on one GPU share that GPU's array: calls that may overlap on one GPU (different
  * streams, different threads or contexts) race on it and must be serialised by the caller; nothing in the
  * array has to survive from one call to the next, and nothing in it has to start out as zero.
  */

@@ -38,17 +38,20 @@ DS_SWITCH(g_gemm_spread, -1);  // 0, 1: never, always
 // from further away (8192 x 12288 x 49152 6.98 and 7.79 ms).  Small ones are better kept (52 MB, 96 to 192 rows: 3 to 14 %
 // slower with the hint; 134 to 170 MB: between 7 % faster and 4 % slower).
 constexpr int kFewRowTiles = 8;
-constexpr double kStreamedBytes = 96e6;
+//   That is for the products of a layer, whose other weights come between two uses of these.  ds_linear may be called with
+// the same weights again, and the last-level cache holds 256 MB, out of which the hint would keep them: 15360 x 5120 (157
+// MB) again and again at 256 / 512 / 1024 / 2048 rows 62 / 86 / 126 / 245 us with the hint, 50 / 73 / 120 / 235 without.
+constexpr double kStreamedBytes = 96e6, kCachedBytes = 256e6;
 
 // Workgroups of such launches start at different places of K where the row stride is a multiple of 4 KB (256 x 36864 x
 // 12288 215 -> 197 us, 256 x 32768 x 8192 128 -> 112, K of 20480 and 49152: no difference).
-static hipError_t launch_tile(int tile, GemmParams p, int splits, hipStream_t stream) {
+static hipError_t launch_tile(int tile, GemmParams p, int splits, bool in_layer, hipStream_t stream) {
   const Tile& t = kTiles[tile];
   p.tiles_m = (p.M + t.bm - 1) / t.bm;
   p.tiles_n = (p.N - p.n_base + t.bn - 1) / t.bn;
   p.spread = p.K % 2048 == 0;
   if (g_gemm_spread >= 0) p.spread = g_gemm_spread;
-  bool nt = p.tiles_m <= kFewRowTiles && 2.0 * p.N * p.K >= kStreamedBytes;
+  bool nt = p.tiles_m <= kFewRowTiles && 2.0 * p.N * p.K >= (in_layer ? kStreamedBytes : kCachedBytes);
   if (g_gemm_nt >= 0) nt = g_gemm_nt;
   return tile < kFirstFewRows
              ? launch_any<1>(tile, p, nt, splits, stream, std::make_integer_sequence<int, kFirstFewRows - 1>())
@@ -256,6 +259,7 @@ GemmPlan layer_plan(int M, int N, int K, size_t partial_bytes, double* us_out) {
     }
   }
   if (us_out) *us_out = best_us;
+  best.in_layer = true;
   return best;
 }
 
@@ -376,11 +380,11 @@ hipError_t launch_gemm(const void* X, const void* W, int M, int N, int K, const 
     GemmParams a = p, b = p;
     a.N = pl.cut_cols;
     b.n_base = pl.cut_cols;
-    e = launch_tile(pl.tile, a, 1, stream);
+    e = launch_tile(pl.tile, a, 1, pl.in_layer, stream);
     if (e != hipSuccess) return e;
-    return launch_tile(pl.tail_tile, b, 1, stream);
+    return launch_tile(pl.tail_tile, b, 1, pl.in_layer, stream);
   }
-  e = launch_tile(pl.tile, p, pl.splits, stream);
+  e = launch_tile(pl.tile, p, pl.splits, pl.in_layer, stream);
   if (e != hipSuccess) return e;
   if (pl.splits > 1) e = launch_splitk_reduce(p.partial, pl.splits, M, N, ep, fused, fused_done, stream);
   return e;

@@ -61,6 +61,7 @@ struct GemmPlan {
   int splits = 1;
   int cut_cols = 0;
   int tail_tile = 0;
+  bool in_layer = false;  // other weights are read between two uses of these
 };
 
 // Y[M,N] = X[M,K] W[N,K]^T (+ epilogue) on the MFMA tile kernel, any M.  Where the tiles alone
