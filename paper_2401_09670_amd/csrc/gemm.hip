@@ -12,9 +12,9 @@
 // 32x32x16 instructions, loads and fragment reads in clumps -> 16x16x32, dealt out one by one, 8 x 4 tiles per XCD:
 // 16384 x 36864 x 12288 10.85 -> 10.18 ms, 2048 x 15360 x 5120 258 -> 250 us.
 // The third stage of weights, two against three in turn: K = 5120: 4096 x 15360 502 -> 482 us, 16384 x 20480 2583 -> 2477
-// (3-4 %); K = 9216: 0-1 %; K = 12288: 2048 x 49152 1.3 %, 4096 x 36864 none, and from 8192 rows on, where power bounds the
-// loop, between 0.3 % faster and 1.1 % slower (16384 x 36864 10.15 -> 10.20 ms, x 49152 13.51 -> 13.63; another time
-// 10.04 -> 10.15).  A ring with two stages only for those would be a kernel more for that 1 %.
+// (3-4 %); K = 9216: 0-1.5 %; K = 12288: none at 4096 rows (x 36864, x 49152), and from 8192 rows on, where power bounds
+// the loop, between 0.6 % faster and 1.1 % slower (16384 x 36864 10.15 -> 10.20 ms, x 49152 13.51 -> 13.63; another time
+// x 36864 10.04 -> 10.15).  A ring with two stages only for those would be a kernel more for that 1 %.
 // What bounds the others: see layer_plan.
 //
 // Tile BM x BN (activation rows x weight rows, kTiles), BK = 64,
