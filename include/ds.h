@@ -105,8 +105,9 @@ ds_status ds_set_validate(ds_ctx *ctx, int32_t on);
 /* Workspace (device bytes) for ds_prefill with up to max_tokens packed tokens.
  * Both sizes are upper bounds over all smaller calls: a workspace sized for the
  * largest batch serves every call with fewer tokens / sequences / cached tokens.
- * A call with less still runs, on plans that split less, as long as the activations and the partial
- * sums of ds_linear's plans for its four products (ds_linear_workspace_bytes) fit. */
+ * A call with less still runs, on plans that split less (equal up to the rounding of the sums, not bit by
+ * bit), as long as the activations and the partial sums of ds_linear's plans for its four products
+ * (ds_linear_workspace_bytes) fit. */
 size_t ds_prefill_workspace_bytes(const ds_ctx *ctx, int32_t max_tokens);
 /* The same for ds_decode_step with up to max_batch sequences of up to max_ctx cached tokens. */
 size_t ds_decode_workspace_bytes(const ds_ctx *ctx, int32_t max_batch, int32_t max_ctx);
@@ -158,15 +159,14 @@ ds_status ds_decode_step(ds_ctx *ctx, const ds_layer_weights *w, const void *x,
 
 /*
  * ds_decode_step for callers that cannot allocate device memory or carry a workspace: code under HIP
- * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and
- * kernels as ds_decode_step, minus the workspace: the step's scratch (activations between its
+ * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and
+ * same results as ds_decode_step, minus the workspace: the step's scratch (activations between its
  * kernels, split-K and attention partial sums) lives in a static device array of DS_STATIC_SCRATCH_BYTES
  * that every GPU the library runs on holds until the process ends.  The call allocates and frees nothing.
- * A step that cannot run in it (e.g. batches beyond ~128 sequences of an OPT-13B layer) is rejected with
- * DS_ERR_WORKSPACE before anything is launched.  ds_decode_workspace_bytes may report more than the array holds for a
- * step that is accepted: the reported size lets the products have their fastest plans, and a step with less
- * takes plans that fit.  Such a step adds its partial sums in other groups than ds_decode_step with all of that
- * workspace: equal up to the rounding of the sums, not bit by bit.
+ * A step that needs more (ds_decode_workspace_bytes(ctx, B, max_ctx) > DS_STATIC_SCRATCH_BYTES, e.g.
+ * batches beyond ~128 sequences of an OPT-13B layer) is rejected with DS_ERR_WORKSPACE before anything is
+ * launched.  (A step that the array can run is planned against its size whichever of the two calls runs it, and
+ * however large the workspace: bit by bit the same, as long as that is not smaller than reported.)
  * All calls on one GPU share that GPU's array: calls that may overlap on one GPU (different
  * streams, different threads or contexts) race on it and must be serialised by the caller; nothing in the
  * array has to survive from one call to the next, and nothing in it has to start out as zero.

@@ -440,6 +440,8 @@ ds_ctx::Workspace decode_workspace(const ds_ctx* ctx, int max_batch, int max_ctx
   ds_ctx::Workspace need = max_gemm_ws(c, max_batch);
   need.least += rest;
   need.full += rest;
+  // A step that the static array can run has the plans that fit there (decode_step), and asks for no more.
+  if (need.least <= DS_STATIC_SCRATCH_BYTES && need.full > DS_STATIC_SCRATCH_BYTES) need.full = DS_STATIC_SCRATCH_BYTES;
   if (ctx->decode_ws.size() < 4096) ctx->decode_ws[key] = need;
   return need;
 }
@@ -822,6 +824,9 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
     if (!workspace || workspace_bytes < need)
       return fail(ctx, DS_ERR_WORKSPACE, "ds_decode_step: workspace %zu < %zu", workspace_bytes, need);
     if ((st = ensure_device(ctx)) != DS_OK) return st;
+    // Both entry points plan a step that either can run against the same size, and so give the same bits.
+    if (need <= (size_t)DS_STATIC_SCRATCH_BYTES && workspace_bytes > (size_t)DS_STATIC_SCRATCH_BYTES)
+      workspace_bytes = (size_t)DS_STATIC_SCRATCH_BYTES;
   }
 
   const ds_model_cfg& c = ctx->cfg;

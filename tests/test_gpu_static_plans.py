@@ -1,0 +1,65 @@
+"""ds_decode_step_static on batches whose products have faster plans than its array has room for: the same bits as
+ds_decode_step (which plans such a step against the same size), also from a larger workspace, and the oracle's values."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ds_oracle as orc
+from paper_2401_09670_amd import binding, synth
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+GUARD = 1 << 20
+
+
+def _shape(heads, n_kv):
+    h = heads * 128
+    return synth.ModelShape(hidden=h, n_heads=heads, head_dim=128, ffn=4 * h, n_kv_heads=n_kv)
+
+
+def _bytes_unlimited(ctx, shape, batch):
+    """Activations and partial sums of the step on the fastest plans of its products."""
+    h, m, w = shape.hidden, shape.ffn, shape.qkv_width
+    plans = ((ctx.ds_layer_plan(batch, k, n), n) for k, n in ((h, w), (h, h), (h, m), (m, h)))
+    return batch * 2 * (3 * h + w + m) + max(4 * p["splits"] * batch * n for p, n in plans)
+
+
+# 8192 x 32768 with grouped queries from 65 to 124 sequences, 4096 x 16384 from 129 to 204, OPT-66B from 65 to 92
+@pytest.mark.parametrize("heads,n_kv,batch", [(64, 8, 96), (64, 8, 120), (32, 0, 160), (32, 0, 192), (72, 0, 88)])
+def test_static_step_equals_a_step_with_any_workspace(gpu, heads, n_kv, batch):
+    shape = _shape(heads, n_kv)
+    ctx = gu.make_ctx(shape)
+    lw, w = gu.dev_layer_weights(shape, 500 + batch)
+    h = shape.hidden
+    lens = [(5 * i) % 30 for i in range(batch)]
+    tables, nblk = synth.make_block_tables([l + 1 for l in lens], 16, 3)
+    kc0 = gu.dev_normal_bits((nblk, shape.kv_heads, 16, 128), 1.0, 1)
+    vc0 = gu.dev_normal_bits((nblk, shape.kv_heads, 16, 128), 1.0, 2)
+    x = gu.dev_normal_bits((batch, h), 1.0, 3)
+    lens_d, tables_d, max_ctx = gu.i32_dev(lens), gu.i32_dev(tables), max(lens) + 1
+
+    def step(ws):
+        kc, vc = kc0.clone(), vc0.clone()
+        y = torch.empty(batch, h, dtype=torch.bfloat16, device="cuda")
+        args = (lw, x, lens_d, tables_d, batch, tables.shape[1], max_ctx, kc, vc, nblk, y)
+        ctx.ds_decode_step_static(*args) if ws is None else ctx.ds_decode_step(*args, ws)
+        torch.cuda.synchronize()
+        return y, kc, vc
+
+    reported = ctx.ds_decode_workspace_bytes(batch, max_ctx)
+    assert reported <= binding.STATIC_SCRATCH_BYTES < _bytes_unlimited(ctx, shape, batch)
+    static = step(None)
+    for size in (reported, 4 * binding.STATIC_SCRATCH_BYTES):
+        ws = torch.full((size + GUARD,), 0x55, dtype=torch.uint8, device="cuda")
+        got = step(ws[:size])
+        assert bool((ws[size:] == 0x55).all()), "wrote past the workspace"
+        assert all(torch.equal(a, b) for a, b in zip(got, static)), size
+
+    if heads > 32:
+        return      # (the others' values: too many weights for the host)
+    rows = [0, 1, batch // 2, batch - 2, batch - 1]     # sequences are independent of each other
+    xin = gu.to_f64(x)[rows]
+    want = orc.layer_decode_cached(orc.weights_from_bits(gu.host_weights(w)), xin, [lens[r] for r in rows],
+                                   tables[rows], gu.to_f64(kc0), gu.to_f64(vc0), heads)
+    got = gu.to_f64(static[0])[rows]
+    assert gu.rel_err(got, want) < 1e-2 and gu.rel_err_rows(got, want) < 1e-2 and gu.update_ok(got, want, xin)

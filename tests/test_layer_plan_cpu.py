@@ -61,3 +61,20 @@ def test_workspaces_hold_the_partial_sums_of_every_smaller_call(name):
             need = max(_partials(ctx.ds_layer_plan(rows, k, o), rows, o) for k, o in _products(name))
             assert pre >= rows * 2 * (4 * h + m + 64) + need
             assert dec >= rows * 2 * (3 * h + wide + m) + need
+
+
+@pytest.mark.parametrize("name,largest", [("opt13b", 128), ("opt66b", 92), ("opt175b", 72), ("gqa", 124)])
+def test_decode_workspace_says_what_the_static_array_takes(name, largest):
+    """The largest batch that ds_decode_step_static accepts is the largest whose reported workspace fits its array: what
+    the plans of ds_linear need, not what the faster ones of a layer would use."""
+    h, n, s, m, n_kv = SHAPES[name]
+    wide, up = (n + 2 * (n_kv or n)) * s, lambda v: (v + 255) // 256 * 256
+    ctx = _ctx(name)
+
+    def least(batch):       # (without attention partials: none at 16 tokens)
+        partials = max(ctx.ds_linear_workspace_bytes(r, k, o) for r in range(1, batch + 1) for k, o in _products(name))
+        return sum(up(2 * batch * f) for f in (h, h, h, wide, m)) + up(partials)
+
+    assert least(largest) <= binding.STATIC_SCRATCH_BYTES < least(largest + 1)
+    assert ctx.ds_decode_workspace_bytes(largest, 16) <= binding.STATIC_SCRATCH_BYTES
+    assert ctx.ds_decode_workspace_bytes(largest + 1, 16) > binding.STATIC_SCRATCH_BYTES
