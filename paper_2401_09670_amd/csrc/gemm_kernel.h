@@ -212,8 +212,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   auto xk = walk();
   const int KT = xk.count();  // >= 1: splits <= K / 64
   // Spread starts: each XCD (id % 8) begins at an eighth of its own, where the row stride puts the pieces that all rows
-  // have at one position of K on few memory channels.
-  if (NT && p.spread) xk.start((int)(((blockIdx.x + gridDim.x * blockIdx.y) & 7) * (unsigned)KT / 8));
+  // have at one position of K on few memory channels.  Where the row tiles of a column lie on two XCDs, all of them begin
+  // where the first does: equal rows have equal sums, whatever their place in the batch.
+  if (NT && p.spread) {
+    const int total = p.tiles_m * p.tiles_n, full = total & ~255, v = tile_n * min(p.tiles_m, 16);  // (patch_tile's numbers)
+    const int xcd = v < full ? (v & 255) >> 5 : (v - full) * 8 / (total - full);
+    xk.start((int)((((unsigned)xcd + gridDim.x * blockIdx.y) & 7) * (unsigned)KT / 8));
+  }
   auto wk = xk;
 
   // per-lane source offsets (bytes, from the tile's first row) of this wave's loads; load j covers rows
