@@ -33,10 +33,14 @@ DS_SWITCH(g_gemm_spread, -1);  // 0, 1: never, always
 
 // Weights carry the non-temporal hint where they come from memory once: up to eight row tiles, which an XCD's 32
 // workgroups take together (patch_tile).  They leave the activations, which every workgroup reads, in L2: 256 x 49152 x
-// 12288 303 -> 241 us, 256 x 12288 x 12288 94 -> 87, 512 x 36864 x 12288 409 -> 367, 1024 x 12288 x 12288 260 -> 231.  At
+// 12288 303 -> 241 us, 256 x 12288 x 12288 98 -> 85, 512 x 36864 x 12288 431 -> 377, 256 x 32768 x 8192 171 -> 121.  At
 // 12 row tiles it is a draw (2985 x 15360 x 5120 362 and 374 us, x 20480 499 and 479), at 32 the weights are read again
-// from further away (8192 x 12288 x 49152 6.98 and 7.79 ms).  Small ones are better kept (52 MB, 96 to 192 rows: 3 to 14 %
-// slower with the hint; 134 to 170 MB: between 7 % faster and 4 % slower).
+// from further away (8192 x 12288 x 49152 6.98 and 7.79 ms).
+//   Small ones are better without it, also where 2.2 GB of other weights come between two uses of theirs.  Each product on
+// its plan, without and with the hint: 4096 x 4096 (34 MB) at 128 rows 17.2 and 19.0 us, at 256 22.7 and 24.8, from 275 on
+// the same; 5120 x 5120 (52 MB) at 128 rows 23.1 and 24.4, at 160 26.0 and 28.2, from 224 on the same; 12288 x 4096 (101
+// MB) at 160 and 256 rows 36.3 and 35.0, 44.1 and 42.1; 8192 x 8192 (134 MB) 43.3 and 38.8, 50.5 and 46.6; 15360 x 5120
+// (157 MB) 45.0 and 43.8, 58.9 and 57.9.  (Slower with it above the line: 4096 x 16384 on 11 splits, 224 rows 48 and 55.)
 constexpr int kFewRowTiles = 8;
 //   That is for the products of a layer, whose other weights come between two uses of these.  ds_linear may be called with
 // the same weights again, and the last-level cache holds 256 MB, out of which the hint would keep them: 15360 x 5120 (157
@@ -53,9 +57,9 @@ static hipError_t launch_tile(int tile, GemmParams p, int splits, bool in_layer,
   if (g_gemm_spread >= 0) p.spread = g_gemm_spread;
   bool nt = p.tiles_m <= kFewRowTiles && 2.0 * p.N * p.K >= (in_layer ? kStreamedBytes : kCachedBytes);
   if (g_gemm_nt >= 0) nt = g_gemm_nt;
-  return tile < kFirstFewRows
-             ? launch_any<1>(tile, p, nt, splits, stream, std::make_integer_sequence<int, kFirstFewRows - 1>())
-             : launch_few_row_tile(tile, p, nt, splits, stream);
+  return tile < kFirstLayerTile
+             ? launch_any<1>(tile, p, nt, splits, stream, std::make_integer_sequence<int, kFirstLayerTile - 1>())
+             : launch_layer_tile(tile, p, nt, splits, stream);
 }
 
 // Cost model used to pick a tile shape: (rounds of workgroups on 256 CUs, one workgroup per CU) x
@@ -250,7 +254,7 @@ GemmPlan layer_plan(int M, int N, int K, size_t partial_bytes, double* us_out) {
     const int rest = N - (int)(c * t.bn);
     const double head_us = layer_us(t, rows, (int)(c * t.bn), K, 1);
     for (int j = 1; j < kNumTiles; ++j) {
-      if (!kTiles[j].large || kTiles[j].bn >= t.bn) continue;
+      if (!kTiles[j].tail || kTiles[j].bn >= t.bn) continue;
       const double us = head_us + layer_us(kTiles[j], rows, rest, K, 1);
       if (us < best_us) {
         best_us = us;

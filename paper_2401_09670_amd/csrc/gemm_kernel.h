@@ -518,11 +518,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
 }
 
 // The tiles there are, numbered from 1 (the numbers are what g_gemm_variant forces): rows x columns, waves along each,
-// stages of X and W, what a kernel is built for, and what the time model (layer_plan) knows of it.  Larger tiles than
+// stages of X and W, what it may be used for, and what the time model (layer_plan) knows of it.  Larger tiles than
 // these do not fit the registers (256 accumulator registers of a wave) or the LDS with two stages.
 struct Tile {
   int bm, bn, wm, wn, xs, ws;
-  bool large;          // also without the non-temporal hint (launch_tile)
+  bool tail;           // may take the columns behind a cut
   bool kv;             // also with the K/V scatter of a decoding step
   double k_us, t0_us;  // of a k-tile, of prologue and epilogue
 };
@@ -560,31 +560,25 @@ inline hipError_t launch_kernel(const GemmParams& p, int splits, hipStream_t str
   return hipGetLastError();
 }
 
-// One launch of tile T; nt: weights with the non-temporal hint.
-template <int T>
-inline hipError_t launch_one(const GemmParams& p, bool nt, int splits, hipStream_t stream) {
-  constexpr Tile t = kTiles[T];
-  if constexpr (t.large) {
-    if (!nt) {
-      if (splits > 1) return launch_kernel<T, kEpiPartial, false>(p, splits, stream);
-      if (!p.k_cache) return launch_kernel<T, kEpiPlain, false>(p, 1, stream);
-    }
-  }
-  if (splits > 1) return launch_kernel<T, kEpiPartial, true>(p, splits, stream);
-  if constexpr (t.kv)
-    if (p.k_cache) return launch_kernel<T, kEpiKvScatter, true>(p, 1, stream);
-  return launch_kernel<T, kEpiPlain, true>(p, 1, stream);
+// One launch of tile T.
+template <int T, bool NT>
+inline hipError_t launch_one(const GemmParams& p, int splits, hipStream_t stream) {
+  if (splits > 1) return launch_kernel<T, kEpiPartial, NT>(p, splits, stream);
+  if constexpr (kTiles[T].kv)
+    if (p.k_cache) return launch_kernel<T, kEpiKvScatter, NT>(p, 1, stream);
+  return launch_kernel<T, kEpiPlain, NT>(p, 1, stream);
 }
 template <int FIRST, int... T>
 inline hipError_t launch_any(int tile, const GemmParams& p, bool nt, int splits, hipStream_t stream,
                              std::integer_sequence<int, T...>) {
   hipError_t e = hipErrorInvalidValue;
-  (void)((tile == FIRST + T && ((e = launch_one<FIRST + T>(p, nt, splits, stream)), true)) || ...);
+  (void)((tile == FIRST + T && ((e = nt ? launch_one<FIRST + T, true>(p, splits, stream)
+                                          : launch_one<FIRST + T, false>(p, splits, stream)), true)) || ...);
   return e;
 }
 
-// The tiles from number kFirstFewRows on (gemm_tiles.hip).
-constexpr int kFirstFewRows = 8;
-hipError_t launch_few_row_tile(int tile, const GemmParams& p, bool nt, int splits, hipStream_t stream);
+// The tiles from number kFirstLayerTile on, which only products of a layer take (gemm_tiles.hip).
+constexpr int kFirstLayerTile = 8;
+hipError_t launch_layer_tile(int tile, const GemmParams& p, bool nt, int splits, hipStream_t stream);
 
 }  // namespace ds
