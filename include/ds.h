@@ -203,9 +203,11 @@ size_t ds_linear_workspace_bytes(const ds_ctx *ctx, int32_t rows, int32_t in_f, 
  * to fill the chip (Sec. 3.1). */
 ds_status ds_linear_plan(const ds_ctx *ctx, int32_t rows, int32_t in_f, int32_t out_f, int32_t *streaming,
                          int32_t *tile_rows, int32_t *tile_cols, int32_t *splits, int32_t *cut_cols);
-/* The same for the product as ds_prefill and ds_decode_step run it, given the workspace of ds_*_workspace_bytes: from 65
+/* The same for the product as ds_prefill and ds_decode_step run it, given all the workspace its plan would use: from 65
  * rows on they choose among more tile shapes and split further than ds_linear, whose plan and workspace stay what
- * its two queries say. */
+ * its two queries say, and below that a small product is left unsplit.  (A step that the static array can run is
+ * planned against its size, see ds_decode_step_static, and may split less than reported here.)  hidden x hidden is
+ * taken for the out-projection, which LayerNorm-2 follows. */
 ds_status ds_layer_plan(const ds_ctx *ctx, int32_t rows, int32_t in_f, int32_t out_f, int32_t *streaming,
                         int32_t *tile_rows, int32_t *tile_cols, int32_t *splits, int32_t *cut_cols);
 ds_status ds_linear(ds_ctx *ctx, const void *x, const void *w, const void *bias,

@@ -544,8 +544,17 @@ ds_status ds_linear_plan(const ds_ctx* ctx, int32_t rows, int32_t in_f, int32_t 
 ds_status ds_layer_plan(const ds_ctx* ctx, int32_t rows, int32_t in_f, int32_t out_f, int32_t* streaming,
                         int32_t* tile_rows, int32_t* tile_cols, int32_t* splits, int32_t* cut_cols) {
   const ds_status st = ds_linear_plan(ctx, rows, in_f, out_f, streaming, tile_rows, tile_cols, splits, cut_cols);
+  if (st != DS_OK) return st;
   ds::GemmPlan plan;
-  if (st != DS_OK || !layer_tiles(rows, in_f, out_f, ~(size_t)0, &plan)) return st;
+  if (!layer_tiles(rows, in_f, out_f, ~(size_t)0, &plan)) {
+    if (*streaming) {  // as layer_linear calls it; LayerNorm-2 rides with the out-projection
+      const bool out_proj = in_f == ctx->cfg.hidden && out_f == ctx->cfg.hidden;
+      int tc, sp;
+      ds::skinny_describe(rows, out_f, in_f, &tc, &sp, !out_proj, true);
+      *tile_cols = tc; *splits = sp;
+    }
+    return DS_OK;
+  }
   int tr, tc;
   ds::gemm_tile_shape(plan.tile, &tr, &tc);
   *streaming = 0;

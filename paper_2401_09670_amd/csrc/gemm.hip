@@ -369,15 +369,15 @@ hipError_t launch_gemm(const void* X, const void* W, int M, int N, int K, const 
                        fused->head_dim % 8 == 0;
   if (pl.splits > 1) {
     p.partial = (float*)workspace;
-  } else if (want_kv && kTiles[pl.tile].kv) {
-    // unsplit: the tile kernel's own epilogue scatters K and V into the cache
+  } else if (want_kv && kTiles[pl.tile].kv && (pl.cut_cols == 0 || kTiles[pl.tail_tile].kv)) {
+    // unsplit: the tile kernels' own epilogue scatters K and V into the cache
     p.ctx_lens = fused->ctx_lens; p.block_tables = fused->block_tables; p.max_blocks = fused->max_blocks;
     p.k_cache = (uint16_t*)fused->k_cache; p.v_cache = (uint16_t*)fused->v_cache;
     p.n_heads = fused->n_heads; p.n_kv_heads = fused->n_kv_heads; p.head_dim = fused->head_dim;
     if (fused_done) *fused_done = true;
   }
   hipError_t e;
-  if (pl.cut_cols > 0 && pl.splits == 1 && !p.k_cache) {
+  if (pl.cut_cols > 0 && pl.splits == 1) {
     // Leading columns on the large tile in whole rounds of 256 workgroups, the rest on a smaller tile: two
     // launches over disjoint column ranges [0, cut) and [cut, N) of the same product (same operands, bias,
     // residual and output segments; only the column range differs).

@@ -944,17 +944,26 @@ hipError_t launch_splitk_reduce(const float* partial, int splits, int M, int N, 
   return hipGetLastError();
 }
 
-// What launch_skinny_gemm does for a plain product of this shape: columns per workgroup and splits over K
-// (1 split and 64 or 80 columns = the unsplit kernel with wave-private rings).
-void skinny_describe(int M, int N, int K, int* tile_cols, int* splits) {
-  if (const int nt = wring_tiles(M, N, K)) {
-    *tile_cols = 16 * nt;
-    *splits = 1;
-    return;
-  }
-  const SkinnyPlan pl = skinny_plan(M, N, K);
-  *tile_cols = 64 * pl.ntw;
-  *splits = pl.splits;
+// Which kernel takes a product: the one with wave-private rings (wring: 16-row tiles of W a workgroup, unsplit), or, with
+// wring = 0, the ring kernel by `plan`.  own_epilogue: no LayerNorm wants a reduce pass to ride in.
+struct SkinnyRoute {
+  int wring;
+  SkinnyPlan plan;
+};
+static SkinnyRoute skinny_route(int M, int N, int K, bool own_epilogue, bool weigh_reduce) {
+  SkinnyRoute r{own_epilogue ? wring_tiles(M, N, K) : 0, {1, 1}};
+  if (r.wring > 0) return r;
+  double split;
+  r.plan = skinny_plan(M, N, K, true, &split);
+  if (weigh_reduce && own_epilogue && r.plan.splits > 1 && unsplit_bytes(M, N, K) < split - kReduceBytes + 24e6)
+    r.plan = SkinnyPlan{1, 1};
+  return r;
+}
+
+void skinny_describe(int M, int N, int K, int* tile_cols, int* splits, bool own_epilogue, bool weigh_reduce) {
+  const SkinnyRoute r = skinny_route(M, N, K, own_epilogue, weigh_reduce);
+  *tile_cols = r.wring > 0 ? 16 * r.wring : 64 * r.plan.ntw;
+  *splits = r.plan.splits;
 }
 
 // By the bytes the plans go by, fitted to 16 products at 65, 96 and 128 rows (within 10 %; 12288 x 49152 left out: two
@@ -996,23 +1005,17 @@ hipError_t launch_skinny_gemm(const void* X, const void* W, int M, int N, int K,
   const bool want_kv = fused && fused->kind == SkinnyFused::kKvAppend && ep.seg_cols == N && !ep.relu &&
                        !ep.residual && N == (fused->n_heads + 2 * fused->n_kv_heads) * fused->head_dim &&
                        fused->head_dim % 4 == 0;
-  const int nt = (plain || want_kv) ? wring_tiles(M, N, K) : 0;
-  SkinnyPlan pl{1, 1};
-  if (nt == 0) {
-    double split;
-    pl = skinny_plan(M, N, K, true, &split);
-    if (weigh_reduce && (plain || want_kv) && pl.splits > 1 && unsplit_bytes(M, N, K) < split - kReduceBytes + 24e6)
-      pl = SkinnyPlan{1, 1};
-  }
+  const SkinnyRoute route = skinny_route(M, N, K, plain || want_kv, weigh_reduce);
+  const SkinnyPlan pl = route.plan;
   if (want_kv && pl.splits == 1) {
     p.kv_ctx_lens = fused->ctx_lens; p.kv_block_tables = fused->block_tables; p.kv_max_blocks = fused->max_blocks;
     p.kv_k_cache = (uint16_t*)fused->k_cache; p.kv_v_cache = (uint16_t*)fused->v_cache;
     p.kv_n_heads = fused->n_heads; p.kv_n_kv_heads = fused->n_kv_heads; p.kv_head_dim = fused->head_dim;
     if (fused_done) *fused_done = true;
   }
-  if (nt > 0) {
+  if (route.wring > 0) {
     p.partial = nullptr;
-    return launch_wring(nt, p, stream);
+    return launch_wring(route.wring, p, stream);
   }
   p.partial = (float*)workspace;
   if (pl.splits > 1 && workspace == nullptr) return hipErrorInvalidValue;

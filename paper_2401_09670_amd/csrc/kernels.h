@@ -110,7 +110,10 @@ hipError_t launch_splitk_reduce(const float* partial, int splits, int M, int N, 
 // launch less for the host (2 rows of 1024 -> 256), 3072 x 1024 at 64 rows 3 us.
 size_t skinny_workspace_bytes(int M, int N, int K);
 double skinny_us(int M, int N, int K);  // time launch_skinny_gemm takes for 65 to 128 rows, to be held against layer_plan's
-void skinny_describe(int M, int N, int K, int* tile_cols, int* splits);  // the plan launch_skinny_gemm follows
+// What launch_skinny_gemm does: columns per workgroup and splits over K (1 split and 64 or 80 columns = the unsplit kernel
+// with wave-private rings, or the ring kernel unsplit).  own_epilogue = false: with a LayerNorm in its reduce pass.
+void skinny_describe(int M, int N, int K, int* tile_cols, int* splits, bool own_epilogue = true,
+                     bool weigh_reduce = false);
 hipError_t launch_skinny_gemm(const void* X, const void* W, int M, int N, int K, const Epilogue& ep,
                               void* workspace, hipStream_t stream, const SkinnyFused* fused = nullptr,
                               bool* fused_done = nullptr, bool weigh_reduce = false);

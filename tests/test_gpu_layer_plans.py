@@ -140,6 +140,15 @@ def test_decode_step_scatters_k_and_v_from_unsplit_tiles(gpu, batch, tile):
     _kv_scatter_case(shape, batch)
 
 
+@pytest.mark.parametrize("heads,n_kv,batch", [(96, 0, 450), (96, 0, 512), (64, 8, 1800)])
+def test_decode_step_scatters_k_and_v_on_both_sides_of_a_cut(gpu, heads, n_kv, batch):
+    """QKV on 256x192 tiles in whole rounds, the remaining columns - of V, or of K and V - on other tiles."""
+    shape = synth.ModelShape(hidden=heads * 128, n_heads=heads, head_dim=128, ffn=512, n_kv_heads=n_kv)
+    plan = gu.make_ctx(shape).ds_layer_plan(batch, shape.hidden, shape.qkv_width)
+    assert (plan["tile_rows"], plan["tile_cols"]) == (256, 192) and 0 < plan["cut_cols"] < shape.qkv_width
+    _kv_scatter_case(shape, batch)
+
+
 @pytest.mark.parametrize("batch", [1, 15, 16, 33, 64, 67, 129])
 @pytest.mark.parametrize("heads,head_dim,n_kv", [(4, 64, 0), (6, 128, 2), (8, 128, 0)])
 def test_decode_step_scatters_k_and_v_of_small_layers(gpu, heads, head_dim, n_kv, batch):
