@@ -228,8 +228,6 @@ static double layer_us(const Tile& t, int rows, int N, int K, int splits) {
   return us;
 }
 
-constexpr int kLayerMaxRows = 4096;
-
 GemmPlan layer_plan(int M, int N, int K, size_t partial_bytes, double* us_out) {
   const int rows = (M + 31) / 32 * 32, kt = K / kBK;  // by rows in 32s: sizing a workspace asks for every plan up to M
   GemmPlan best{2, 1};
