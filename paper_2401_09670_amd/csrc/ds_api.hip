@@ -3,6 +3,7 @@
 // are enqueued.  No device memory is allocated here.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -27,13 +28,27 @@ struct ds_ctx {
   };
   std::vector<Rec> recs;
   std::vector<hipEvent_t> pool;
-  // Workspace sizes already worked out (they walk every smaller row count through the GEMM planners, tens of
-  // microseconds; every ds_prefill / ds_decode_step call checks its workspace against them).
-  struct Workspace {
-    size_t least, full;  // below `least` a call is refused, from `full` on every product has its fastest plan
+  // What a workspace must hold takes the plans of every smaller row count too, 0.1 to 0.3 us each: hundreds of
+  // microseconds for long prompts if each call of a new size (a ragged batch: almost every one) went through them anew.
+  // So the largest partial sums of the rows gone through are kept, and a new size adds the rows that are new.
+  struct RunningMax {
+    std::vector<size_t> upto;
+    template <class Of>
+    size_t at(size_t i, Of&& of) {
+      while (upto.size() <= i) {
+        const size_t v = of(upto.size());
+        upto.push_back(upto.empty() || v > upto.back() ? v : upto.back());
+      }
+      return upto[i];
+    }
   };
-  mutable std::map<int, Workspace> prefill_ws;
-  mutable std::map<std::pair<int, int>, Workspace> decode_ws;
+  mutable RunningMax linear_partials, layer_partials;
+  // ... and the sizes worked out that a call is checked against (below them it is refused)
+  struct Least {
+    size_t all, partials;
+  };
+  mutable std::map<int, Least> prefill_least;
+  mutable std::map<std::pair<int, int>, Least> decode_least;
 };
 
 // ---- per-device set-up: kernel attributes, address of the static scratch array ----
@@ -284,44 +299,47 @@ size_t linear_ws_exact(int rows, int in_f, int out_f) {
                                 : ds::gemm_workspace_bytes(rows, out_f, in_f);
 }
 
-// ... and for any row count up to `rows` (fewer rows can mean more splits), so that a workspace sized
-// for a maximum serves every smaller call.  Up to 256 rows the plan may change with every row count; above,
-// only with the number of row tiles (multiples of 64).
-size_t linear_ws(int rows, int in_f, int out_f) {
+// The largest of of(in_f, out_f) over the four products of a layer.
+template <class Of>
+size_t largest_product(const ds_model_cfg& c, Of&& of) {
+  const int shapes[4][2] = {{c.hidden, qkv_width(c)}, {c.hidden, c.hidden}, {c.hidden, c.ffn}, {c.ffn, c.hidden}};
   size_t need = 0;
-  for (int r = 1; r <= rows; r = r < 256 ? r + 1 : r + 64) {
-    const size_t b = linear_ws_exact(r, in_f, out_f);
-    if (b > need) need = b;
-  }
-  const size_t b = linear_ws_exact(rows, in_f, out_f);
-  return b > need ? b : need;
-}
-
-// Partial sums of the layer's own plans for any row count up to `rows`: they go by rows in 32s.
-size_t layer_ws(int rows, int in_f, int out_f) {
-  size_t need = 0;
-  const int last = rows < kLayerMaxRows ? rows : kLayerMaxRows;
-  for (int r = (kLayerMinRows + 31) / 32 * 32; r < last + 32; r += 32) {
-    const ds::GemmPlan plan = ds::layer_plan(r, out_f, in_f, ~(size_t)0);
-    const size_t b = plan.splits > 1 ? sizeof(float) * plan.splits * r * (size_t)out_f : 0;
+  for (const auto& f : shapes) {
+    const size_t b = of(f[0], f[1]);
     if (b > need) need = b;
   }
   return need;
 }
 
-// ... of the four products of a layer: what the plans of `linear` need, and what the layer's own would use
-ds_ctx::Workspace max_gemm_ws(const ds_model_cfg& c, int rows) {
-  const int shapes[4][2] = {{c.hidden, qkv_width(c)}, {c.hidden, c.hidden}, {c.hidden, c.ffn}, {c.ffn, c.hidden}};
-  ds_ctx::Workspace ws{0, 0};
-  for (const auto& f : shapes) {
-    const size_t least = linear_ws(rows, f[0], f[1]), full = layer_ws(rows, f[0], f[1]);
-    if (least > ws.least) ws.least = least;
-    if (full > ws.full) ws.full = full;
-  }
-  if (ws.full < ws.least) ws.full = ws.least;
-  ws.least = align_up(ws.least, 256);
-  ws.full = align_up(ws.full, 256);
-  return ws;
+// What `linear` needs for the four products with `rows` rows or any fewer (fewer rows can mean more splits), so that a
+// workspace sized for a maximum serves every smaller call.  Up to 256 rows the plan may change with every row count;
+// above, only with the number of row tiles (multiples of 64).
+size_t least_gemm_ws(const ds_ctx* ctx, int rows) {
+  constexpr int kFine = 256, kStep = 64, kKeptRows = 65536;
+  const auto exact = [&](int r) {
+    return largest_product(ctx->cfg, [&](int in_f, int out_f) { return linear_ws_exact(r, in_f, out_f); });
+  };
+  const int kept = rows < kKeptRows ? rows : kKeptRows;
+  const size_t last = kept <= kFine ? kept - 1 : kFine - 1 + (kept - kFine) / kStep;
+  size_t need = ctx->linear_partials.at(
+      last, [&](size_t i) { return exact(i < kFine ? (int)i + 1 : kFine + kStep * ((int)i - kFine + 1)); });
+  for (long r = kKeptRows + kStep; r <= rows; r += kStep) need = std::max(need, exact((int)r));
+  return align_up(std::max(need, exact(rows)), 256);
+}
+
+// A workspace in which the layer's own plans (they go by rows in 32s) have room too.
+size_t full_ws(const ds_ctx* ctx, int rows, const ds_ctx::Least& least) {
+  constexpr int kStep = 32, kFirst = (kLayerMinRows + kStep - 1) / kStep * kStep;
+  if (rows < kLayerMinRows) return least.all;
+  const int most = ((rows < kLayerMaxRows ? rows : kLayerMaxRows) + kStep - 1) / kStep * kStep;
+  const size_t layer = ctx->layer_partials.at((most - kFirst) / kStep, [&](size_t i) {
+    const int r = kFirst + kStep * (int)i;
+    return largest_product(ctx->cfg, [&](int in_f, int out_f) {
+      const ds::GemmPlan plan = ds::layer_plan(r, out_f, in_f, ~(size_t)0);
+      return plan.splits > 1 ? sizeof(float) * plan.splits * r * (size_t)out_f : 0;
+    });
+  });
+  return least.all - least.partials + std::max(least.partials, align_up(layer, 256));
 }
 
 // Every call that launches goes through here first: the device's one-time set-up (normally done by ds_create;
@@ -406,25 +424,24 @@ ds_status check_weights(ds_ctx* ctx, const ds_layer_weights* w) {
   return DS_OK;
 }
 
-ds_ctx::Workspace prefill_workspace(const ds_ctx* ctx, int max_tokens) {
-  const auto hit = ctx->prefill_ws.find(max_tokens);
-  if (hit != ctx->prefill_ws.end()) return hit->second;
+ds_ctx::Least prefill_least(const ds_ctx* ctx, int max_tokens) {
+  const auto hit = ctx->prefill_least.find(max_tokens);
+  if (hit != ctx->prefill_least.end()) return hit->second;
   const ds_model_cfg& c = ctx->cfg;
   const size_t th = align_up((size_t)max_tokens * c.hidden * 2, 256);
   const size_t tm = align_up((size_t)max_tokens * (c.ffn + kRowPad) * 2, 256);
+  const size_t partials = least_gemm_ws(ctx, max_tokens);
   // a (LN out, reused for LN2), q, o, x1, u (rows padded), + split-K partials of the GEMMs
-  ds_ctx::Workspace need = max_gemm_ws(c, max_tokens);
-  need.least += 4 * th + tm;
-  need.full += 4 * th + tm;
-  if (ctx->prefill_ws.size() < 4096) ctx->prefill_ws[max_tokens] = need;
+  const ds_ctx::Least need{4 * th + tm + partials, partials};
+  if (ctx->prefill_least.size() < 4096) ctx->prefill_least[max_tokens] = need;
   return need;
 }
 
-ds_ctx::Workspace decode_workspace(const ds_ctx* ctx, int max_batch, int max_ctx) {
+ds_ctx::Least decode_least(const ds_ctx* ctx, int max_batch, int max_ctx) {
   // the attention partials depend on max_ctx only through its page count
   const std::pair<int, int> key(max_batch, (max_ctx + 15) / 16);
-  const auto hit = ctx->decode_ws.find(key);
-  if (hit != ctx->decode_ws.end()) return hit->second;
+  const auto hit = ctx->decode_least.find(key);
+  if (hit != ctx->decode_least.end()) return hit->second;
   const ds_model_cfg& c = ctx->cfg;
   const size_t bh = align_up((size_t)max_batch * c.hidden * 2, 256);
   const size_t b3h = align_up((size_t)max_batch * qkv_width(c) * 2, 256);
@@ -436,13 +453,9 @@ ds_ctx::Workspace decode_workspace(const ds_ctx* ctx, int max_batch, int max_ctx
     if (v > att) att = v;
   }
   // a, qkv, o, x1, u, attention partials, split-K partials
-  const size_t rest = 3 * bh + b3h + bm + align_up(att, 256);
-  ds_ctx::Workspace need = max_gemm_ws(c, max_batch);
-  need.least += rest;
-  need.full += rest;
-  // A step that the static array can run has the plans that fit there (decode_step), and asks for no more.
-  if (need.least <= DS_STATIC_SCRATCH_BYTES && need.full > DS_STATIC_SCRATCH_BYTES) need.full = DS_STATIC_SCRATCH_BYTES;
-  if (ctx->decode_ws.size() < 4096) ctx->decode_ws[key] = need;
+  const size_t partials = least_gemm_ws(ctx, max_batch);
+  const ds_ctx::Least need{3 * bh + b3h + bm + align_up(att, 256) + partials, partials};
+  if (ctx->decode_least.size() < 4096) ctx->decode_least[key] = need;
   return need;
 }
 
@@ -496,12 +509,17 @@ void ds_destroy(ds_ctx* ctx) {
 
 const char* ds_last_error(const ds_ctx* ctx) { return ctx ? ctx->err : "ctx is NULL"; }
 
+// From these sizes on every product has its fastest plan.
 size_t ds_prefill_workspace_bytes(const ds_ctx* ctx, int32_t max_tokens) {
-  return ctx && max_tokens > 0 ? prefill_workspace(ctx, max_tokens).full : 0;
+  return ctx && max_tokens > 0 ? full_ws(ctx, max_tokens, prefill_least(ctx, max_tokens)) : 0;
 }
 
 size_t ds_decode_workspace_bytes(const ds_ctx* ctx, int32_t max_batch, int32_t max_ctx) {
-  return ctx && max_batch > 0 && max_ctx > 0 ? decode_workspace(ctx, max_batch, max_ctx).full : 0;
+  if (!ctx || max_batch <= 0 || max_ctx <= 0) return 0;
+  const ds_ctx::Least least = decode_least(ctx, max_batch, max_ctx);
+  const size_t full = full_ws(ctx, max_batch, least);
+  // A step that the static array can run has the plans that fit there (decode_step), and asks for no more.
+  return least.all <= DS_STATIC_SCRATCH_BYTES && full > DS_STATIC_SCRATCH_BYTES ? DS_STATIC_SCRATCH_BYTES : full;
 }
 
 ds_status ds_layernorm(ds_ctx* ctx, const void* x, const void* gamma, const void* beta, int32_t rows,
@@ -668,7 +686,7 @@ ds_status ds_prefill(ds_ctx* ctx, const ds_layer_weights* w, const void* x, cons
   if (x == y) return fail(ctx, DS_ERR_INVALID_ARG, "ds_prefill: y must not alias x");
   if (!aligned16(x) || !aligned16(y) || !aligned16(k_out) || !aligned16(v_out) || !aligned16(workspace))
     return fail(ctx, DS_ERR_INVALID_ARG, "ds_prefill: pointers must be 16-byte aligned");
-  const size_t need = prefill_workspace(ctx, t).least;
+  const size_t need = prefill_least(ctx, t).all;
   if (!workspace || workspace_bytes < need)
     return fail(ctx, DS_ERR_WORKSPACE, "ds_prefill: workspace %zu < %zu", workspace_bytes, need);
   if ((st = ensure_device(ctx)) != DS_OK) return st;
@@ -819,7 +837,7 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
   if (x == y) return fail(ctx, DS_ERR_INVALID_ARG, "ds_decode_step: y must not alias x");
   if (!aligned16(x) || !aligned16(y) || !aligned16(k_cache) || !aligned16(v_cache) || !aligned16(workspace))
     return fail(ctx, DS_ERR_INVALID_ARG, "ds_decode_step: pointers must be 16-byte aligned");
-  const size_t need = decode_workspace(ctx, B, max_ctx).least;
+  const size_t need = decode_least(ctx, B, max_ctx).all;
   const DeviceState* dev = nullptr;
   if (use_static) {
     if (need > (size_t)DS_STATIC_SCRATCH_BYTES)
