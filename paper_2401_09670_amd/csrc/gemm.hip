@@ -212,21 +212,43 @@ static GemmPlan prefill_plan(int M, int N, int K) {
 // mean; 0.3 % from 1025 rows on).  Against the plans above it saves 27 % of a product's time at 129 to 256 rows (12288 x
 // 49152: 461 -> 273 us at 256), 20 % at 257 to 512 (the four of OPT-13B at 275 rows: 283 -> 232 us), 10 % to 1024, 3 %
 // to 4096.  More rows are left to the plans above (within 1 % of each other).
+//   Four things a second sweep showed (32 products: those and the ones of layers of 1024, 2048 and 4096 features, 38 row
+// counts, 2.2 GB of weights in rotation, against the plans above and the ones without these terms):
+// kAlone: one row tile over weights without the hint (launch_tile), where its k_us, fitted with it, are short: 5120 x 5120 at
+//   208 and 256 rows 29.7 and 31.7 us on 256x128 tiles, 27.4 and 29.7 on 128x128.
+// kFewChannels: rows a multiple of 64 KB apart; a multiple of four splits meets fewer memory channels there, turns or not:
+//   8192 x 32768 on 128x256 tiles at 96 and 128 rows 104.8 and 111.7 us with 8 splits, 97.7 and 105.7 with 7.  Not with 256x256
+//   tiles, whose loads do not bound them (240 rows: 139 us on 8 splits, 145 on 256x192), nor with more row tiles (512 rows: 228
+//   on 4 splits, 250 on 2).
+// kCut: 57 cuts within 3 % of the best plan without one took 2 % more beside it than the sum of their launches says (median).
+//   9216 x 9216 at 2048 rows 279 us cut, 269 not, 12288 x 49152 1897 and 1808; those that pay stay (27648 x 9216 at 2048 rows
+//   746 us cut, 797 not).
+// kKeep: up to 256 rows of weights without the hint the plan above (most often 128x128 tiles, of which the model has two row
+//   tiles 10 to 15 % too long) stays unless another tile promises 10 %: 5120 x 5120 at 160 rows 26.0 -> 25.2 us, 4096 x 4096
+//   22.1 -> 20.3.
+// What stays slower than without plans of a layer: 65 to 112 rows of 4096 and 2048 features to three times as many (26.7 us
+// before, 29.1; 14.3 before, 17.3), where skinny_us is too long for launches that leave units idle.
 struct LayerModel {
   static constexpr double kLaunch = 4.8, kIdle = 0.33, kLate = 0.71, kHeat = 0.06;  // us, shares
   static constexpr double kHbm = 10.7e6, kReduce = 4.0, kPartials = 8.7e6;          // bytes a us, us, bytes a us
+  static constexpr double kCut = 1.015, kKeep = 0.90;
+  static constexpr double kAlone = 0.15, kFewChannels = 0.10;                       // shares
 };
 static double layer_us(const Tile& t, int rows, int N, int K, int splits) {
-  const long tiles = (long)((rows + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
+  const long tiles_m = (rows + t.bm - 1) / t.bm, tiles = tiles_m * ((N + t.bn - 1) / t.bn) * splits;
   const double exact = tiles / 256.0, full = (double)((tiles + 255) / 256);
   const double rounds = tiles <= 256 ? 1.0 - LayerModel::kIdle * (1.0 - exact) : exact + LayerModel::kLate * (full - exact);
   const double heat = tiles <= 256 ? 1.0 : 1.0 + LayerModel::kHeat * (1.0 - 1.0 / exact);
-  const double loop = rounds * ((K / kBK + splits - 1) / splits) * t.k_us * heat;
+  double loop = rounds * ((K / kBK + splits - 1) / splits) * t.k_us * heat;
+  if (tiles_m == 1 && 2.0 * N * K < kStreamedBytes) loop *= 1.0 + LayerModel::kAlone;
+  if (splits % 4 == 0 && K % 32768 == 0 && tiles_m == 1 && t.bm * t.bn < 256 * 256) loop *= 1.0 + LayerModel::kFewChannels;
   const double hbm = 2.0 * N * K / LayerModel::kHbm;
   double us = LayerModel::kLaunch + sqrt(loop * loop + hbm * hbm) + (rounds > 1.0 ? rounds : 1.0) * t.t0_us;
   if (splits > 1) us += LayerModel::kReduce + (8.0 * splits + 2.0) * rows * N / LayerModel::kPartials;
   return us;
 }
+
+static GemmPlan gemm_plan(int M, int N, int K);
 
 GemmPlan layer_plan(int M, int N, int K, size_t partial_bytes, double* us_out) {
   const int rows = (M + 31) / 32 * 32, kt = K / kBK;  // by rows in 32s: sizing a workspace asks for every plan up to M
@@ -253,11 +275,19 @@ GemmPlan layer_plan(int M, int N, int K, size_t partial_bytes, double* us_out) {
     const double head_us = layer_us(t, rows, (int)(c * t.bn), K, 1);
     for (int j = 1; j < kNumTiles; ++j) {
       if (!kTiles[j].tail || kTiles[j].bn >= t.bn) continue;
-      const double us = head_us + layer_us(kTiles[j], rows, rest, K, 1);
+      const double us = (head_us + layer_us(kTiles[j], rows, rest, K, 1)) * LayerModel::kCut;
       if (us < best_us) {
         best_us = us;
         best = GemmPlan{i, 1, (int)(c * t.bn), j};
       }
+    }
+  }
+  if (rows > 128 && rows <= 256 && 2.0 * N * K < kStreamedBytes) {
+    const GemmPlan own = gemm_plan(rows, N, K);
+    const double us = layer_us(kTiles[own.tile], rows, N, K, own.splits);
+    if (own.tile != best.tile && best_us > LayerModel::kKeep * us && (own.splits == 1 || sizeof(float) * own.splits * rows * (size_t)N <= partial_bytes)) {
+      best_us = us;
+      best = own;
     }
   }
   if (us_out) *us_out = best_us;

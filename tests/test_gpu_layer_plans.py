@@ -26,9 +26,9 @@ def layer(gpu):
     return _layer(synth.OPT_13B, 4711)
 
 
-def _plan(ctx, rows):
+def _plan(ctx, rows, products=PRODUCTS):
     out = []
-    for k, n in PRODUCTS:
+    for k, n in products:
         p = ctx.ds_layer_plan(rows, k, n)
         out.append("stream" if p["streaming"] else f"{p['tile_rows']}x{p['tile_cols']}/{p['splits']}")
     return out
@@ -59,10 +59,10 @@ def _check(layer, x, y, k, v):
 @pytest.mark.parametrize("t,plan", [
     (70, ["96x192/3", "64x128/3", "stream", "96x192/9"]),
     (100, ["128x128/2", "64x128/3", "stream", "128x128/6"]),
-    (160, ["160x192/3", "192x128/5", "160x192/2", "160x192/9"]),      # rows end with the tile
-    (161, ["192x192/3", "192x128/5", "192x192/2", "192x192/9"]),      # one row more
-    (193, ["224x192/3", "256x128/5", "224x192/2", "224x192/9"]),
-    (230, ["128x128/1", "256x128/5", "256x160/2", "256x160/8"]),      # eight splits: they turn
+    (160, ["160x192/3", "128x128/3", "160x192/2", "160x192/9"]),      # rows end with the tile
+    (161, ["192x192/3", "128x128/3", "192x192/2", "192x192/9"]),      # one row more
+    (193, ["224x192/3", "128x128/3", "224x192/2", "224x192/9"]),
+    (230, ["128x128/1", "128x128/3", "256x160/2", "256x160/8"]),      # eight splits: they turn
     (287, ["288x192/3", "160x192/4", "288x192/2", "288x192/9"]),
     (289, ["320x192/3", "160x192/4", "160x192/1", "320x192/9"]),
     (383, ["192x128/1", "192x128/3", "192x192/1", "384x160/8"]),
@@ -71,6 +71,19 @@ def _check(layer, x, y, k, v):
 ])
 def test_prefill_on_the_tiles_of_its_plan(layer, t, plan):
     assert _plan(layer["ctx"], t) == plan
+    _check(layer, *_prefill(layer, t, gu.workspace(layer["ctx"].ds_prefill_workspace_bytes(t))))
+
+
+@pytest.mark.parametrize("h,ffn,t,product,plan", [
+    (1024, 16384, 583, 2, "384x128/1"), (1024, 16384, 1122, 3, "384x128/10"),      # tiles that no OPT-13B batch takes
+    (1536, 16384, 583, 2, "160x256/1"), (1024, 24576, 772, 3, "160x256/12"),
+    (4096, 32768, 114, 3, "128x256/15"),
+    (1024, 12288, 261, 3, "192x128/16"), (1024, 12288, 387, 3, "256x128/16"),
+])
+def test_prefill_on_the_tiles_of_other_layers(gpu, h, ffn, t, product, plan):
+    layer = _layer(synth.ModelShape(hidden=h, n_heads=h // 128, head_dim=128, ffn=ffn), 4713)
+    products = ((h, 3 * h), (h, h), (h, ffn), (ffn, h))
+    assert _plan(layer["ctx"], t, products)[product] == plan
     _check(layer, *_prefill(layer, t, gu.workspace(layer["ctx"].ds_prefill_workspace_bytes(t))))
 
 
@@ -140,12 +153,13 @@ def test_decode_step_scatters_k_and_v_from_unsplit_tiles(gpu, batch, tile):
     _kv_scatter_case(shape, batch)
 
 
-@pytest.mark.parametrize("heads,n_kv,batch", [(96, 0, 450), (96, 0, 512), (64, 8, 1800)])
-def test_decode_step_scatters_k_and_v_on_both_sides_of_a_cut(gpu, heads, n_kv, batch):
-    """QKV on 256x192 tiles in whole rounds, the remaining columns - of V, or of K and V - on other tiles."""
+@pytest.mark.parametrize("heads,n_kv,batch,tile", [(56, 0, 970, (256, 192)), (72, 8, 1810, (256, 192)),
+                                                   (16, 8, 4200, (256, 160)), (16, 0, 6000, (256, 160))])
+def test_decode_step_scatters_k_and_v_on_both_sides_of_a_cut(gpu, heads, n_kv, batch, tile):
+    """QKV on large tiles in whole rounds, the remaining columns - of V, or of K and V - on other tiles."""
     shape = synth.ModelShape(hidden=heads * 128, n_heads=heads, head_dim=128, ffn=512, n_kv_heads=n_kv)
     plan = gu.make_ctx(shape).ds_layer_plan(batch, shape.hidden, shape.qkv_width)
-    assert (plan["tile_rows"], plan["tile_cols"]) == (256, 192) and 0 < plan["cut_cols"] < shape.qkv_width
+    assert (plan["tile_rows"], plan["tile_cols"]) == tile and 0 < plan["cut_cols"] < shape.qkv_width
     _kv_scatter_case(shape, batch)
 
 

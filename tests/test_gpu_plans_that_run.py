@@ -54,7 +54,8 @@ def _step(shape, batch):
     (4, 64, 1024, 0, 2), (4, 64, 1024, 0, 8), (4, 64, 1024, 0, 64), (8, 128, 4096, 0, 33),    # small: unsplit in a layer
     (96, 128, 512, 0, 4), (96, 128, 512, 0, 64),                                              # a wide out-projection
     (40, 128, 5248, 0, 48),
-    (96, 128, 512, 0, 450), (96, 128, 512, 0, 512),                                           # QKV is cut at a column
+    (56, 128, 512, 0, 970), (72, 128, 512, 8, 1810), (16, 128, 512, 0, 6000),                 # QKV is cut at a column
+    (96, 128, 512, 0, 512),
 ])
 def test_what_is_reported_is_what_runs(gpu, heads, head_dim, ffn, n_kv, batch):
     shape = synth.ModelShape(hidden=heads * head_dim, n_heads=heads, head_dim=head_dim, ffn=ffn, n_kv_heads=n_kv)

@@ -87,3 +87,27 @@ def test_decode_workspace_says_what_the_static_array_takes(name, largest):
     assert least(largest) <= binding.STATIC_SCRATCH_BYTES < least(largest + 1)
     assert ctx.ds_decode_workspace_bytes(largest, 16) <= binding.STATIC_SCRATCH_BYTES
     assert ctx.ds_decode_workspace_bytes(largest + 1, 16) > binding.STATIC_SCRATCH_BYTES
+
+
+@pytest.mark.parametrize("name,product,rows,lost", [
+    # tile and splits of plans that were measured slower than what ds_linear runs, or than others of the layer's own
+    ("opt13b", 1, (129, 160, 161, 192), ((192, 128), 5)), ("opt13b", 1, (193, 208, 225, 256), ((256, 128), 5)),
+    ("gqa", 3, (88, 96, 128), ((128, 256), 8)), ("gqa", 3, (129, 160), ((160, 256), 8)), ("gqa", 3, (161, 192), ((192, 256), 8)),
+])
+def test_plans_that_measured_slower_are_not_taken(name, product, rows, lost):
+    ctx = _ctx(name)
+    for r in rows:
+        p = ctx.ds_layer_plan(r, *_products(name)[product])
+        assert ((p["tile_rows"], p["tile_cols"]), p["splits"]) != lost
+        if name == "opt13b":
+            assert p == ctx.ds_linear_plan(r, *_products(name)[product])
+
+
+def test_a_cut_is_taken_where_it_pays():
+    """A second launch costs more than the model's sum: 279 us cut, 269 not (OPT-66B out-projection, 2048 rows); 746 and 797
+    (its QKV)."""
+    ctx = _ctx("opt66b")
+    (k, qkv), out = _products("opt66b")[0], _products("opt66b")[1]
+    assert ctx.ds_layer_plan(2048, *out)["cut_cols"] == 0 < ctx.ds_layer_plan(2048, k, qkv)["cut_cols"]
+    for name in ("opt66b", "opt175b"):
+        assert _ctx(name).ds_layer_plan(512, *_products(name)[0])["cut_cols"] == 0
