@@ -67,8 +67,8 @@ inline unsigned long long* g_gemm_dbg = nullptr;
 // 16 x 16 output tiles, and inside it every XCD a block of 8 x 4: 16 + 16 operand tiles from HBM per 256 output
 // tiles, 8 + 4 through each L2 per 32.  (A strip of 16 x 2 per XCD - 16 + 2 through each L2 - cost 1-3 % at 16384
 // rows; with 8 row tiles the plain m-fastest order inside a chunk is the 8 x 4 block.)
-__device__ __forceinline__ void patch_tile(int pid, int tiles_m, int tiles_n, int& tm, int& tn) {
-  constexpr int kXcd = 8, kPerXcd = 32, kChunk = kXcd * kPerXcd, kGroupM = 16;
+constexpr int kXcd = 8, kPerXcd = 32, kChunk = kXcd * kPerXcd, kGroupM = 16;
+__host__ __device__ constexpr void patch_tile(int pid, int tiles_m, int tiles_n, int& tm, int& tn) {
   const int total = tiles_m * tiles_n;
   const int full = total / kChunk * kChunk;
   int v = pid;
@@ -84,11 +84,31 @@ __device__ __forceinline__ void patch_tile(int pid, int tiles_m, int tiles_n, in
   }
   const int per_group = kGroupM * tiles_n;
   const int g = v / per_group;
-  const int gsz = min(kGroupM, tiles_m - g * kGroupM);
+  const int left = tiles_m - g * kGroupM, gsz = left < kGroupM ? left : kGroupM;
   const int r = v - g * per_group;
   tm = g * kGroupM + r % gsz;
   tn = r / gsz;
 }
+
+// The XCD whose workgroup takes row tile 0 of column tile tn (fewer than kGroupM row tiles).
+__host__ __device__ constexpr int column_xcd(int tn, int tiles_m, int tiles_n) {
+  const int total = tiles_m * tiles_n, full = total / kChunk * kChunk, v = tn * tiles_m;
+  if (v < full) return v % kChunk / kPerXcd;
+  const int per = (total - full) / kXcd;
+  return v - full < per * kXcd ? (v - full) / per : (v - full) % kXcd;
+}
+constexpr bool column_xcd_follows_patch_tile(int tiles_m, int tiles_n) {
+  for (int pid = 0; pid < tiles_m * tiles_n; ++pid) {
+    int tm = 0, tn = 0;
+    patch_tile(pid, tiles_m, tiles_n, tm, tn);
+    if (tm == 0 && column_xcd(tn, tiles_m, tiles_n) != pid % kXcd) return false;
+  }
+  return true;
+}
+static_assert(column_xcd_follows_patch_tile(1, 5) && column_xcd_follows_patch_tile(1, 27) &&
+              column_xcd_follows_patch_tile(1, 260) && column_xcd_follows_patch_tile(2, 129) &&
+              column_xcd_follows_patch_tile(3, 171) && column_xcd_follows_patch_tile(7, 75) &&
+              column_xcd_follows_patch_tile(8, 64), "spread starts");
 
 // ---------------------------------------------------------------------------
 // Direct global->LDS loads (no register staging, no ds_write):
@@ -215,9 +235,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   // have at one position of K on few memory channels.  Where the row tiles of a column lie on two XCDs, all of them begin
   // where the first does: equal rows have equal sums, whatever their place in the batch.
   if (NT && p.spread) {
-    const int total = p.tiles_m * p.tiles_n, full = total & ~255, v = tile_n * min(p.tiles_m, 16);  // (patch_tile's numbers)
-    const int xcd = v < full ? (v & 255) >> 5 : (v - full) * 8 / (total - full);
-    xk.start((int)((((unsigned)xcd + gridDim.x * blockIdx.y) & 7) * (unsigned)KT / 8));
+    const unsigned xcd = column_xcd(tile_n, p.tiles_m, p.tiles_n) + gridDim.x * blockIdx.y;
+    xk.start((int)((xcd & 7) * (unsigned)KT / 8));
   }
   auto wk = xk;
 
