@@ -337,10 +337,7 @@ size_t full_ws(const ds_ctx* ctx, int rows, const ds_ctx::Least& least) {
   const int most = ((rows < kLayerMaxRows ? rows : kLayerMaxRows) + kStep - 1) / kStep * kStep;
   const size_t layer = ctx->layer_partials.at((most - kFirst) / kStep, [&](size_t i) {
     const int r = kFirst + kStep * (int)i;
-    return largest_product(ctx->cfg, [&](int in_f, int out_f) {
-      const ds::GemmPlan plan = ds::layer_plan(r, out_f, in_f, ~(size_t)0);
-      return plan.splits > 1 ? sizeof(float) * plan.splits * r * (size_t)out_f : 0;
-    });
+    return largest_product(ctx->cfg, [&](int in_f, int out_f) { return ds::layer_partial_bytes(r, out_f, in_f); });
   });
   return least.all - least.partials + std::max(least.partials, align_up(layer, 256));
 }

@@ -343,8 +343,27 @@ int gemm_splits(int M, int N, int K) {
 }
 
 // Bytes of split-K partials a launch with exactly M rows needs.
+// Splits stay within one round of 256 workgroups, so a product of more than 128 of the largest tiles has none; known without
+// a plan, which matters to whoever sizes a workspace for all row counts up to some thousand.
+static bool never_split(int M, int N) {
+  constexpr int kLargest = 256 * 256;
+  constexpr auto fits = [] {
+    for (const Tile& t : kTiles)
+      if (t.bm * t.bn > kLargest) return false;
+    return true;
+  };
+  static_assert(fits(), "tiles");
+  return M > 256 && (double)M * N > 128.0 * kLargest && g_gemm_variant == 0 && g_gemm_splits == 0;
+}
+
+size_t layer_partial_bytes(int M, int N, int K) {
+  if (never_split(M, N)) return 0;
+  const GemmPlan pl = layer_plan(M, N, K, ~(size_t)0);
+  return pl.splits > 1 ? (size_t)pl.splits * M * N * sizeof(float) : 0;
+}
+
 size_t gemm_workspace_bytes(int M, int N, int K) {
-  if (M <= 0 || N <= 0 || K < kBK || K % kBK != 0) return 0;
+  if (M <= 0 || N <= 0 || K < kBK || K % kBK != 0 || never_split(M, N)) return 0;
   const GemmPlan pl = gemm_plan(M, N, K);
   return pl.splits > 1 ? (size_t)pl.splits * M * N * sizeof(float) : 0;
 }

@@ -77,6 +77,7 @@ hipError_t launch_gemm(const void* X, const void* W, int M, int N, int K, const 
 // The same by a given plan.  layer_plan is the fastest the time model knows for a product of a layer whose partial sums
 // may take partial_bytes, with the time it expects.
 GemmPlan layer_plan(int M, int N, int K, size_t partial_bytes, double* us = nullptr);
+size_t layer_partial_bytes(int M, int N, int K);  // the partial sums of that plan where they may take any room
 void gemm_tile_shape(int tile, int* tile_rows, int* tile_cols);
 hipError_t launch_gemm(const void* X, const void* W, int M, int N, int K, const Epilogue& ep, GemmPlan plan,
                        hipStream_t stream, void* workspace, const SkinnyFused* fused, bool* fused_done);
