@@ -6,7 +6,7 @@
 // of the sequence's pages; wave w takes pages w, w+4, ... of that split.  In
 // a wave, s/8 lanes cover one token row (8 elements each), so one load
 // instruction covers 64/(s/8) tokens.  Scores are reduced across the lanes
-// of a token with xor-shuffles, softmax runs online in fp32, and the four
+// of a token (within_group), softmax runs online in fp32, and the four
 // waves' (max, sum, acc) states are merged through LDS.  With one split the
 // result is written as bf16; with several, fp32 partial states go to the
 // workspace and a second kernel merges them (fixed order: deterministic).
@@ -105,15 +105,12 @@ __global__ __launch_bounds__(kDecThreads) void decode_attention_kernel(
     float tmax = -INFINITY;
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
-      float d = dot8(qv, kr[j]);
-#pragma unroll
-      for (int off = 1; off < LPT; off <<= 1) d += __shfl_xor(d, off, 64);
+      const float d = within_group<LPT>(dot8(qv, kr[j]), AddOp());
       const int tok = pg * kDecPage + j * TPL + tg;
       sc[j] = (tok < kv_len) ? d : -INFINITY;
       tmax = fmaxf(tmax, sc[j]);
     }
-#pragma unroll
-    for (int off = LPT; off < 64; off <<= 1) tmax = fmaxf(tmax, __shfl_xor(tmax, off, 64));
+    tmax = across_groups<LPT>(tmax, MaxOp());
     // the first token of a visited page is always < kv_len, so tmax is finite
     const float m_new = fmaxf(m_run, tmax);
     const float alpha = exp2f((m_run - m_new) * scale_log2e);
@@ -144,12 +141,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_attention_kernel(
   }
 
   // merge the token groups of the wave: every lane of a group carries the same l_run
+  l_run = across_groups<LPT>(l_run, AddOp());
 #pragma unroll
-  for (int off = LPT; off < 64; off <<= 1) {
-    l_run += __shfl_xor(l_run, off, 64);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] += __shfl_xor(acc[j], off, 64);
-  }
+  for (int j = 0; j < 8; ++j) acc[j] = across_groups<LPT>(acc[j], AddOp());
   if (lane < LPT) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) sm_acc[wave][lane * 8 + j] = acc[j];
@@ -330,8 +324,7 @@ __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(2))
       sc[4 + r] = key0 + kDecPage + r < end1 ? s1[r] : -INFINITY;
       tmax = fmaxf(tmax, fmaxf(sc[r], sc[4 + r]));
     }
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+    tmax = across_groups<16>(tmax, MaxOp());
     // the first key of a visited pair is always < kv_len, so tmax is finite
     const float m_new = fmaxf(m_run, tmax);
     const float alpha = exp2f((m_run - m_new) * scale_log2e);
@@ -386,8 +379,7 @@ __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(2))
   }
 
   // the four lane groups' shares of the sum
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
+  l_run = across_groups<16>(l_run, AddOp());
   __syncthreads();  // every wave is done with its staging area: the merge area overlays it
   float* mg = reinterpret_cast<float*>(smem);  // [wave][head][max, sum, acc[HD]]
   {

@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kAttThreads) __attribute__((amdgpu_waves_per_eu(2))
       for (int u = 0; u < 2; ++u)
 #pragma unroll
         for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, sacc[u][r]);
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+      tmax = lane_op<32>(tmax, MaxOp());
       // The reference point m_run of the exponentials only has to keep them in range, so it is moved
       // (and the accumulators rescaled) only when some query's maximum grew by more than kSlack in
       // the exponent: probabilities then stay below 2^kSlack and the final quotient is unchanged.
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(kAttThreads) __attribute__((amdgpu_waves_per_eu(2))
     }
 
     // ---- normalise and store: lane holds O[my_q][32d + 8g + 4hl + i] ----
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    const float l_tot = lane_op<32>(l_run, AddOp());
     if (my_q < len) {
       const float inv = 1.f / l_tot;
       uint16_t* orow = o + ((size_t)start + my_q) * h + (size_t)head * HD + hl * 4;
