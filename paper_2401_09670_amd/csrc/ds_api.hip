@@ -231,13 +231,14 @@ bool use_skinny(int rows, int in_f) { return rows <= kStreamMaxRows && in_f % 12
 
 ds_status linear(ds_ctx* ctx, const void* x, const void* w, int rows, int in_f, int out_f,
                  const ds::Epilogue& ep, void* gemm_ws, hipStream_t stream,
-                 const ds::SkinnyFused* fused = nullptr, bool* fused_done = nullptr, bool weigh_reduce = false) {
+                 const ds::SkinnyFused* fused = nullptr, bool* fused_done = nullptr, bool weigh_reduce = false,
+                 const ds::InputNorm* norm = nullptr) {
   if (fused_done) *fused_done = false;
   hipError_t e;
   {
     Timed t(ctx, stream, rows <= kSkinnyMaxRows ? DS_K_SKINNY_GEMM : DS_K_GEMM);
     if (use_skinny(rows, in_f))
-      e = ds::launch_skinny_gemm(x, w, rows, out_f, in_f, ep, gemm_ws, stream, fused, fused_done, weigh_reduce);
+      e = ds::launch_skinny_gemm(x, w, rows, out_f, in_f, ep, gemm_ws, stream, fused, fused_done, weigh_reduce, norm);
     else
       e = ds::launch_gemm(x, w, rows, out_f, in_f, ep, stream, gemm_ws, fused, fused_done);
   }
@@ -264,10 +265,11 @@ int layer_splits(int rows, int in_f, int out_f, size_t ws_bytes) {
 
 ds_status layer_linear(ds_ctx* ctx, const void* x, const void* w, int rows, int in_f, int out_f,
                        const ds::Epilogue& ep, void* gemm_ws, size_t ws_bytes, hipStream_t stream,
-                       const ds::SkinnyFused* fused = nullptr, bool* fused_done = nullptr) {
+                       const ds::SkinnyFused* fused = nullptr, bool* fused_done = nullptr,
+                       const ds::InputNorm* norm = nullptr) {
   ds::GemmPlan plan;
   if (!layer_tiles(rows, in_f, out_f, ws_bytes, &plan))
-    return linear(ctx, x, w, rows, in_f, out_f, ep, gemm_ws, stream, fused, fused_done, true);
+    return linear(ctx, x, w, rows, in_f, out_f, ep, gemm_ws, stream, fused, fused_done, true, norm);
   hipError_t e;
   {
     Timed t(ctx, stream, rows <= kSkinnyMaxRows ? DS_K_SKINNY_GEMM : DS_K_GEMM);
@@ -294,6 +296,25 @@ ds_status linear_and_norm(ds_ctx* ctx, const void* x, const void* w, int rows, i
   DS_LAUNCH(ctx, stream, DS_K_LAYERNORM,
             ds::launch_layernorm(ep.out[0], gamma, beta, normed, rows, out_f, ctx->cfg.ln_eps, stream));
   return DS_OK;
+}
+
+// Whether such a product can take its rows as they are before a LayerNorm and normalise them itself (fewer than
+// kLayerMinRows of them, short ones): a launch less.
+bool norms_input(int rows, int in_f, int out_f) {
+  return use_skinny(rows, in_f) && ds::skinny_norms_input(rows, out_f, in_f);
+}
+
+// LN(x) W^T: in one launch where the product can, else by way of `normed`.
+ds_status norm_and_linear(ds_ctx* ctx, const void* x, const void* gamma, const void* beta, void* normed, const void* w,
+                          int rows, int in_f, int out_f, const ds::Epilogue& ep, void* gemm_ws, size_t ws_bytes,
+                          hipStream_t stream, const ds::LengthOrder& sort = {}, const ds::SkinnyFused* fused = nullptr,
+                          bool* fused_done = nullptr) {
+  const ds::InputNorm norm{gamma, beta, ctx->cfg.ln_eps};
+  if (sort.count == 0 && norms_input(rows, in_f, out_f))
+    return layer_linear(ctx, x, w, rows, in_f, out_f, ep, gemm_ws, ws_bytes, stream, fused, fused_done, &norm);
+  DS_LAUNCH(ctx, stream, DS_K_LAYERNORM,
+            ds::launch_layernorm(x, gamma, beta, normed, rows, in_f, norm.eps, stream, nullptr, sort));
+  return layer_linear(ctx, normed, w, rows, in_f, out_f, ep, gemm_ws, ws_bytes, stream, fused, fused_done);
 }
 
 // split-K partials of the kernel that `linear` picks for exactly `rows` rows
@@ -707,16 +728,14 @@ ds_status ds_prefill(ds_ctx* ctx, const ds_layer_weights* w, const void* x, cons
   void* sk = ws.take(0);
   const size_t sk_bytes = workspace_bytes - ws.off;
 
-  // a = LN1(x)
-  DS_LAUNCH(ctx, s, DS_K_LAYERNORM, ds::launch_layernorm(x, w->ln1_g, w->ln1_b, a, t, h, c.ln_eps, s));
-  // [q | k_out | v_out] = a W_qkv^T + b_qkv
+  // [q | k_out | v_out] = LN1(x) W_qkv^T + b_qkv
   {
     ds::Epilogue ep;
     ep.bias = w->b_qkv;
     ep.out[0] = q; ep.out[1] = k_out; ep.out[2] = v_out;
     ep.seg_cols = h;
     ep.seg_cols_kv = kv_width(c);
-    st = layer_linear(ctx, a, w->w_qkv, t, h, qkv_width(c), ep, sk, sk_bytes, s);
+    st = norm_and_linear(ctx, x, w->ln1_g, w->ln1_b, a, w->w_qkv, t, h, qkv_width(c), ep, sk, sk_bytes, s);
     if (st != DS_OK) return st;
   }
   // o = causal attention per request
@@ -724,11 +743,13 @@ ds_status ds_prefill(ds_ctx* ctx, const ds_layer_weights* w, const void* x, cons
             ds::launch_prefill_attention(q, k_out, v_out, cu_seqlens, B, t, max_seqlen, c.n_heads, c.n_kv_heads,
                                          c.head_dim, o, s));
   // x1 = x + o W_o^T + b_o, f = LN2(x1) (reuses a)
+  const bool fc1_norms = norms_input(t, h, m);
   {
     ds::Epilogue ep;
     ep.bias = w->b_o; ep.residual = x;
     ep.out[0] = x1; ep.seg_cols = h;
-    st = linear_and_norm(ctx, o, w->w_o, t, h, h, ep, sk, sk_bytes, w->ln2_g, w->ln2_b, a, s);
+    st = fc1_norms ? layer_linear(ctx, o, w->w_o, t, h, h, ep, sk, sk_bytes, s)
+                   : linear_and_norm(ctx, o, w->w_o, t, h, h, ep, sk, sk_bytes, w->ln2_g, w->ln2_b, a, s);
     if (st != DS_OK) return st;
   }
   // The FFN intermediate is written by one tile GEMM and read by the next: give its rows 128 bytes of
@@ -743,7 +764,8 @@ ds_status ds_prefill(ds_ctx* ctx, const ds_layer_weights* w, const void* x, cons
     ep.bias = w->b_fc1; ep.relu = 1;
     ep.out[0] = u; ep.seg_cols = m;
     if (pad_u) ep.out_ld = ld_u;
-    st = layer_linear(ctx, a, w->w_fc1, t, h, m, ep, sk, sk_bytes, s);
+    st = fc1_norms ? norm_and_linear(ctx, x1, w->ln2_g, w->ln2_b, a, w->w_fc1, t, h, m, ep, sk, sk_bytes, s)
+                   : layer_linear(ctx, a, w->w_fc1, t, h, m, ep, sk, sk_bytes, s);
     if (st != DS_OK) return st;
   }
   // y = x1 + u W_2^T + b_2
@@ -881,11 +903,9 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
   ds::LengthOrder by_length;
   if (ds::decode_attention_wants_order(B, c.n_heads, c.n_kv_heads, c.head_dim, max_ctx))
     by_length = ds::LengthOrder{ctx_lens, static_cast<int32_t*>(x1), B};
-  DS_LAUNCH(ctx, s, DS_K_LAYERNORM,
-            ds::launch_layernorm(x, w->ln1_g, w->ln1_b, a, B, h, c.ln_eps, s, nullptr, by_length));
   const uint16_t* qkv16 = static_cast<const uint16_t*>(qkv);
   {
-    // [q | k | v] = a W_qkv^T + b_qkv; the split-K reduction writes k, v straight into the cache
+    // [q | k | v] = LN1(x) W_qkv^T + b_qkv; the split-K reduction writes k, v straight into the cache
     ds::Epilogue ep;
     ep.bias = w->b_qkv;
     ep.out[0] = qkv; ep.seg_cols = wqkv;
@@ -895,7 +915,8 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
     fu.k_cache = k_cache; fu.v_cache = v_cache;
     fu.n_heads = c.n_heads; fu.n_kv_heads = c.n_kv_heads; fu.head_dim = c.head_dim;
     bool appended = false;
-    st = layer_linear(ctx, a, w->w_qkv, B, h, wqkv, ep, sk, sk_bytes, s, &fu, &appended);
+    st = norm_and_linear(ctx, x, w->ln1_g, w->ln1_b, a, w->w_qkv, B, h, wqkv, ep, sk, sk_bytes, s, by_length, &fu,
+                         &appended);
     if (st != DS_OK) return st;
     if (!appended)
       DS_LAUNCH(ctx, s, DS_K_KV_APPEND,
@@ -906,19 +927,22 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
             ds::launch_decode_attention(qkv, wqkv, ctx_lens, 1, block_tables, B, max_blocks_per_seq, max_ctx,
                                         k_cache, v_cache, c.n_heads, c.n_kv_heads, c.head_dim, o, att, s,
                                         by_length.order));
+  const bool fc1_norms = norms_input(B, h, m);
   {
     // x1 = x + o W_o^T + b_o, f = LN2(x1)
     ds::Epilogue ep;
     ep.bias = w->b_o; ep.residual = x;
     ep.out[0] = x1; ep.seg_cols = h;
-    st = linear_and_norm(ctx, o, w->w_o, B, h, h, ep, sk, sk_bytes, w->ln2_g, w->ln2_b, a, s);
+    st = fc1_norms ? layer_linear(ctx, o, w->w_o, B, h, h, ep, sk, sk_bytes, s)
+                   : linear_and_norm(ctx, o, w->w_o, B, h, h, ep, sk, sk_bytes, w->ln2_g, w->ln2_b, a, s);
     if (st != DS_OK) return st;
   }
   {
     ds::Epilogue ep;
     ep.bias = w->b_fc1; ep.relu = 1;
     ep.out[0] = u; ep.seg_cols = m;
-    st = layer_linear(ctx, a, w->w_fc1, B, h, m, ep, sk, sk_bytes, s);
+    st = fc1_norms ? norm_and_linear(ctx, x1, w->ln2_g, w->ln2_b, a, w->w_fc1, B, h, m, ep, sk, sk_bytes, s)
+                   : layer_linear(ctx, a, w->w_fc1, B, h, m, ep, sk, sk_bytes, s);
     if (st != DS_OK) return st;
   }
   {

@@ -4,10 +4,11 @@
 // (App. A.3: 4h^2 + 2hm elements per layer), so the kernels are organised
 // around streaming W at HBM rate while the matrix cores do the M x ... work.
 //
-// Two streaming kernels live here, plus the second passes of split-K:
+// Two streaming kernels live here, one for products too short to stream, and the second passes of split-K:
 //   * wring_gemm_kernel  - wave-private rings, no split of K over workgroups, no second launch;
 //     taken for M <= 64 when N alone yields enough workgroups (described at the kernel).
 //   * skinny_gemm_kernel - one ring per workgroup, K split over workgroups; everything else.
+//   * short_wring_gemm_kernel - a layer's products of up to 8.5 MB of weights, optionally with the LayerNorm before it.
 //   * skinny_reduce*_kernel - add the split partials in a fixed order and apply the epilogue,
 //     optionally fused with the LayerNorm that follows or with the append to the paged KV cache;
 //     also used by the tile GEMM when it splits K.
@@ -67,6 +68,10 @@ struct SkinnyParams {
   uint16_t* kv_k_cache = nullptr;
   uint16_t* kv_v_cache = nullptr;
   int kv_n_heads = 0, kv_n_kv_heads = 0, kv_head_dim = 0;
+  // short_wring_gemm_kernel<.., true> only: the rows of X are normalised first.
+  const uint16_t* norm_gamma = nullptr;
+  const uint16_t* norm_beta = nullptr;
+  float norm_eps = 0.f;
 };
 
 template <int VM>
@@ -94,6 +99,29 @@ __device__ __forceinline__ void store4(const SkinnyParams& p, int m, int n, u32x
   const int ld = seg == 0 ? p.seg_cols : p.seg_cols_kv;
   const int first = seg == 0 ? 0 : p.seg_cols + (seg - 1) * p.seg_cols_kv;
   *reinterpret_cast<u32x2*>(p.out[seg] + (size_t)m * ld + (n - first)) = v;
+}
+
+// Four finished sums of an unsplit launch: bias, ReLU, residual, out.
+__device__ __forceinline__ void store_epilogue(const SkinnyParams& p, int m, int n, floatx4 v) {
+  float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
+  if (p.bias) {
+    const u32x2 bb = *reinterpret_cast<const u32x2*>(p.bias + n);
+    v0 += bf16_lo(bb[0]); v1 += bf16_hi(bb[0]);
+    v2 += bf16_lo(bb[1]); v3 += bf16_hi(bb[1]);
+  }
+  if (p.relu) {
+    v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f);
+    v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f);
+  }
+  if (p.residual) {
+    const u32x2 rr = *reinterpret_cast<const u32x2*>(p.residual + (size_t)m * p.N + n);
+    v0 += bf16_lo(rr[0]); v1 += bf16_hi(rr[0]);
+    v2 += bf16_lo(rr[1]); v3 += bf16_hi(rr[1]);
+  }
+  u32x2 ov;
+  ov[0] = pack_bf16(v0, v1);
+  ov[1] = pack_bf16(v2, v3);
+  store4(p, m, n, ov);
 }
 
 // Waits until at most `slabs` (0 .. MOST) slabs of G loads are in flight.
@@ -340,25 +368,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
         *reinterpret_cast<floatx4*>(p.partial + ((size_t)split * p.M + m) * p.N + n) = acc[a][t];
         continue;
       }
-      float v0 = acc[a][t][0], v1 = acc[a][t][1], v2 = acc[a][t][2], v3 = acc[a][t][3];
-      if (p.bias) {
-        const u32x2 bb = *reinterpret_cast<const u32x2*>(p.bias + n);
-        v0 += bf16_lo(bb[0]); v1 += bf16_hi(bb[0]);
-        v2 += bf16_lo(bb[1]); v3 += bf16_hi(bb[1]);
-      }
-      if (p.relu) {
-        v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f);
-        v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f);
-      }
-      if (p.residual) {
-        const u32x2 rr = *reinterpret_cast<const u32x2*>(p.residual + (size_t)m * p.N + n);
-        v0 += bf16_lo(rr[0]); v1 += bf16_hi(rr[0]);
-        v2 += bf16_lo(rr[1]); v3 += bf16_hi(rr[1]);
-      }
-      u32x2 ov;
-      ov[0] = pack_bf16(v0, v1);
-      ov[1] = pack_bf16(v2, v3);
-      store4(p, m, n, ov);
+      store_epilogue(p, m, n, acc[a][t]);
     }
   }
 }
@@ -485,27 +495,136 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
       floatx4 v = red[((0 * NT + a) * MT + t) * 64 + lane];
 #pragma unroll
       for (int w2 = 1; w2 < NW; ++w2) v += red[((w2 * NT + a) * MT + t) * 64 + lane];
-      float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
-      if (p.bias) {
-        const u32x2 bb = *reinterpret_cast<const u32x2*>(p.bias + n);
-        v0 += bf16_lo(bb[0]); v1 += bf16_hi(bb[0]);
-        v2 += bf16_lo(bb[1]); v3 += bf16_hi(bb[1]);
-      }
-      if (p.relu) {
-        v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f);
-        v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f);
-      }
-      if (p.residual) {
-        const u32x2 rr = *reinterpret_cast<const u32x2*>(p.residual + (size_t)m * p.N + n);
-        v0 += bf16_lo(rr[0]); v1 += bf16_hi(rr[0]);
-        v2 += bf16_lo(rr[1]); v3 += bf16_hi(rr[1]);
-      }
-      u32x2 ov;
-      ov[0] = pack_bf16(v0, v1);
-      ov[1] = pack_bf16(v2, v3);
-      store4(p, m, n, ov);
+      store_epilogue(p, m, n, v);
     }
   }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Short products (up to 64 rows, up to some MB of weights: layers of 256 to 1024 features).  Such a launch is
+// its own start, one memory latency and its end; what made it longer were the bytes of a workgroup (64 columns and 64
+// rows of X, most of them copies, through a single compute unit) and a ring that takes them one barrier after another.
+// So the waves split K among themselves as above, but a workgroup owns 16 columns and there is no ring: a lane asks for
+// all pieces of its wave's share at once, straight into the registers that the matrix instructions read.
+//
+// With LN the rows of X are normalised on the way (norm_gamma, norm_beta): every workgroup computes the rows' mean and
+// variance for itself, as layernorm_kernel does for rows of up to 512 elements, sum by sum in the same order, and
+// each lane normalises the pieces it multiplies, so the bits are those of a launch of its own.
+//
+// C = slabs of 64 a wave asks for at once; K is a multiple of that many for every wave, or C = 1.
+// ---------------------------------------------------------------------------------------------
+constexpr int kShortWaves = 4;
+constexpr int kShortNormK = 512;  // one 16-byte piece of a row per lane
+
+template <int NT, int MT, int C, bool LN>
+__global__ __launch_bounds__(64 * kShortWaves) void short_wring_gemm_kernel(const SkinnyParams p) {
+  static_assert(NT == 1, "16 columns a workgroup");
+  constexpr int NW = kShortWaves, BM = 16 * MT, ROWS = LN ? BM / NW : 1;
+  __shared__ floatx4 red[NW][MT][64];
+  __shared__ float mean_s[BM], rstd_s[BM];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, q = lane >> 4;  // row of a fragment, its quarter of 32 k
+  const int n0 = blockIdx.x * 16, K = p.K, slabs = K / kWrKS;
+  const uint16_t* wrow = p.W + (size_t)min(n0 + r, p.N - 1) * K + 8 * q;
+  const uint16_t* xrow[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) xrow[t] = p.X + (size_t)min(16 * t + r, p.M - 1) * K + 8 * q;
+
+  // whole rows for their statistics: wave w has rows w, w + NW, ...
+  u32x4 raw[ROWS];
+  if constexpr (LN) {
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i)
+      raw[i] = ld16(p.X + (size_t)min(wave + NW * i, p.M - 1) * K + min(lane, K / 8 - 1) * 8);
+  }
+  floatx4 acc[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  float mean[MT], rstd[MT];
+  for (int s0 = wave; s0 < slabs; s0 += NW * C) {
+    u32x4 wf[C][2], xf[C][2][MT], gf[C][2], bf[C][2];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int k0 = (s0 + NW * c) * kWrKS;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        wf[c][h] = ld16(wrow + k0 + 32 * h);
+#pragma unroll
+        for (int t = 0; t < MT; ++t) xf[c][h][t] = ld16(xrow[t] + k0 + 32 * h);
+        if constexpr (LN) {
+          gf[c][h] = ld16(p.norm_gamma + k0 + 32 * h + 8 * q);
+          bf[c][h] = ld16(p.norm_beta + k0 + 32 * h + 8 * q);
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);  // all of them on their way before the first is waited for
+    if constexpr (LN) {
+      if (s0 == wave) {  // statistics first; every wave comes here once (slabs >= NW)
+        const bool live = lane < K / 8;
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+          float v[8], sum = 0.f, sq = 0.f;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            v[2 * j] = bf16_lo(raw[i][j]);
+            v[2 * j + 1] = bf16_hi(raw[i][j]);
+            sum += live ? v[2 * j] + v[2 * j + 1] : 0.f;
+          }
+          const float mu = wave_sum(sum) / (float)K;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const float d = v[j] - mu;
+            sq += live ? d * d : 0.f;
+          }
+          const float rs = rsqrtf(wave_sum(sq) / (float)K + p.norm_eps);
+          if (lane == 0) {
+            mean_s[wave + NW * i] = mu;
+            rstd_s[wave + NW * i] = rs;
+          }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+          mean[t] = mean_s[16 * t + r];
+          rstd[t] = rstd_s[16 * t + r];
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int t = 0; t < MT; ++t) {
+            u32x4& x = xf[c][h][t];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              x[j] = pack_bf16((bf16_lo(x[j]) - mean[t]) * rstd[t] * bf16_lo(gf[c][h][j]) + bf16_lo(bf[c][h][j]),
+                               (bf16_hi(x[j]) - mean[t]) * rstd[t] * bf16_hi(gf[c][h][j]) + bf16_hi(bf[c][h][j]));
+          }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf[c][h]),
+                                                           __builtin_bit_cast(bf16x8, xf[c][h][t]), acc[t], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < MT; ++t) red[wave][t][lane] = acc[t];
+  __syncthreads();
+  // wave w finishes row tile w: the waves' parts are added in wave order
+  const int n = n0 + q * 4;
+  if (wave >= MT || n >= p.N) return;
+  const int m = 16 * wave + r;
+  if (m >= p.M) return;
+  floatx4 v = red[0][wave][lane];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) v += red[w][wave][lane];
+  store_epilogue(p, m, n, v);
 }
 
 // Sum of the split partials of 8 consecutive columns of row m, added in split order.  The reduce passes are bound by
@@ -819,6 +938,50 @@ static hipError_t launch_wring(int nt, const SkinnyParams& p, hipStream_t stream
   return launch_wring_cfg<4, 8, 2, 3>(p, stream);                 // 144 KB
 }
 
+template <int MT, int C>
+static hipError_t launch_short_cfg(const SkinnyParams& p, hipStream_t stream) {
+  const dim3 grid((p.N + 15) / 16), block(64 * kShortWaves);
+  if constexpr (MT == 1 && C * kShortWaves * kWrKS <= kShortNormK)
+    if (p.norm_gamma) {
+      hipLaunchKernelGGL((short_wring_gemm_kernel<1, MT, C, true>), grid, block, 0, stream, p);
+      return hipGetLastError();
+    }
+  hipLaunchKernelGGL((short_wring_gemm_kernel<1, MT, C, false>), grid, block, 0, stream, p);
+  return hipGetLastError();
+}
+template <int MT>
+static hipError_t launch_short_rows(const SkinnyParams& p, hipStream_t stream) {
+  constexpr int kAll = kShortWaves * kWrKS;
+  if (p.K % (4 * kAll) == 0) return launch_short_cfg<MT, 4>(p, stream);
+  if (p.K % (2 * kAll) == 0) return launch_short_cfg<MT, 2>(p, stream);
+  return launch_short_cfg<MT, 1>(p, stream);
+}
+static hipError_t launch_short(const SkinnyParams& p, hipStream_t stream) {
+  if (p.M <= 16) return launch_short_rows<1>(p, stream);
+  if (p.M <= 32) return launch_short_rows<2>(p, stream);
+  return launch_short_rows<4>(p, stream);
+}
+
+// Whether a product of a layer is short: up to 1024 of K, so that a lane holds its whole share, and 8.5 MB of weights.  A
+// decoding step (us, of a graph of 24) by the former kernels, with short products, with those that normalise too:
+//   256 x 1024 features, 1 row 24.7, 18.6, 16.5; 16 rows 25.3, 20.4, 17.9; 64 rows 31.1, 26.6, -
+//   512 x 2048            1 row 29.3, 22.6, 21.2; 16 rows 30.9, 25.6, 23.0; 64 rows 38.6, 33.2, -
+//   1024 x 4096           1 row 32.8, 28.8, -;    64 rows 48.8, 47.1, -
+// 1024 x 8192 (17 MB): 1 row 32.2 without it, 32.4 with; 64 rows 52.4 and 53.7.  K = 2048 -> 512 features: 1 row 24.1
+// and 22.0, 64 rows 48.3 and 51.3; K = 4096 -> 1024: 29.8 and 30.1, 47.6 and 58.1.  (One line for all row counts, so that a
+// row's bits do not depend on them.)
+// Rows are normalised up to 16 of them: at 32 it is a draw (22.7 and 21.9, 27.5 and 27.3), at 48 25.2 us without and 28.8
+// with, since every workgroup computes all rows' statistics.
+DS_SWITCH(g_skinny_short_k, 1024);   // longest K
+DS_SWITCH(g_skinny_short_kb, 8500);  // most weights (KB)
+constexpr int kShortNormRows = 16;
+static bool short_product(int M, int N, int K) {
+  return M <= 64 && K >= kShortWaves * kWrKS && K % kWrKS == 0 && K <= g_skinny_short_k && 2e-3 * N * K <= g_skinny_short_kb;
+}
+bool skinny_norms_input(int M, int N, int K) {
+  return M <= kShortNormRows && K <= kShortNormK && short_product(M, N, K);
+}
+
 // Column-tile width (in 16-row tiles) for the wave-private-ring kernel, or 0 if the shape is not one it
 // is good at: K a multiple of 256 and enough column tiles to occupy most of the chip without splitting K.
 // Up to 64 rows it takes both widths; for 65..128 rows only the 80-column one, where a workgroup re-reads 1.6
@@ -944,13 +1107,15 @@ hipError_t launch_splitk_reduce(const float* partial, int splits, int M, int N, 
   return hipGetLastError();
 }
 
-// Which kernel takes a product: the one with wave-private rings (wring: 16-row tiles of W a workgroup, unsplit), or, with
-// wring = 0, the ring kernel by `plan`.  own_epilogue: no LayerNorm wants a reduce pass to ride in.
+// Which kernel takes a product: the one with wave-private rings (wring: 16-row tiles of W a workgroup, unsplit; 1: the
+// one for short products), or, with wring = 0, the ring kernel by `plan`.  own_epilogue: no LayerNorm wants a reduce pass
+// to ride in.
 struct SkinnyRoute {
   int wring;
   SkinnyPlan plan;
 };
 static SkinnyRoute skinny_route(int M, int N, int K, bool own_epilogue, bool weigh_reduce) {
+  if (weigh_reduce && short_product(M, N, K)) return SkinnyRoute{1, {1, 1}};
   SkinnyRoute r{own_epilogue ? wring_tiles(M, N, K) : 0, {1, 1}};
   if (r.wring > 0) return r;
   double split;
@@ -982,7 +1147,7 @@ double skinny_us(int M, int N, int K) {
 
 hipError_t launch_skinny_gemm(const void* X, const void* W, int M, int N, int K, const Epilogue& ep,
                               void* workspace, hipStream_t stream, const SkinnyFused* fused, bool* fused_done,
-                              bool weigh_reduce) {
+                              bool weigh_reduce, const InputNorm* norm) {
   if (fused_done) *fused_done = false;
   if (M <= 0 || N <= 0) return hipSuccess;
   if (M > 256 || K % kSkPlanK != 0 || N % 8 != 0 || ep.seg_cols <= 0 || ep.seg_cols % 8 != 0 || ep.seg_cols_kv < 0 ||
@@ -1013,8 +1178,15 @@ hipError_t launch_skinny_gemm(const void* X, const void* W, int M, int N, int K,
     p.kv_n_heads = fused->n_heads; p.kv_n_kv_heads = fused->n_kv_heads; p.kv_head_dim = fused->head_dim;
     if (fused_done) *fused_done = true;
   }
+  if (norm) {
+    if (!weigh_reduce || !skinny_norms_input(M, N, K)) return hipErrorInvalidValue;
+    p.norm_gamma = (const uint16_t*)norm->gamma;
+    p.norm_beta = (const uint16_t*)norm->beta;
+    p.norm_eps = norm->eps;
+  }
   if (route.wring > 0) {
     p.partial = nullptr;
+    if (route.wring == 1) return launch_short(p, stream);
     return launch_wring(route.wring, p, stream);
   }
   p.partial = (float*)workspace;

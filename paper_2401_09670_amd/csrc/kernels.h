@@ -108,16 +108,23 @@ hipError_t launch_splitk_reduce(const float* partial, int splits, int M, int N, 
 // `*fused_done` tells whether the requested fused work was carried out (LayerNorm needs the split-K
 // reduction pass); if not, the caller launches the separate kernel.  With `weigh_reduce` a product stays unsplit where
 // that takes no longer than splitting and the reduce pass together (24e6 of the plans' bytes, 2 us, for a small one): one
-// launch less for the host (2 rows of 1024 -> 256), 3072 x 1024 at 64 rows 3 us.
+// launch less (3072 x 2048), and a short one goes to the kernel for those.
 size_t skinny_workspace_bytes(int M, int N, int K);
 double skinny_us(int M, int N, int K);  // time launch_skinny_gemm takes for 65 to 128 rows, to be held against layer_plan's
 // What launch_skinny_gemm does: columns per workgroup and splits over K (1 split and 64 or 80 columns = the unsplit kernel
 // with wave-private rings, or the ring kernel unsplit).  own_epilogue = false: with a LayerNorm in its reduce pass.
 void skinny_describe(int M, int N, int K, int* tile_cols, int* splits, bool own_epilogue = true,
                      bool weigh_reduce = false);
+// With `norm` (only where skinny_norms_input says so, and with weigh_reduce) X is LayerNorm'd on the way in.
+struct InputNorm {
+  const void* gamma;
+  const void* beta;
+  float eps;
+};
+bool skinny_norms_input(int M, int N, int K);
 hipError_t launch_skinny_gemm(const void* X, const void* W, int M, int N, int K, const Epilogue& ep,
                               void* workspace, hipStream_t stream, const SkinnyFused* fused = nullptr,
-                              bool* fused_done = nullptr, bool weigh_reduce = false);
+                              bool* fused_done = nullptr, bool weigh_reduce = false, const InputNorm* norm = nullptr);
 
 // Greedy token choice over logits = X[M,K] W[N,K]^T (M <= 256, fp32 accumulation, never written out):
 // the weight-streaming kernel keeps, per row and column block, the largest logit and its column; a
