@@ -104,6 +104,29 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ u32x4 ld16(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
 __device__ __forceinline__ void st16(void* p, u32x4 v) { *reinterpret_cast<u32x4*>(p) = v; }
 
+// The output segments (Q | K | V) of a product: buffers, row strides and first columns, as sums of what each of a lane's
+// two comparisons adds.  Indexed by the lane's segment, or selected, the pointers would come from the argument block in
+// memory (that is what the compiler makes of either): one load per store, and a store that waits for a load waits for
+// the store before it too.
+typedef __attribute__((address_space(1))) uint16_t gmem_u16;
+struct OutSegments {
+  uint64_t base, to_k, to_v;  // address of column 0 as Q has it; what K and then V add
+  int ld, to_kv, c1, c2;
+  __device__ __forceinline__ gmem_u16* at(int row, int n) const {
+    const int kv = n >= c1 ? -1 : 0, v = n >= c2 ? -1 : 0;
+    const uint64_t o = base + (to_k & (uint64_t)(int64_t)kv) + (to_v & (uint64_t)(int64_t)v);
+    return (gmem_u16*)(o + 2 * ((uint64_t)row * (uint32_t)(ld + (to_kv & kv)) + n));
+  }
+};
+template <class P>
+__device__ __forceinline__ OutSegments out_segments(const P& p, int ld_first) {
+  const int c1 = p.seg_cols, c2 = c1 + p.seg_cols_kv;
+  const uint64_t q = (uint64_t)p.out[0], k = (uint64_t)p.out[1] - 2 * (uint64_t)c1, v = (uint64_t)p.out[2] - 2 * (uint64_t)c2;
+  return OutSegments{q, k - q, v - k, ld_first, p.seg_cols_kv - ld_first, c1, c2};
+}
+__device__ __forceinline__ void st16(gmem_u16* p, u32x4 v) { *(__attribute__((address_space(1))) u32x4*)p = v; }
+__device__ __forceinline__ void st8(gmem_u16* p, u32x2 v) { *(__attribute__((address_space(1))) u32x2*)p = v; }
+
 // Workgroup barrier that closes this wave's LDS reads and leaves its direct-to-LDS loads in flight (behind
 // __syncthreads() the compiler may wait for all of them).
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }

@@ -465,6 +465,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   __syncthreads();                 // every wave has finished reading the k-loop buffers
   DS_STAMP(2);
   float* stg = reinterpret_cast<float*>(lds) + wave * (WTM * RSTR);
+  const OutSegments out = out_segments(p, p.ld_out);
 #pragma unroll
   for (int pass = 0; pass < NPASS; ++pass) {
     const int a0 = pass * GA;
@@ -525,10 +526,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
           const int blk = p.block_tables[(size_t)row * p.max_blocks + pos / 16];
           st16((which ? p.v_cache : p.k_cache) + (((size_t)blk * p.n_kv_heads + head) * 16 + (pos % 16)) * p.head_dim + d, o);
         } else {
-          const int seg = (n >= p.seg_cols) + (n >= p.seg_cols + p.seg_cols_kv);
-          const int ld = seg == 0 ? p.ld_out : p.seg_cols_kv;
-          const int first = seg == 0 ? 0 : p.seg_cols + (seg - 1) * p.seg_cols_kv;
-          st16(p.out[seg] + (size_t)row * ld + (n - first), o);
+          st16(out.at(row, n), o);
         }
       }
     }

@@ -80,49 +80,69 @@ __device__ __forceinline__ void sk_wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((VM & 0xf) | (0x7 << 4) | (0xf << 8) | ((VM >> 4) << 14));
 }
 
-// Four finished outputs of row m, columns n .. n+3: into their output segment, or, in a decode QKV projection, this
-// step's K / V row straight into its page.
-__device__ __forceinline__ void store4(const SkinnyParams& p, int m, int n, u32x2 v) {
-  const int hq = p.kv_n_heads * p.kv_head_dim, hkv = p.kv_n_kv_heads * p.kv_head_dim;
-  if (p.kv_k_cache && n >= hq) {
-    const int which = n >= hq + hkv;
-    const int col = n - hq - which * hkv;
-    const int head = col / p.kv_head_dim, d = col - head * p.kv_head_dim;
-    const int pos = p.kv_ctx_lens[m];
-    const int blk = p.kv_block_tables[(size_t)m * p.kv_max_blocks + pos / 16];
-    uint16_t* dst = (which ? p.kv_v_cache : p.kv_k_cache) +
-                    (((size_t)blk * p.kv_n_kv_heads + head) * 16 + (pos % 16)) * p.kv_head_dim + d;
-    *reinterpret_cast<u32x2*>(dst) = v;
-    return;
+// Epilogue of the unsplit kernels, four columns n .. n+3 of a row at a time: bias, ReLU, residual, then into their output
+// segment, or, in a decode QKV projection, this step's K / V row straight into its page.  Everything it reads is asked for
+// while the product runs (Epilogue4): a load between two stores makes the second wait for the first to arrive, four to
+// eight round trips in a row (prefill of 57 OPT-13B tokens 156.8 -> 154.7 us, a step at 64 rows 262.3 -> 261.2).  A wave
+// finishes C column tiles of MT row tiles.
+template <int C, int MT>
+struct Epilogue4 {
+  u32x2 bias[C], res[C][MT];
+  int pos[MT], block[MT];  // slot of each row's sequence, and its page
+  int first = 0;           // row of the first row tile
+  // First column of tile c: col(c).  Rows and columns past the end are read inside the output, an absent operand from the
+  // weights and not used: a branch around a load ends in a wait for all that are in flight.
+  template <class Col>
+  __device__ __forceinline__ void request(const SkinnyParams& p, int lane, Col&& col) {
+    const uint16_t* bias_at = p.bias ? p.bias : p.W;
+    const uint16_t* res_at = p.residual ? p.residual : p.W;
+    const int ld_res = p.residual ? p.N : 0;
+    const int32_t* pos_at = p.kv_k_cache ? p.kv_ctx_lens : reinterpret_cast<const int32_t*>(p.W);
+    const int seqs = p.kv_k_cache ? ~0 : 0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int n = min(col(c) + (lane >> 4) * 4, p.N - 4);
+      bias[c] = *reinterpret_cast<const u32x2*>(bias_at + n);
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+        res[c][t] = *reinterpret_cast<const u32x2*>(res_at + (size_t)row(p, lane, t) * ld_res + n);
+    }
+#pragma unroll
+    for (int t = 0; t < MT; ++t) pos[t] = pos_at[row(p, lane, t) & seqs];
   }
-  const int seg = (n >= p.seg_cols) + (n >= p.seg_cols + p.seg_cols_kv);
-  const int ld = seg == 0 ? p.seg_cols : p.seg_cols_kv;
-  const int first = seg == 0 ? 0 : p.seg_cols + (seg - 1) * p.seg_cols_kv;
-  *reinterpret_cast<u32x2*>(p.out[seg] + (size_t)m * ld + (n - first)) = v;
-}
-
-// Four finished sums of an unsplit launch: bias, ReLU, residual, out.
-__device__ __forceinline__ void store_epilogue(const SkinnyParams& p, int m, int n, floatx4 v) {
-  float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
-  if (p.bias) {
-    const u32x2 bb = *reinterpret_cast<const u32x2*>(p.bias + n);
-    v0 += bf16_lo(bb[0]); v1 += bf16_hi(bb[0]);
-    v2 += bf16_lo(bb[1]); v3 += bf16_hi(bb[1]);
+  __device__ __forceinline__ void pages(const SkinnyParams& p, int lane) {
+    const int32_t* at = p.kv_k_cache ? p.kv_block_tables : reinterpret_cast<const int32_t*>(p.W);
+    const size_t seqs = p.kv_k_cache ? ~(size_t)0 : 0;
+#pragma unroll
+    for (int t = 0; t < MT; ++t) block[t] = at[((size_t)row(p, lane, t) * p.kv_max_blocks + (pos[t] >> 4)) & seqs];
   }
-  if (p.relu) {
-    v0 = fmaxf(v0, 0.f); v1 = fmaxf(v1, 0.f);
-    v2 = fmaxf(v2, 0.f); v3 = fmaxf(v3, 0.f);
+  __device__ __forceinline__ int row(const SkinnyParams& p, int lane, int t) const {
+    return min(first + 16 * t + (lane & 15), p.M - 1);
   }
-  if (p.residual) {
-    const u32x2 rr = *reinterpret_cast<const u32x2*>(p.residual + (size_t)m * p.N + n);
-    v0 += bf16_lo(rr[0]); v1 += bf16_hi(rr[0]);
-    v2 += bf16_lo(rr[1]); v3 += bf16_hi(rr[1]);
+  __device__ __forceinline__ void store(const SkinnyParams& p, const OutSegments& out, int c, int t, int m, int n,
+                                        const floatx4& v) const {
+    float r[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      r[j] = v[j];
+      if (p.bias) r[j] += j & 1 ? bf16_hi(bias[c][j / 2]) : bf16_lo(bias[c][j / 2]);
+      if (p.relu) r[j] = fmaxf(r[j], 0.f);
+      if (p.residual) r[j] += j & 1 ? bf16_hi(res[c][t][j / 2]) : bf16_lo(res[c][t][j / 2]);
+    }
+    const u32x2 o{pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3])};
+    const int hq = p.kv_n_heads * p.kv_head_dim, hkv = p.kv_n_kv_heads * p.kv_head_dim;
+    if (p.kv_k_cache && n >= hq) {
+      const int which = n >= hq + hkv;
+      const int col = n - hq - which * hkv, shift = __builtin_ctz(p.kv_head_dim);  // 64 or 128
+      const int head = col >> shift, d = col - (head << shift);
+      const uint64_t k = (uint64_t)p.kv_k_cache, to_v = (uint64_t)p.kv_v_cache - k;
+      st8((gmem_u16*)(k + (to_v & (uint64_t)(int64_t)-which) +
+                      2 * ((((uint64_t)block[t] * p.kv_n_kv_heads + head) * 16 + (pos[t] & 15)) * p.kv_head_dim + d)), o);
+      return;
+    }
+    st8(out.at(m, n), o);
   }
-  u32x2 ov;
-  ov[0] = pack_bf16(v0, v1);
-  ov[1] = pack_bf16(v2, v3);
-  store4(p, m, n, ov);
-}
+};
 
 // Waits until at most `slabs` (0 .. MOST) slabs of G loads are in flight.
 template <int MOST, int G>
@@ -280,6 +300,11 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
     multiply(st);
     st = (st + 1 == S) ? 0 : st + 1;
   }
+  Epilogue4<NTW, MT> epi;
+  if (n_splits == 1 && !p.amax_val && kh == 0) {  // (before the loop these loads held up the split launches, 1 %)
+    epi.request(p, lane, [&](int a) { return n0 + (ng * NTW + a) * 16; });
+    epi.pages(p, lane);
+  }
   sk_wait_vmcnt<0>();  // no global->LDS write of this workgroup may still be in flight ...
   __syncthreads();     // ... and nobody reads the stages any more: reuse them to add the two k-halves
   {
@@ -356,6 +381,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
     }
     return;
   }
+  const OutSegments out = out_segments(p, p.seg_cols);
 #pragma unroll
   for (int a = 0; a < NTW; ++a) {
     const int n = n0 + (ng * NTW + a) * 16 + (lane >> 4) * 4;
@@ -368,7 +394,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
         *reinterpret_cast<floatx4*>(p.partial + ((size_t)split * p.M + m) * p.N + n) = acc[a][t];
         continue;
       }
-      store_epilogue(p, m, n, acc[a][t]);
+      epi.store(p, out, a, t, m, n, acc[a][t]);
     }
   }
 }
@@ -448,6 +474,9 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
   for (int s2 = 0; s2 < 2; ++s2)
     fo[s2] = (lane & 15) * kWrKS + (((4 * s2 + (lane >> 4)) ^ (((lane & 15) >> 1) & 7)) * 8);
 
+  constexpr int MINE = (NT + NW - 1) / NW;  // weight row tiles a wave finishes
+  Epilogue4<MINE, MT> epi;
+  epi.request(p, lane, [&](int i) { return n0 + 16 * (wave + i * NW); });
 #pragma unroll
   for (int i = 0; i < S - 1; ++i) request(i, i);
   int st = 0, st_in = S - 1;  // stage read in this iteration; stage the newest request goes into
@@ -472,6 +501,7 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
     st = st + 1 == S ? 0 : st + 1;
     st_in = st_in + 1 == S ? 0 : st_in + 1;
   }
+  epi.pages(p, lane);
   sk_wait_vmcnt<0>();  // the clamped re-load of the last iteration must not land in the reduction area
   __syncthreads();     // every wave is done with its ring: reuse the LDS to add the four waves' tiles
   {
@@ -485,9 +515,12 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
   // wave w finishes weight row tiles a = w (and w + 4): the four waves' tiles are added in wave order.
   // Lane: row m = 16t + lane%16, columns n = n0 + 16a + 4*(lane/16) + 0..3.
   const floatx4* red = reinterpret_cast<const floatx4*>(lds);
-  for (int a = wave; a < NT; a += NW) {
+  const OutSegments out = out_segments(p, p.seg_cols);
+#pragma unroll
+  for (int i = 0; i < MINE; ++i) {
+    const int a = wave + i * NW;
     const int n = n0 + 16 * a + (lane >> 4) * 4;
-    if (n >= p.N) continue;
+    if (a >= NT || n >= p.N) continue;
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
       const int m = t * 16 + (lane & 15);
@@ -495,7 +528,7 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
       floatx4 v = red[((0 * NT + a) * MT + t) * 64 + lane];
 #pragma unroll
       for (int w2 = 1; w2 < NW; ++w2) v += red[((w2 * NT + a) * MT + t) * 64 + lane];
-      store_epilogue(p, m, n, v);
+      epi.store(p, out, i, t, m, n, v);
     }
   }
 }
@@ -538,6 +571,8 @@ __global__ __launch_bounds__(64 * kShortWaves) void short_wring_gemm_kernel(cons
     for (int i = 0; i < ROWS; ++i)
       raw[i] = ld16(p.X + (size_t)min(wave + NW * i, p.M - 1) * K + min(lane, K / 8 - 1) * 8);
   }
+  Epilogue4<1, 1> epi;  // wave w finishes row tile w
+  epi.first = 16 * min(wave, MT - 1);
   floatx4 acc[MT];
 #pragma unroll
   for (int t = 0; t < MT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -558,6 +593,7 @@ __global__ __launch_bounds__(64 * kShortWaves) void short_wring_gemm_kernel(cons
         }
       }
     }
+    if (s0 == wave) epi.request(p, lane, [&](int) { return n0; });
     __builtin_amdgcn_sched_barrier(0);  // all of them on their way before the first is waited for
     if constexpr (LN) {
       if (s0 == wave) {  // statistics first; every wave comes here once (slabs >= NW)
@@ -613,18 +649,19 @@ __global__ __launch_bounds__(64 * kShortWaves) void short_wring_gemm_kernel(cons
                                                            __builtin_bit_cast(bf16x8, xf[c][h][t]), acc[t], 0, 0, 0);
     }
   }
+  epi.pages(p, lane);
+  // the waves' parts are added in wave order
+  const int n = n0 + q * 4;
 #pragma unroll
   for (int t = 0; t < MT; ++t) red[wave][t][lane] = acc[t];
   __syncthreads();
-  // wave w finishes row tile w: the waves' parts are added in wave order
-  const int n = n0 + q * 4;
   if (wave >= MT || n >= p.N) return;
   const int m = 16 * wave + r;
   if (m >= p.M) return;
   floatx4 v = red[0][wave][lane];
 #pragma unroll
   for (int w = 1; w < NW; ++w) v += red[w][wave][lane];
-  store_epilogue(p, m, n, v);
+  epi.store(p, out_segments(p, p.seg_cols), 0, 0, m, n, v);
 }
 
 // Sum of the split partials of 8 consecutive columns of row m, added in split order.  The reduce passes are bound by
@@ -705,13 +742,10 @@ __global__ __launch_bounds__(256) void skinny_reduce_kernel(const SkinnyParams p
   float v[8];
   sum_partials8(p, n_splits, m, n, v);
   epi_apply(p, e, v);
-  const int seg = (n >= p.seg_cols) + (n >= p.seg_cols + p.seg_cols_kv);
-  const int ld = seg == 0 ? p.seg_cols : p.seg_cols_kv;
-  const int first = seg == 0 ? 0 : p.seg_cols + (seg - 1) * p.seg_cols_kv;
   u32x4 ov;
 #pragma unroll
   for (int j = 0; j < 4; ++j) ov[j] = pack_bf16(v[2 * j], v[2 * j + 1]);
-  st16(p.out[seg] + (size_t)m * ld + (n - first), ov);
+  st16(out_segments(p, p.seg_cols).at(m, n), ov);
 }
 
 // The same reduction, one workgroup per output row, followed by LayerNorm of that row: writes

@@ -107,8 +107,8 @@ hipError_t launch_splitk_reduce(const float* partial, int splits, int M, int N, 
 // Same contraction for M <= 256 (decode): weights are streamed once from HBM.
 // `*fused_done` tells whether the requested fused work was carried out (LayerNorm needs the split-K
 // reduction pass); if not, the caller launches the separate kernel.  With `weigh_reduce` a product stays unsplit where
-// that takes no longer than splitting and the reduce pass together (24e6 of the plans' bytes, 2 us, for a small one): one
-// launch less (3072 x 2048), and a short one goes to the kernel for those.
+// that takes no longer than splitting and the reduce pass together (24e6 of the plans' bytes, 2 us, for a small one): a
+// launch less, and a short one goes to the kernel for those.
 size_t skinny_workspace_bytes(int M, int N, int K);
 double skinny_us(int M, int N, int K);  // time launch_skinny_gemm takes for 65 to 128 rows, to be held against layer_plan's
 // What launch_skinny_gemm does: columns per workgroup and splits over K (1 split and 64 or 80 columns = the unsplit kernel
