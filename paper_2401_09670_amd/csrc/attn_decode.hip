@@ -10,6 +10,8 @@
 // waves' (max, sum, acc) states are merged through LDS.  With one split the
 // result is written as bf16; with several, fp32 partial states go to the
 // workspace and a second kernel merges them (fixed order: deterministic).
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -180,21 +182,48 @@ __global__ __launch_bounds__(kDecThreads) void decode_attention_kernel(
   }
 }
 
+// What bounds it is latency: the states of eight splits are asked for together, not one after another.  With the kernel
+// before it, 8 key/value heads, one sequence of 2048 tokens on 16 splits 18.9 -> 11.6 us, 4 sequences 20.8 -> 15.3; 40
+// heads, one of 2048 15.6 -> 14.2.
+constexpr int kCombined = 8;
 template <int HD>
 __global__ __launch_bounds__(HD) void decode_combine_kernel(const float* __restrict__ partial, int n_splits,
                                                             float scale_log2e, uint16_t* __restrict__ o) {
+  constexpr int U = kCombined;
   const size_t item = blockIdx.x;  // seq * n_heads + head
   const float* src = partial + item * n_splits * (HD + 2);
   const int tid = threadIdx.x;
+  float ms[U], ls[U], as[U];
+  auto load = [&](int s0) {  // (past the last split: the last again, not used)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float* state = src + (size_t)min(s0 + u, n_splits - 1) * (HD + 2);
+      ms[u] = state[0];
+      ls[u] = state[1];
+      as[u] = state[2 + tid];
+    }
+  };
+  load(0);
   float m = -INFINITY;
-  for (int s = 0; s < n_splits; ++s) m = fmaxf(m, src[s * (HD + 2)]);
+#pragma unroll
+  for (int u = 0; u < U; ++u) m = fmaxf(m, ms[u]);
+  for (int s0 = U; s0 < n_splits; s0 += U) {
+    float more[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) more[u] = src[(size_t)min(s0 + u, n_splits - 1) * (HD + 2)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) m = fmaxf(m, more[u]);
+  }
   float l = 0.f, a = 0.f;
-  for (int s = 0; s < n_splits; ++s) {
-    const float ms = src[s * (HD + 2)];
-    if (ms > -INFINITY) {
-      const float f = exp2f((ms - m) * scale_log2e);
-      l += src[s * (HD + 2) + 1] * f;
-      a += src[s * (HD + 2) + 2 + tid] * f;
+  for (int s0 = 0; s0 < n_splits; s0 += U) {
+    if (s0 > 0) load(s0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (s0 + u < n_splits && ms[u] > -INFINITY) {
+        const float f = exp2f((ms[u] - m) * scale_log2e);
+        l += ls[u] * f;
+        a += as[u] * f;
+      }
     }
   }
   reinterpret_cast<__bf16*>(o)[item * HD + tid] = (__bf16)(l > 0.f ? a / l : 0.f);  // no key at all (kv_len = 0): defined as 0
@@ -439,16 +468,22 @@ static bool gqa_kernel_serves(int n_heads, int n_kv_heads, int head_dim) {
   return head_dim == kGqaHD && G >= 2 && G <= 16;
 }
 
-// Enough workgroups to cover the chip about twice, but never less than 8 pages per split.  A workgroup
-// serves one (sequence, head), or one (sequence, key/value head) in the grouped-query kernel.
+// Splits of the KV axis where (sequence, head) pairs - (sequence, key/value head) in the grouped-query kernel - are too few
+// to cover the chip: 768 workgroups, three per compute unit; in the grouped-query kernel, of which two fit a compute unit,
+// one round of 512 as long as a workgroup has little to do (fewer than 128 pairs).  512 and 768 (us): 40 heads, 8 sequences
+// of 2048 58.2 and 55.7, 6 of 1024 to 4096 54.1 and 48.7; 96 heads, 2 of 2048 38.8 and 34.7 (the other way: 40 heads, 4 of
+// 2048 31.1 and 32.2); 8 key/value heads, 32 of 1024 to 4096 78 and 71, 16 ragged ones 20.3 and 16.1, but 8 of 2048 18.5
+// and 22.6.  (1024: 12 sequences of 40 heads 99.9 -> 93.6, 4 of 96 heads 84.6 -> 87.6.)  No split has fewer than 8 pages, and
+// more than 8 splits, which the combining launch takes in one go, are made only of 16 pages and more: 8 key/value heads, 2
+// sequences up to 3400 tokens 18.3 -> 14.6, one of 2048 with 40 heads 14.2 -> 12.5.
 int decode_attention_splits(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len) {
   const int pages = (max_kv_len + kDecPage - 1) / kDecPage;
-  const long items = (long)B * (gqa_kernel_serves(n_heads, n_kv_heads, head_dim) ? n_kv_heads : n_heads);
-  int splits = (int)((2 * 256 + items - 1) / items);
-  const int max_splits = (pages + 2 * kDecWaves - 1) / (2 * kDecWaves);
-  if (splits > max_splits) splits = max_splits;
-  if (splits < 1) splits = 1;
-  return splits;
+  const bool grouped = gqa_kernel_serves(n_heads, n_kv_heads, head_dim);
+  const long items = (long)B * (grouped ? n_kv_heads : n_heads);
+  if (items >= 512) return 1;
+  const int wanted = (int)(((grouped && items < 128 ? 512 : 768) + items - 1) / items);
+  const int most = std::max(std::min((pages + 7) / 8, kCombined), pages / 16);
+  return std::max(1, std::min(wanted, most));
 }
 
 // The order in which sequences start matters where workgroups queue for a place (two per compute unit): a long sequence
