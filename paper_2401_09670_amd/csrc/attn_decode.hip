@@ -2,7 +2,8 @@
 // HBM-bound: the kernel's job is to stream each (page, head) run of K and V
 // (16 tokens x s elements, contiguous) exactly once with 16-byte loads.
 //
-// grid = (heads, sequences, splits).  A workgroup of 4 waves takes one split
+// grid = (heads, sequences, splits); sizes of the grid are arguments here and elsewhere (a kernel that asks for gridDim
+// is given 256 bytes of arguments more, half a microsecond of the host's for each launch).  A workgroup of 4 waves takes one split
 // of the sequence's pages; wave w takes pages w, w+4, ... of that split.  In
 // a wave, s/8 lanes cover one token row (8 elements each), so one load
 // instruction covers 64/(s/8) tokens.  Scores are reduced across the lanes
@@ -45,8 +46,8 @@ template <int HD>
 __global__ __launch_bounds__(kDecThreads) void decode_attention_kernel(
     const uint16_t* __restrict__ q, int q_stride, const int32_t* __restrict__ kv_lens, int kv_len_add,
     const int32_t* __restrict__ block_tables, int max_blocks, const uint16_t* __restrict__ k_cache,
-    const uint16_t* __restrict__ v_cache, int n_heads, int n_kv_heads, int pages_per_split, float scale_log2e,
-    uint16_t* __restrict__ o, float* __restrict__ partial, const int32_t* __restrict__ order) {
+    const uint16_t* __restrict__ v_cache, int n_heads, int n_kv_heads, int pages_per_split, int n_splits,
+    float scale_log2e, uint16_t* __restrict__ o, float* __restrict__ partial, const int32_t* __restrict__ order) {
   constexpr int LPT = HD / 8;          // lanes per token row
   constexpr int TPL = 64 / LPT;        // tokens per load instruction
   constexpr int NL = kDecPage / TPL;   // load instructions per page
@@ -60,7 +61,6 @@ __global__ __launch_bounds__(kDecThreads) void decode_attention_kernel(
   const int kv_head = blockIdx.x % n_kv_heads;
   const int head = kv_head * kv_group + blockIdx.x / n_kv_heads;
   const int seq = order ? order[blockIdx.y] : blockIdx.y, split = blockIdx.z;
-  const int n_splits = gridDim.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tg = lane / LPT, dc = lane % LPT;
 
@@ -255,8 +255,8 @@ constexpr int kGqaVRow = kGqaHD + 8;  // LDS row of a staged V page in elements:
 __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(2))) void decode_attention_gqa_kernel(
     const uint16_t* __restrict__ q, int q_stride, const int32_t* __restrict__ kv_lens, int kv_len_add,
     const int32_t* __restrict__ block_tables, int max_blocks, const uint16_t* __restrict__ k_cache,
-    const uint16_t* __restrict__ v_cache, int n_heads, int n_kv_heads, int pages_per_split, float scale_log2e,
-    uint16_t* __restrict__ o, float* __restrict__ partial, const int32_t* __restrict__ order) {
+    const uint16_t* __restrict__ v_cache, int n_heads, int n_kv_heads, int pages_per_split, int n_splits,
+    float scale_log2e, uint16_t* __restrict__ o, float* __restrict__ partial, const int32_t* __restrict__ order) {
   constexpr int HD = kGqaHD;
   constexpr int kStage = 2 * kDecPage * kGqaVRow;            // elements of one wave's V staging area
   constexpr int kMergeFloats = kDecWaves * 16 * (HD + 2);    // [wave][head][max, sum, acc[HD]]
@@ -265,7 +265,6 @@ __global__ __launch_bounds__(kDecThreads) __attribute__((amdgpu_waves_per_eu(2))
 
   const int G = n_heads / n_kv_heads;  // 2..16 query heads share this key/value head
   const int kv_head = blockIdx.x, seq = order ? order[blockIdx.y] : blockIdx.y, split = blockIdx.z;
-  const int n_splits = gridDim.z;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hl = lane & 15, g = lane >> 4;  // head (or key, or d) index inside a tile; lane group
@@ -518,7 +517,7 @@ hipError_t launch_decode_attention(const void* q, int q_stride, const int32_t* k
   if (gqa_kernel_serves(n_heads, n_kv_heads, head_dim)) {
     hipLaunchKernelGGL(decode_attention_gqa_kernel, dim3(n_kv_heads, B, splits), dim3(kDecThreads), 0, stream,
                        (const uint16_t*)q, q_stride, kv_lens, kv_len_add, block_tables, max_blocks,
-                       (const uint16_t*)k_cache, (const uint16_t*)v_cache, n_heads, n_kv_heads, pps, scale_log2e,
+                       (const uint16_t*)k_cache, (const uint16_t*)v_cache, n_heads, n_kv_heads, pps, splits, scale_log2e,
                        (uint16_t*)o, (float*)workspace, order);
     if (splits > 1)
       hipLaunchKernelGGL(decode_combine_kernel<128>, dim3(B * n_heads), dim3(128), 0, stream,
@@ -526,14 +525,14 @@ hipError_t launch_decode_attention(const void* q, int q_stride, const int32_t* k
   } else if (head_dim == 128) {
     hipLaunchKernelGGL(decode_attention_kernel<128>, grid, dim3(kDecThreads), 0, stream, (const uint16_t*)q,
                        q_stride, kv_lens, kv_len_add, block_tables, max_blocks, (const uint16_t*)k_cache,
-                       (const uint16_t*)v_cache, n_heads, n_kv_heads, pps, scale_log2e, (uint16_t*)o, (float*)workspace, order);
+                       (const uint16_t*)v_cache, n_heads, n_kv_heads, pps, splits, scale_log2e, (uint16_t*)o, (float*)workspace, order);
     if (splits > 1)
       hipLaunchKernelGGL(decode_combine_kernel<128>, dim3(B * n_heads), dim3(128), 0, stream,
                          (const float*)workspace, splits, scale_log2e, (uint16_t*)o);
   } else if (head_dim == 64) {
     hipLaunchKernelGGL(decode_attention_kernel<64>, grid, dim3(kDecThreads), 0, stream, (const uint16_t*)q,
                        q_stride, kv_lens, kv_len_add, block_tables, max_blocks, (const uint16_t*)k_cache,
-                       (const uint16_t*)v_cache, n_heads, n_kv_heads, pps, scale_log2e, (uint16_t*)o, (float*)workspace, order);
+                       (const uint16_t*)v_cache, n_heads, n_kv_heads, pps, splits, scale_log2e, (uint16_t*)o, (float*)workspace, order);
     if (splits > 1)
       hipLaunchKernelGGL(decode_combine_kernel<64>, dim3(B * n_heads), dim3(64), 0, stream,
                          (const float*)workspace, splits, scale_log2e, (uint16_t*)o);

@@ -53,6 +53,7 @@ static hipError_t launch_tile(int tile, GemmParams p, int splits, bool in_layer,
   const Tile& t = kTiles[tile];
   p.tiles_m = (p.M + t.bm - 1) / t.bm;
   p.tiles_n = (p.N - p.n_base + t.bn - 1) / t.bn;
+  p.splits = splits;
   p.spread = p.K % 2048 == 0;
   if (g_gemm_spread >= 0) p.spread = g_gemm_spread;
   bool nt = p.tiles_m <= kFewRowTiles && 2.0 * p.N * p.K >= (in_layer ? kStreamedBytes : kCachedBytes);
@@ -403,6 +404,7 @@ hipError_t launch_gemm(const void* X, const void* W, int M, int N, int K, const 
   p.M = M; p.N = N; p.K = K;
   p.relu = ep.relu;
   p.tiles_m = p.tiles_n = 0;
+  p.splits = 1;
   p.partial = nullptr;
   p.ctx_lens = nullptr; p.block_tables = nullptr; p.max_blocks = 0;
   p.k_cache = nullptr; p.v_cache = nullptr; p.n_heads = 0; p.n_kv_heads = 0; p.head_dim = 0;

@@ -33,7 +33,8 @@ struct GemmParams {
   int ld_res;  // row stride of residual
   int n_base;  // first output column of this launch (a launch may cover the columns [n_base, N) only)
   int spread;  // workgroups start at different places of K
-  // Split-K (gridDim.y = S > 1): split s multiplies k-tiles s, s + S, ... and stores its fp32
+  int splits;
+  // Split-K (splits = gridDim.y = S > 1): split s multiplies k-tiles s, s + S, ... and stores its fp32
   // accumulators to partial[s][M][N]; the epilogue then belongs to whoever adds the partials.
   float* partial;
   // Decode QKV projection (N = (n_heads + 2 n_kv_heads) head_dim): with k_cache set, the K and V parts of
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   const int n0 = p.n_base + tile_n * BN;
   const int K = p.K;
   auto walk = [&] {
-    if constexpr (EPI == kEpiPartial) return KSplitWalk(K / kBK, blockIdx.y, gridDim.y);
+    if constexpr (EPI == kEpiPartial) return KSplitWalk(K / kBK, blockIdx.y, p.splits);
     else return KWalk<NT>(K / kBK);
   };
   auto xk = walk();
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_dl_kernel(const G
   // have at one position of K on few memory channels.  Where the row tiles of a column lie on two XCDs, all of them begin
   // where the first does: equal rows have equal sums, whatever their place in the batch.
   if (NT && p.spread) {
-    const unsigned xcd = column_xcd(tile_n, p.tiles_m, p.tiles_n) + gridDim.x * blockIdx.y;
+    const unsigned xcd = column_xcd(tile_n, p.tiles_m, p.tiles_n) + p.tiles_m * p.tiles_n * blockIdx.y;
     xk.start((int)((xcd & 7) * (unsigned)KT / 8));
   }
   auto wk = xk;

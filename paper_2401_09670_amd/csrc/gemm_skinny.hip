@@ -55,9 +55,10 @@ struct SkinnyParams {
   int seg_cols, seg_cols_kv;  // widths of the first and of the other two output segments
   int M, N, K;
   int relu;
-  float* partial;  // [KSPLIT][M][N] fp32 when gridDim.y > 1
+  int splits = 1;  // gridDim.y
+  float* partial;  // [KSPLIT][M][N] fp32 when splits > 1
   // Greedy-choice mode (unsplit launches only): nothing is written to `out`; per row the largest
-  // accumulator of this workgroup's columns and its column go to amax_val / amax_idx [gridDim.x][M].
+  // accumulator of this workgroup's columns and its column go to amax_val / amax_idx [column block][M].
   float* amax_val = nullptr;
   int32_t* amax_idx = nullptr;
   // Unsplit launches only: with kv_k_cache set (decode QKV projection, N = (n + 2 n_kv) s) the K and V
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
   const int ng = wave & 3, kh = wave >> 2;  // column group, k half
   const int n0 = blockIdx.x * BN;
   const int split = blockIdx.y;
-  const int n_splits = gridDim.y;
+  const int n_splits = p.splits;
   // The K axis is dealt to the splits slab by slab: split s takes number s of every group of n_splits slabs.  With a
   // multiple of 4 splits it takes number (s + i) % n_splits of group i instead, or it would meet only every fourth
   // 128-byte piece of a row, a fraction of the memory channels (8192 x 32768, 48 rows, 8 splits: 118 -> 93 us; other
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
   const int K = p.K;
   // Greedy choice: one order for all column blocks, so that equal vocabulary rows get equal logits, bit for bit, and the
   // tie goes to the lowest id.
-  const int rot = p.amax_val ? 0 : start_slab(blockIdx.x + gridDim.x * split, ns, n_splits * kSkKS, MP, K);
+  const int rot = p.amax_val ? 0 : start_slab(blockIdx.x + (p.N + BN - 1) / BN * split, ns, n_splits * kSkKS, MP, K);
 
   // load j of this wave is row group g = j*8 + wave of the stage (8 rows): X rows first, then W rows
   const int lr = lane >> 3;
@@ -935,7 +936,8 @@ size_t skinny_workspace_bytes(int M, int N, int K) {
 }
 
 template <int MT, int NTW, int S>
-static hipError_t launch_skinny_cfg(const SkinnyParams& p, int splits, hipStream_t stream) {
+static hipError_t launch_skinny_cfg(SkinnyParams p, int splits, hipStream_t stream) {
+  p.splits = splits;
   constexpr int BN = 64 * NTW;
   constexpr size_t lds_bytes = (size_t)S * (MT * 16 + BN) * kSkKS * sizeof(uint16_t);
   static_assert(lds_bytes <= 160 * 1024, "LDS");

@@ -39,9 +39,9 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_kernel(const uint16_t* _
                                                                const uint16_t* __restrict__ beta,
                                                                uint16_t* __restrict__ out, int h, float eps,
                                                                const int32_t* __restrict__ row_index,
-                                                               const LengthOrder sort) {
+                                                               const LengthOrder sort, int rows) {
   __shared__ float red[4];
-  if (sort.count > 0 && blockIdx.x == gridDim.x - 1) {
+  if (blockIdx.x == rows) {  // (the workgroup beside the rows': one is there if an order is wanted)
     sort_lengths(sort);
     return;
   }
@@ -110,7 +110,7 @@ hipError_t launch_layernorm(const void* x, const void* gamma, const void* beta, 
   const int nch = ((h >> 3) + kLnThreads - 1) / kLnThreads;
 #define DS_LN_LAUNCH(N)                                                                                   \
   hipLaunchKernelGGL(layernorm_kernel<N>, dim3(rows + (sort.count > 0 ? 1 : 0)), dim3(kLnThreads), 0, stream, (const uint16_t*)x, \
-                     (const uint16_t*)gamma, (const uint16_t*)beta, (uint16_t*)out, h, eps, row_index, sort)
+                     (const uint16_t*)gamma, (const uint16_t*)beta, (uint16_t*)out, h, eps, row_index, sort, rows)
   if (nch <= 1) DS_LN_LAUNCH(1);
   else if (nch == 2) DS_LN_LAUNCH(2);
   else if (nch == 3) DS_LN_LAUNCH(3);
