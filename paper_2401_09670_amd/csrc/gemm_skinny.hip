@@ -30,6 +30,8 @@
 // as MFMA row operand), so a lane ends up with 4 consecutive output columns
 // of one row.  With KSPLIT > 1 each split writes fp32 partial sums and a
 // second kernel adds them in a fixed order and applies the epilogue.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -173,8 +175,9 @@ __device__ __forceinline__ int start_slab(unsigned id, int ns, int slab_stride, 
   return (int)(((id & 7) * (unsigned)ns / 8 + ((id >> 3) & 31) * (unsigned)window / 32) % (unsigned)ns);
 }
 
-// MT = activation row tiles of 16 (4, 8, 16); NTW = column tiles per wave (1, 2, 4: BN = 64 * NTW);
-// S = LDS stages (prefetch distance D = S - 1).
+// MT = activation row tiles of 16 (1, 2, 4, 8, 16); NTW = most column tiles of a wave (1 to 4); S = LDS stages (prefetch
+// distance D = S - 1); NT = column tiles of the workgroup: 4 * NTW, or for the greedy choice also 10, 13 and 14, dealt
+// out in turn to the four column groups of waves.
 //
 // Stage layout: [MP rows of X | BN rows of W], every row 64 k-elements = 128 B = 8 chunks of
 // 16 B, unpadded; chunk c of row r sits at position c ^ ((r >> 1) & 7), so the 16 consecutive rows a
@@ -189,16 +192,17 @@ __device__ __forceinline__ int start_slab(unsigned id, int ns, int slab_stride, 
 // pass included, from 128-element slabs: 5120 x 5120 at 1 row 18.3 -> 14.0 us, at 64 rows 21.0 -> 19.5; 5120 x 20480 at
 // 1 row 47.7 -> 39.5, at 64 rows 53.8 -> 46.4; 32768 x 8192 at 48 rows 128 -> 89 (6.0 TB/s of weights); 12288 x 49152 at
 // 128 rows 301 -> 296.
-template <int MT, int NTW, int S>
+template <int MT, int NTW, int S, int NT = 4 * NTW>
 __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyParams p) {
-  constexpr int MP = MT * 16;   // padded activation rows held in LDS
-  constexpr int BN = 64 * NTW;  // weight rows per workgroup
+  constexpr int MP = MT * 16;  // padded activation rows held in LDS
+  constexpr int BN = 16 * NT;  // weight rows per workgroup
   constexpr int D = S - 1;      // slabs in flight ahead of the one being multiplied
   constexpr int STAGE_ELEMS = (MP + BN) * kSkKS;
   constexpr int GROUPS = (MP + BN) / 8;  // wave-level loads (8 rows each) per slab
-  static_assert(GROUPS % kSkWaves == 0 && MP % (8 * kSkWaves) == 0, "every wave issues the same number of loads");
-  constexpr int G = GROUPS / kSkWaves;  // loads per wave per slab
-  static_assert(D >= 1 && (D - 1) * G < 64, "vmcnt range");
+  constexpr int XGROUPS = MP / 8, MORE = GROUPS % kSkWaves;  // the first MORE waves issue one load more than the others
+  static_assert(XGROUPS % kSkWaves == 0 || XGROUPS < kSkWaves, "X rows: whole loads of all waves, or of some");
+  static_assert(D >= 1 && (D - 1) * ((GROUPS + kSkWaves - 1) / kSkWaves) < 64, "vmcnt range");
+  static_assert(NT <= 4 * NTW && NT > 4 * (NTW - 1), "column tiles of four groups of waves");
   extern __shared__ __attribute__((aligned(1024))) uint16_t lds[];  // [S][MP + BN][64]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -223,37 +227,9 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
   const int K = p.K;
   // Greedy choice: one order for all column blocks, so that equal vocabulary rows get equal logits, bit for bit, and the
   // tie goes to the lowest id.
-  const int rot = p.amax_val ? 0 : start_slab(blockIdx.x + (p.N + BN - 1) / BN * split, ns, n_splits * kSkKS, MP, K);
-
-  // load j of this wave is row group g = j*8 + wave of the stage (8 rows): X rows first, then W rows
-  const int lr = lane >> 3;
-  const uint16_t* src[G];
-#pragma unroll
-  for (int j = 0; j < G; ++j) {
-    const int r = 8 * (j * kSkWaves + wave) + lr;  // stage row
-    const int sw = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
-    if (r < MP) src[j] = p.X + (size_t)min(r, p.M - 1) * K + sw;
-    else src[j] = p.W + (size_t)min(n0 + r - MP, p.N - 1) * K + sw;
-  }
-  // requests the next slab of this split into stage `st`
-  int group = rot, turn = turn_by && rot ? (split + rot) % n_splits : split;
-  auto request = [&](int st) {
-    const int ofs = (group * n_splits + turn) * kSkKS;
-    turn = turn + turn_by == n_splits ? 0 : turn + turn_by;
-    if (++group == ns) group = 0, turn = split;
-    uint16_t* dst = lds + st * STAGE_ELEMS + wave_s * 512;  // one wave-load = 8 rows = 1 KB = 512 elements
-#pragma unroll
-    for (int j = 0; j < G; ++j) {
-      if (j < MP / (8 * kSkWaves))  // activation rows
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[j] + ofs),
-                                         (__attribute__((address_space(3))) void*)(dst + j * kSkWaves * 512), 16,
-                                         0, 0);
-      else
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[j] + ofs),
-                                         (__attribute__((address_space(3))) void*)(dst + j * kSkWaves * 512), 16,
-                                         0, kWeightAux);
-    }
-  };
+  const int rot = p.amax_val ? 0
+                             : start_slab(blockIdx.x + (p.N + BN - 1) / BN * split, ns, n_splits * kSkKS,
+                                          MP < 64 ? 64 : MP, K);
 
   floatx4 acc[NTW][MT];
 #pragma unroll
@@ -261,17 +237,20 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
 #pragma unroll
     for (int t = 0; t < MT; ++t) acc[a][t] = floatx4{0.f, 0.f, 0.f, 0.f};
 
+  // Column tile number a of this wave: its group's own range, or, where the groups have unequal numbers, every fourth.
+  auto column_tile = [&](int a) __attribute__((always_inline)) { return NT == 4 * NTW ? ng * NTW + a : 4 * a + ng; };
   // fragment read offset of this wave's k-step: lane (row = lane%16, kq = lane/16) reads chunk 4*step + kq of its row
   const int fo = (lane & 15) * kSkKS + (((4 * kh + (lane >> 4)) ^ (((lane & 15) >> 1) & 7)) * 8);
-  const int wfrag0 = (MP + ng * NTW * 16) * kSkKS;
-  auto multiply = [&](int st) {
+  const int ngs = __builtin_amdgcn_readfirstlane(ng);
+  auto multiply = [&](int st) __attribute__((always_inline)) {
     const uint16_t* sb = lds + st * STAGE_ELEMS;
     u32x4 xf[MT];
 #pragma unroll
     for (int t = 0; t < MT; ++t) xf[t] = *reinterpret_cast<const u32x4*>(sb + t * 16 * kSkKS + fo);
 #pragma unroll
     for (int a = 0; a < NTW; ++a) {
-      const u32x4 wf = *reinterpret_cast<const u32x4*>(sb + wfrag0 + a * 16 * kSkKS + fo);
+      if (NT < 4 * NTW && 4 * a + ngs >= NT) break;
+      const u32x4 wf = *reinterpret_cast<const u32x4*>(sb + (MP + column_tile(a) * 16) * kSkKS + fo);
 #pragma unroll
       for (int t = 0; t < MT; ++t)
         acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf),
@@ -279,31 +258,70 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
     }
   };
 
+  // The loop of a wave that issues G loads a slab: load j is row group g = j*8 + wave of the stage (8 rows), X rows first,
+  // then W rows.
+  auto run = [&](auto loads) __attribute__((always_inline)) {
+    constexpr int G = decltype(loads)::value;
+    const int lr = lane >> 3;
+    const uint16_t* src[G];
 #pragma unroll
-  for (int d = 0; d < D; ++d)
-    if (d < ns) request(d);
+    for (int j = 0; j < G; ++j) {
+      const int r = 8 * (j * kSkWaves + wave) + lr;  // stage row
+      const int sw = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+      if (r < MP) src[j] = p.X + (size_t)min(r, p.M - 1) * K + sw;
+      else src[j] = p.W + (size_t)min(n0 + r - MP, p.N - 1) * K + sw;
+    }
+    // requests the next slab of this split into stage `st`
+    int group = rot, turn = turn_by && rot ? (split + rot) % n_splits : split;
+    auto request = [&](int st) __attribute__((always_inline)) {
+      const int ofs = (group * n_splits + turn) * kSkKS;
+      turn = turn + turn_by == n_splits ? 0 : turn + turn_by;
+      if (++group == ns) group = 0, turn = split;
+      uint16_t* dst = lds + st * STAGE_ELEMS + wave_s * 512;  // one wave-load = 8 rows = 1 KB = 512 elements
+#pragma unroll
+      for (int j = 0; j < G; ++j) {
+        if (j < XGROUPS / kSkWaves || (j == 0 && wave_s < XGROUPS))  // activation rows
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[j] + ofs),
+                                           (__attribute__((address_space(3))) void*)(dst + j * kSkWaves * 512), 16,
+                                           0, 0);
+        else
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[j] + ofs),
+                                           (__attribute__((address_space(3))) void*)(dst + j * kSkWaves * 512), 16,
+                                           0, kWeightAux);
+      }
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+      if (d < ns) request(d);
 
-  int st = 0;      // stage of slab i
-  int st_req = D;  // stage slab i+D goes to (= the stage slab i-1 used)
-  int i = 0;
-  for (; i + D < ns; ++i) {
-    sk_wait_vmcnt<(D - 1) * G>();  // this wave's part of slab i has landed
-    lds_barrier();                 // slab i visible to all waves; everyone is done with slab i-1
-    request(st_req);
-    multiply(st);
-    st_req = st;
-    st = (st + 1 == S) ? 0 : st + 1;
-  }
-  // The last D slabs, all requested: ns - 1 - i younger ones may still be in flight.
-  for (; i < ns; ++i) {
-    sk_wait_slabs<D - 1, G>(ns - 1 - i);
-    lds_barrier();
-    multiply(st);
-    st = (st + 1 == S) ? 0 : st + 1;
+    int st = 0;      // stage of slab i
+    int st_req = D;  // stage slab i+D goes to (= the stage slab i-1 used)
+    int i = 0;
+    for (; i + D < ns; ++i) {
+      sk_wait_vmcnt<(D - 1) * G>();  // this wave's part of slab i has landed
+      lds_barrier();                 // slab i visible to all waves; everyone is done with slab i-1
+      request(st_req);
+      multiply(st);
+      st_req = st;
+      st = (st + 1 == S) ? 0 : st + 1;
+    }
+    // The last D slabs, all requested: ns - 1 - i younger ones may still be in flight.
+    for (; i < ns; ++i) {
+      sk_wait_slabs<D - 1, G>(ns - 1 - i);
+      lds_barrier();
+      multiply(st);
+      st = (st + 1 == S) ? 0 : st + 1;
+    }
+  };
+  if constexpr (MORE == 0) {
+    run(std::integral_constant<int, GROUPS / kSkWaves>{});
+  } else {
+    if (wave_s < MORE) run(std::integral_constant<int, GROUPS / kSkWaves + 1>{});
+    else run(std::integral_constant<int, GROUPS / kSkWaves>{});
   }
   Epilogue4<NTW, MT> epi;
   if (n_splits == 1 && !p.amax_val && kh == 0) {  // (before the loop these loads held up the split launches, 1 %)
-    epi.request(p, lane, [&](int a) { return n0 + (ng * NTW + a) * 16; });
+    epi.request(p, lane, [&](int a) { return n0 + column_tile(a) * 16; });
     epi.pages(p, lane);
   }
   sk_wait_vmcnt<0>();  // no global->LDS write of this workgroup may still be in flight ...
@@ -324,7 +342,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
       for (int t = 0; t < MT; ++t) acc[a][t] += red[((ng * NTW + a) * MT + t) * 64 + lane];
   }
 
-  // acc[a][t][r]: row m = 16t + lane%16, column n = n0 + 16*(ng*NTW + a) + 4*(lane/16) + r
+  // acc[a][t][r]: row m = 16t + lane%16, column n = n0 + 16*column_tile(a) + 4*(lane/16) + r
   if (p.amax_val) {
     // candidates of this lane per row tile, then across the 4 lanes that share a row (lane/16), then
     // across the 4 column-group waves through LDS (behind the k-half buffer, which may still be read)
@@ -339,9 +357,9 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
       for (int a = 0; a < NTW; ++a)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int n = n0 + (ng * NTW + a) * 16 + (lane >> 4) * 4 + r;
+          const int n = n0 + column_tile(a) * 16 + (lane >> 4) * 4 + r;
           const float v = acc[a][t][r];
-          if (n < p.N && (v > bv || (v == bv && n < bi))) {
+          if (column_tile(a) < NT && n < p.N && (v > bv || (v == bv && n < bi))) {
             bv = v;
             bi = n;
           }
@@ -385,8 +403,8 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
   const OutSegments out = out_segments(p, p.seg_cols);
 #pragma unroll
   for (int a = 0; a < NTW; ++a) {
-    const int n = n0 + (ng * NTW + a) * 16 + (lane >> 4) * 4;
-    if (n >= p.N) continue;
+    const int n = n0 + column_tile(a) * 16 + (lane >> 4) * 4;
+    if (column_tile(a) >= NT || n >= p.N) continue;
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
       const int m = t * 16 + (lane & 15);
@@ -935,15 +953,20 @@ size_t skinny_workspace_bytes(int M, int N, int K) {
   return pl.splits > 1 ? (size_t)pl.splits * M * N * sizeof(float) : 0;
 }
 
-template <int MT, int NTW, int S>
+// Stages of 16 MT + 16 NT rows that the LDS has room for (more than eight gain nothing).
+constexpr int ring_stages(int MT, int NT) {
+  const int fit = 160 * 1024 / ((MT + NT) * 16 * kSkKS * 2);
+  return fit < 8 ? fit : 8;
+}
+template <int MT, int NTW, int NT = 4 * NTW>
 static hipError_t launch_skinny_cfg(SkinnyParams p, int splits, hipStream_t stream) {
   p.splits = splits;
-  constexpr int BN = 64 * NTW;
+  constexpr int BN = 16 * NT, S = ring_stages(MT, NT);
   constexpr size_t lds_bytes = (size_t)S * (MT * 16 + BN) * kSkKS * sizeof(uint16_t);
   static_assert(lds_bytes <= 160 * 1024, "LDS");
   static_assert((size_t)4 * NTW * MT * 64 * 16 + (size_t)4 * MT * 16 * 8 <= lds_bytes,
                 "k-half reduction (and the greedy-choice candidates behind it) fit the stages");
-  constexpr auto kern = skinny_gemm_kernel<MT, NTW, S>;
+  constexpr auto kern = skinny_gemm_kernel<MT, NTW, S, NT>;
   (void)KernelAttrReg<kern, (int)lds_bytes>::done;
   hipLaunchKernelGGL(kern, dim3((p.N + BN - 1) / BN, splits), dim3(kSkThreads), lds_bytes, stream, p);
   return hipGetLastError();
@@ -1053,35 +1076,58 @@ static int wring_tiles(int M, int N, int K) {
   return nt;
 }
 
+// Activation rows of a stage: the batch's, up to 16, 32 or 64 (the last row again makes up the rest; with 64 for every
+// batch the token loop's two ends took 91.8 us at 1 row; 85.8 with these and the tiles of `greedy_tiles`).
+template <int NTW, int NT = 4 * NTW>
+static hipError_t dispatch_skinny_rows(const SkinnyParams& p, int splits, hipStream_t stream) {
+  if (p.M <= 16) return launch_skinny_cfg<1, NTW, NT>(p, splits, stream);
+  if (p.M <= 32) return launch_skinny_cfg<2, NTW, NT>(p, splits, stream);
+  return launch_skinny_cfg<4, NTW, NT>(p, splits, stream);
+}
 static hipError_t dispatch_skinny(const SkinnyParams& p, const SkinnyPlan& pl, hipStream_t stream) {
-  // fewer than 64 rows run as 64 (clamped duplicates; the matrix cores are idle anyway)
   if (p.M <= 64) {
-    if (pl.ntw == 4) return launch_skinny_cfg<4, 4, 4>(p, pl.splits, stream);  // 160 KB
-    if (pl.ntw == 2) return launch_skinny_cfg<4, 2, 6>(p, pl.splits, stream);  // 144 KB
-    return launch_skinny_cfg<4, 1, 8>(p, pl.splits, stream);                   // 128 KB
+    if (pl.ntw == 4) return dispatch_skinny_rows<4>(p, pl.splits, stream);
+    if (pl.ntw == 2) return dispatch_skinny_rows<2>(p, pl.splits, stream);
+    return dispatch_skinny_rows<1>(p, pl.splits, stream);
   }
   if (p.M <= 128) {
-    if (pl.ntw == 2) return launch_skinny_cfg<8, 2, 5>(p, pl.splits, stream);  // 160 KB
-    return launch_skinny_cfg<8, 1, 6>(p, pl.splits, stream);                   // 144 KB
+    if (pl.ntw == 2) return launch_skinny_cfg<8, 2>(p, pl.splits, stream);
+    return launch_skinny_cfg<8, 1>(p, pl.splits, stream);
   }
-  return launch_skinny_cfg<16, 1, 4>(p, pl.splits, stream);                    // 160 KB
+  return launch_skinny_cfg<16, 1>(p, pl.splits, stream);
 }
 
 hipError_t launch_argmax_merge(const float* part_val, const int32_t* part_idx, int n_blocks, int M,
                                int32_t* next_token, float* best_logit, hipStream_t stream);
 
+// Tiles of 16 columns that a workgroup of the greedy choice takes: what one CU streams over all rounds of workgroups is
+// smallest.  The launch is not split, so with 64, 128 and 256 columns alone 50272 x 5120 left 59 of the 256 CUs idle (197
+// tiles of 256); a CU has only so much in flight, and 242 tiles of 208 bring 515 MB in faster: with the embedding and
+// the LayerNorm 104.1 -> 97.0 us at 64 rows.  Reckoned for 64 rows whatever the batch has, so that a workspace for
+// many rows is enough for fewer.
+static int greedy_tiles(int M, int N, int K) {
+  int best = 4 * skinny_plan(M, N, K, false).ntw;
+  if (M > 64 || g_skinny_force_ntw > 0) return best;
+  double best_cost = 1e300;
+  for (int nt : {4, 8, 10, 12, 13, 14, 16}) {
+    const int wgs = (N + 16 * nt - 1) / (16 * nt);
+    const double cost = ((wgs + 255) / 256) * (16.0 * nt + 64);
+    if (cost < best_cost) best_cost = cost, best = nt;
+  }
+  return best;
+}
+
 size_t skinny_argmax_workspace_bytes(int M, int N, int K) {
   if (K % kSkPlanK != 0 || M > 256 || M <= 0 || N <= 0) return 0;
-  const SkinnyPlan pl = skinny_plan(M, N, K, false);
-  const size_t blocks = (size_t)(N + 64 * pl.ntw - 1) / (64 * pl.ntw);
+  const int cols = 16 * greedy_tiles(M, N, K);
+  const size_t blocks = (size_t)(N + cols - 1) / cols;
   return blocks * M * (sizeof(float) + sizeof(int32_t));
 }
 
 hipError_t launch_skinny_argmax(const void* X, const void* W, int M, int N, int K, void* workspace,
                                 int32_t* next_token, float* best_logit, hipStream_t stream) {
   if (M <= 0 || M > 256 || N <= 0 || K % kSkPlanK != 0 || !workspace || !next_token) return hipErrorInvalidValue;
-  const SkinnyPlan pl = skinny_plan(M, N, K, false);
-  const int blocks = (N + 64 * pl.ntw - 1) / (64 * pl.ntw);
+  const int tiles = greedy_tiles(M, N, K), blocks = (N + 16 * tiles - 1) / (16 * tiles);
   SkinnyParams p;
   p.X = (const uint16_t*)X;
   p.W = (const uint16_t*)W;
@@ -1095,7 +1141,14 @@ hipError_t launch_skinny_argmax(const void* X, const void* W, int M, int N, int 
   p.partial = nullptr;
   p.amax_val = (float*)workspace;
   p.amax_idx = (int32_t*)(p.amax_val + (size_t)blocks * M);
-  hipError_t e = dispatch_skinny(p, pl, stream);
+  hipError_t e;
+  switch (tiles) {
+    case 10: e = dispatch_skinny_rows<3, 10>(p, 1, stream); break;
+    case 12: e = dispatch_skinny_rows<3>(p, 1, stream); break;
+    case 13: e = dispatch_skinny_rows<4, 13>(p, 1, stream); break;
+    case 14: e = dispatch_skinny_rows<4, 14>(p, 1, stream); break;
+    default: e = dispatch_skinny(p, SkinnyPlan{tiles / 4, 1}, stream);
+  }
   if (e != hipSuccess) return e;
   return launch_argmax_merge(p.amax_val, p.amax_idx, blocks, M, next_token, best_logit, stream);
 }

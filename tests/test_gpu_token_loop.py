@@ -167,6 +167,29 @@ def test_next_token_ties_between_column_blocks(h, rows):
     assert torch.equal(best2, best)
 
 
+@pytest.mark.parametrize("rows", [1, 16, 17, 33, 64])
+@pytest.mark.parametrize("vocab", [16384, 16392, 32776, 40960, 40968, 49152, 49160, 53248, 53256, 57344, 57352, 65544])
+def test_next_token_at_the_edges_of_the_column_tiles(vocab, rows):
+    """The most and the fewest columns for which each tile width is taken (64, 128, 160, 192, 208, 224 and 256): the
+    choice and its logit against float64, and an exact tie between column blocks and within one."""
+    h = 256
+    ctx = _ctx(h, 4, 64, 1024)
+    x = gu.dev_normal_bits((rows, h), 1.0, 61)
+    g, b = gu.dev_normal_bits((h,), 0.05, 62, 1.0), gu.dev_normal_bits((h,), 0.05, 63)
+    w = gu.dev_normal_bits((vocab, h), 0.05, 64)
+    w[vocab - 3] = w[vocab // 2] = w[5]                  # twins of a row that row 0 is made to choose
+    ws = gu.workspace(ctx.ds_next_token_workspace_bytes(rows, vocab))
+    assert ctx.ds_next_token_workspace_bytes(rows, vocab) <= ctx.ds_next_token_workspace_bytes(rows + 1, vocab)
+    tok = torch.full((rows,), -7, dtype=torch.int32, device="cuda")
+    best = torch.zeros(rows, dtype=torch.float32, device="cuda")
+    x[0] = w[5] * 20
+    ctx.ds_next_token(x, None, rows, g, b, w, vocab, tok, best, ws)
+    torch.cuda.synchronize()
+    logits = _oracle_logits(gu.to_bits(x), gu.to_f64(g), gu.to_f64(b), w, 1e-5)
+    _check_choice(tok.cpu().numpy(), best.cpu().numpy().astype(np.float64), logits)
+    assert orc.greedy(logits)[0] == 5 and int(tok[0]) == 5
+
+
 def test_next_token_opt13b_vocab_after_prefill_rows():
     """OPT-13B width and OPT's vocabulary (50272 ids, Sec. 6.1), rows picked like the last positions of a
     packed prefill batch, and a 64-wide decode batch."""
