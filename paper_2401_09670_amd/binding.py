@@ -1,15 +1,19 @@
-"""ctypes binding of libds.so — argument marshalling only.
+"""Binding of libds.so — argument marshalling only: ctypes for contexts, sizes and plans, the module ``_calls``
+(``csrc/py_calls.cpp``) for the calls that take tensors.
 
 Every function here has the name and argument order of its C counterpart in
 ``include/ds.h`` (minus the context, which ``Context`` carries).  Tensors are
 torch CUDA tensors used purely as device buffers: the binding passes
 ``data_ptr()`` and sizes, and the current torch stream as the HIP stream.
+The arguments of a decode step take 1.0 us (3.0 with ctypes, and the stream's object came on top: of a small model's
+request, ten calls of a few launches each, that was a sixth).
 There is no CPU fallback: if the library cannot be loaded, calls raise.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+from types import SimpleNamespace
 from typing import Dict, Optional, Tuple
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
@@ -48,6 +52,10 @@ class LayerWeights(ctypes.Structure):
                  "w_fc1", "b_fc1", "w_fc2", "b_fc2")]
 
 
+# the entry points that take tensors: their library functions are called through the module _calls
+TENSOR_CALLS = ("ds_prefill", "ds_kv_migrate", "ds_decode_step", "ds_decode_step_static", "ds_layernorm", "ds_linear",
+                "ds_prefill_attention", "ds_decode_attention", "ds_embed", "ds_next_token")
+
 _lib = None
 
 
@@ -63,6 +71,7 @@ def load_library() -> ctypes.CDLL:
     # before libds.so asks for it, or torch later finds the system's copy loaded in its place (seen as a
     # segmentation fault at torch's first GPU call when this library was loaded first)
     import torch  # noqa: F401
+    from . import _calls
     lib = ctypes.CDLL(LIB_PATH)
     vp, i32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
     lib.ds_create.argtypes = [ctypes.POINTER(ModelCfg), ctypes.POINTER(vp)]
@@ -110,6 +119,8 @@ def load_library() -> ctypes.CDLL:
     lib.ds_profile_enable.restype = ctypes.c_int
     lib.ds_profile_collect.argtypes = [vp, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int64)]
     lib.ds_profile_collect.restype = ctypes.c_int
+    lib.tensor_calls = SimpleNamespace(**{
+        n: _calls.bind(n, ctypes.cast(getattr(lib, n), vp).value, LayerWeights) for n in TENSOR_CALLS})
     _lib = lib
     return lib
 
@@ -121,14 +132,12 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
-def _stream() -> Optional[int]:
+def _stream() -> int:
+    """The current torch stream of the current device (0: the default stream)."""
     import torch
-    s = torch.cuda.current_stream().cuda_stream
-    return s if s else None
-
-
-def _nbytes(t) -> int:
-    return 0 if t is None else t.numel() * t.element_size()
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 class Context:
@@ -137,6 +146,7 @@ class Context:
     def __init__(self, hidden: int, n_heads: int, head_dim: int, ffn: int, block_size: int = 16,
                  ln_eps: float = 1e-5, n_kv_heads: int = 0):
         self.lib = load_library()
+        self.calls = self.lib.tensor_calls
         self.cfg = ModelCfg(hidden, n_heads, head_dim, ffn, block_size, ln_eps, n_kv_heads)
         self.handle = ctypes.c_void_p()
         st = self.lib.ds_create(ctypes.byref(self.cfg), ctypes.byref(self.handle))
@@ -183,33 +193,30 @@ class Context:
     # ---- the three calls of the path ----
     def ds_prefill(self, weights: LayerWeights, x, cu_seqlens, B: int, t: int, max_seqlen: int, y, k_out, v_out,
                    workspace):
-        self._check(self.lib.ds_prefill(self.handle, ctypes.byref(weights), _ptr(x), _ptr(cu_seqlens), B, t,
-                                        max_seqlen, _ptr(y), _ptr(k_out), _ptr(v_out), _ptr(workspace),
-                                        _nbytes(workspace), _stream()))
+        self._check(self.calls.ds_prefill(self.handle.value, weights, x, cu_seqlens, B, t, max_seqlen, y, k_out,
+                                          v_out, workspace, workspace, _stream()))
 
     def ds_kv_migrate(self, k_src, v_src, cu_seqlens, B: int, t: int, max_seqlen: int, block_tables,
                       max_blocks_per_seq: int, k_cache, v_cache, num_blocks: int):
-        self._check(self.lib.ds_kv_migrate(self.handle, _ptr(k_src), _ptr(v_src), _ptr(cu_seqlens), B, t,
-                                           max_seqlen, _ptr(block_tables), max_blocks_per_seq, _ptr(k_cache),
-                                           _ptr(v_cache), num_blocks, _stream()))
+        self._check(self.calls.ds_kv_migrate(self.handle.value, k_src, v_src, cu_seqlens, B, t, max_seqlen,
+                                             block_tables, max_blocks_per_seq, k_cache, v_cache, num_blocks,
+                                             _stream()))
 
     def ds_decode_step(self, weights: LayerWeights, x, ctx_lens, block_tables, B: int, max_blocks_per_seq: int,
                        max_ctx: int, k_cache, v_cache, num_blocks: int, y, workspace):
-        self._check(self.lib.ds_decode_step(self.handle, ctypes.byref(weights), _ptr(x), _ptr(ctx_lens),
-                                            _ptr(block_tables), B, max_blocks_per_seq, max_ctx, _ptr(k_cache),
-                                            _ptr(v_cache), num_blocks, _ptr(y), _ptr(workspace),
-                                            _nbytes(workspace), _stream()))
+        self._check(self.calls.ds_decode_step(self.handle.value, weights, x, ctx_lens, block_tables, B,
+                                              max_blocks_per_seq, max_ctx, k_cache, v_cache, num_blocks, y,
+                                              workspace, workspace, _stream()))
 
     def ds_decode_step_static(self, weights: LayerWeights, x, ctx_lens, block_tables, B: int,
                               max_blocks_per_seq: int, max_ctx: int, k_cache, v_cache, num_blocks: int, y):
-        self._check(self.lib.ds_decode_step_static(self.handle, ctypes.byref(weights), _ptr(x), _ptr(ctx_lens),
-                                                   _ptr(block_tables), B, max_blocks_per_seq, max_ctx,
-                                                   _ptr(k_cache), _ptr(v_cache), num_blocks, _ptr(y), _stream()))
+        self._check(self.calls.ds_decode_step_static(self.handle.value, weights, x, ctx_lens, block_tables, B,
+                                                     max_blocks_per_seq, max_ctx, k_cache, v_cache, num_blocks, y,
+                                                     _stream()))
 
     # ---- single steps ----
     def ds_layernorm(self, x, gamma, beta, rows: int, out):
-        self._check(self.lib.ds_layernorm(self.handle, _ptr(x), _ptr(gamma), _ptr(beta), rows, _ptr(out),
-                                          _stream()))
+        self._check(self.calls.ds_layernorm(self.handle.value, x, gamma, beta, rows, out, _stream()))
 
     def ds_linear_plan(self, rows: int, in_f: int, out_f: int) -> dict:
         return self._plan(self.lib.ds_linear_plan, rows, in_f, out_f)
@@ -224,33 +231,31 @@ class Context:
                     cut_cols=v[4].value)
 
     def ds_linear(self, x, w, bias, residual, relu: int, rows: int, in_f: int, out_f: int, y, workspace=None):
-        self._check(self.lib.ds_linear(self.handle, _ptr(x), _ptr(w), _ptr(bias), _ptr(residual), relu, rows,
-                                       in_f, out_f, _ptr(y), _ptr(workspace), _nbytes(workspace), _stream()))
+        self._check(self.calls.ds_linear(self.handle.value, x, w, bias, residual, relu, rows, in_f, out_f, y,
+                                         workspace, workspace, _stream()))
 
     def ds_prefill_attention(self, q, k, v, cu_seqlens, B: int, t: int, max_seqlen: int, o):
-        self._check(self.lib.ds_prefill_attention(self.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens), B, t,
-                                                  max_seqlen, _ptr(o), _stream()))
+        self._check(self.calls.ds_prefill_attention(self.handle.value, q, k, v, cu_seqlens, B, t, max_seqlen, o,
+                                                    _stream()))
 
     def ds_decode_attention(self, q, kv_lens, block_tables, B: int, max_blocks_per_seq: int, max_kv_len: int,
                             k_cache, v_cache, num_blocks: int, o, workspace=None):
-        self._check(self.lib.ds_decode_attention(self.handle, _ptr(q), _ptr(kv_lens), _ptr(block_tables), B,
-                                                 max_blocks_per_seq, max_kv_len, _ptr(k_cache), _ptr(v_cache),
-                                                 num_blocks, _ptr(o), _ptr(workspace), _nbytes(workspace),
-                                                 _stream()))
+        self._check(self.calls.ds_decode_attention(self.handle.value, q, kv_lens, block_tables, B,
+                                                   max_blocks_per_seq, max_kv_len, k_cache, v_cache, num_blocks, o,
+                                                   workspace, workspace, _stream()))
 
     # ---- the two ends of the token loop ----
     def ds_embed(self, token_ids, positions, tok_emb, vocab: int, pos_emb, n_pos: int, rows: int, x):
-        self._check(self.lib.ds_embed(self.handle, _ptr(token_ids), _ptr(positions), _ptr(tok_emb), vocab,
-                                      _ptr(pos_emb), n_pos, rows, _ptr(x), _stream()))
+        self._check(self.calls.ds_embed(self.handle.value, token_ids, positions, tok_emb, vocab, pos_emb, n_pos,
+                                        rows, x, _stream()))
 
     def ds_next_token_workspace_bytes(self, rows: int, vocab: int) -> int:
         return self.lib.ds_next_token_workspace_bytes(self.handle, rows, vocab)
 
     def ds_next_token(self, x, row_index, rows: int, ln_g, ln_b, w_vocab, vocab: int, next_token, best_logit,
                       workspace):
-        self._check(self.lib.ds_next_token(self.handle, _ptr(x), _ptr(row_index), rows, _ptr(ln_g), _ptr(ln_b),
-                                           _ptr(w_vocab), vocab, _ptr(next_token), _ptr(best_logit),
-                                           _ptr(workspace), _nbytes(workspace), _stream()))
+        self._check(self.calls.ds_next_token(self.handle.value, x, row_index, rows, ln_g, ln_b, w_vocab, vocab,
+                                             next_token, best_logit, workspace, workspace, _stream()))
 
     # ---- timing ----
     def ds_profile_enable(self, on: bool):

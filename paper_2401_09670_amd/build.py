@@ -1,15 +1,18 @@
-"""Builds libds.so (the C-ABI library) for gfx950 with hipcc, in-tree."""
+"""Builds libds.so (the C-ABI library) for gfx950 with hipcc, and the Python module _calls, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libds.so")
 SOURCES = ["gemm.hip", "gemm_tiles.hip", "gemm_skinny.hip", "ds_api.hip", "layernorm.hip", "kv_cache.hip",
            "attn_prefill.hip", "attn_decode.hip", "token_io.hip"]
+CALLS_PATH = os.path.join(PKG_DIR, "_calls.so")
+CXX = os.environ.get("CXX", "g++")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -19,8 +22,15 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
 DEV_LIB_PATH = os.path.join(PKG_DIR, "libds_dev.so")
 
 
+def build_calls() -> str:
+    """Compile the module through which the binding calls the library (host code only)."""
+    subprocess.run([CXX, "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"],
+                    os.path.join(CSRC, "py_calls.cpp"), "-o", CALLS_PATH], check=True)
+    return CALLS_PATH
+
+
 def build_library(verbose: bool = False, jobs: int = 8, dev: bool = False) -> str:
-    """Compile every kernel source and link libds.so.  Always recompiles.
+    """Compile every kernel source and link libds.so, and the module _calls.  Always recompiles.
 
     dev=True builds libds_dev.so instead: the same sources with -DDS_DEV_SWITCHES, in which the planning
     choices (tile shape, split count, column cut, kernel family) can be forced at run time through
@@ -29,6 +39,7 @@ def build_library(verbose: bool = False, jobs: int = 8, dev: bool = False) -> st
     lib_path = DEV_LIB_PATH if dev else LIB_PATH
     flags = FLAGS + (["-DDS_DEV_SWITCHES"] if dev else [])
     os.makedirs(obj_dir, exist_ok=True)
+    build_calls()
     procs = []
     objs = []
     for src in SOURCES:
