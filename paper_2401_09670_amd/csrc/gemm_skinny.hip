@@ -563,7 +563,8 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
 // variance for itself, as layernorm_kernel does for rows of up to 512 elements, sum by sum in the same order, and
 // each lane normalises the pieces it multiplies, so the bits are those of a launch of its own.
 //
-// C = slabs of 64 a wave asks for at once; K is a multiple of that many for every wave, or C = 1.
+// MT row tiles a workgroup (blockIdx.y: which); C = slabs of 64 a wave asks for at once, K is a multiple of that many for
+// every wave, or C = 1.
 // ---------------------------------------------------------------------------------------------
 constexpr int kShortWaves = 4;
 constexpr int kShortNormK = 512;  // one 16-byte piece of a row per lane
@@ -577,21 +578,21 @@ __global__ __launch_bounds__(64 * kShortWaves) void short_wring_gemm_kernel(cons
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, q = lane >> 4;  // row of a fragment, its quarter of 32 k
-  const int n0 = blockIdx.x * 16, K = p.K, slabs = K / kWrKS;
+  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * BM, K = p.K, slabs = K / kWrKS;
   const uint16_t* wrow = p.W + (size_t)min(n0 + r, p.N - 1) * K + 8 * q;
   const uint16_t* xrow[MT];
 #pragma unroll
-  for (int t = 0; t < MT; ++t) xrow[t] = p.X + (size_t)min(16 * t + r, p.M - 1) * K + 8 * q;
+  for (int t = 0; t < MT; ++t) xrow[t] = p.X + (size_t)min(m0 + 16 * t + r, p.M - 1) * K + 8 * q;
 
   // whole rows for their statistics: wave w has rows w, w + NW, ...
   u32x4 raw[ROWS];
   if constexpr (LN) {
 #pragma unroll
     for (int i = 0; i < ROWS; ++i)
-      raw[i] = ld16(p.X + (size_t)min(wave + NW * i, p.M - 1) * K + min(lane, K / 8 - 1) * 8);
+      raw[i] = ld16(p.X + (size_t)min(m0 + wave + NW * i, p.M - 1) * K + min(lane, K / 8 - 1) * 8);
   }
   Epilogue4<1, 1> epi;  // wave w finishes row tile w
-  epi.first = 16 * min(wave, MT - 1);
+  epi.first = m0 + 16 * min(wave, MT - 1);
   floatx4 acc[MT];
 #pragma unroll
   for (int t = 0; t < MT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -619,6 +620,7 @@ __global__ __launch_bounds__(64 * kShortWaves) void short_wring_gemm_kernel(cons
         const bool live = lane < K / 8;
 #pragma unroll
         for (int i = 0; i < ROWS; ++i) {
+          if (i > 0 && m0 + NW * i >= p.M) break;  // four rows that are not there (step of 1 row of 256 features 16.0 -> 14.4)
           float v[8], sum = 0.f, sq = 0.f;
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
@@ -675,7 +677,7 @@ __global__ __launch_bounds__(64 * kShortWaves) void short_wring_gemm_kernel(cons
   for (int t = 0; t < MT; ++t) red[wave][t][lane] = acc[t];
   __syncthreads();
   if (wave >= MT || n >= p.N) return;
-  const int m = 16 * wave + r;
+  const int m = m0 + 16 * wave + r;
   if (m >= p.M) return;
   floatx4 v = red[0][wave][lane];
 #pragma unroll
@@ -999,7 +1001,7 @@ static hipError_t launch_wring(int nt, const SkinnyParams& p, hipStream_t stream
 
 template <int MT, int C>
 static hipError_t launch_short_cfg(const SkinnyParams& p, hipStream_t stream) {
-  const dim3 grid((p.N + 15) / 16), block(64 * kShortWaves);
+  const dim3 grid((p.N + 15) / 16, (p.M + 16 * MT - 1) / (16 * MT)), block(64 * kShortWaves);
   if constexpr (MT == 1 && C * kShortWaves * kWrKS <= kShortNormK)
     if (p.norm_gamma) {
       hipLaunchKernelGGL((short_wring_gemm_kernel<1, MT, C, true>), grid, block, 0, stream, p);
@@ -1015,30 +1017,34 @@ static hipError_t launch_short_rows(const SkinnyParams& p, hipStream_t stream) {
   if (p.K % (2 * kAll) == 0) return launch_short_cfg<MT, 2>(p, stream);
   return launch_short_cfg<MT, 1>(p, stream);
 }
-static hipError_t launch_short(const SkinnyParams& p, hipStream_t stream) {
-  if (p.M <= 16) return launch_short_rows<1>(p, stream);
-  if (p.M <= 32) return launch_short_rows<2>(p, stream);
-  return launch_short_rows<4>(p, stream);
-}
 
 // Whether a product of a layer is short: up to 1024 of K, so that a lane holds its whole share, and 8.5 MB of weights.  A
 // decoding step (us, of a graph of 24) by the former kernels, with short products, with those that normalise too:
-//   256 x 1024 features, 1 row 24.7, 18.6, 16.5; 16 rows 25.3, 20.4, 17.9; 64 rows 31.1, 26.6, -
-//   512 x 2048            1 row 29.3, 22.6, 21.2; 16 rows 30.9, 25.6, 23.0; 64 rows 38.6, 33.2, -
-//   1024 x 4096           1 row 32.8, 28.8, -;    64 rows 48.8, 47.1, -
+//   256 x 1024 features, 1 row 24.7, 17.1, 14.4; 16 rows 25.3, 19.1, 17.0; 64 rows 31.1, 19.9, 17.5
+//   512 x 2048            1 row 29.3, 21.0, 18.2; 16 rows 30.9, 23.9, 21.7; 64 rows 38.6, 28.6, 27.2
+//   1024 x 4096           1 row 32.8, 26.1, -;    64 rows 48.8, 41.4, -
 // 1024 x 8192 (17 MB): 1 row 32.2 without it, 32.4 with; 64 rows 52.4 and 53.7.  K = 2048 -> 512 features: 1 row 24.1
 // and 22.0, 64 rows 48.3 and 51.3; K = 4096 -> 1024: 29.8 and 30.1, 47.6 and 58.1.  (One line for all row counts, so that a
 // row's bits do not depend on them.)
-// Rows are normalised up to 16 of them: at 32 it is a draw (22.7 and 21.9, 27.5 and 27.3), at 48 25.2 us without and 28.8
-// with, since every workgroup computes all rows' statistics.
 DS_SWITCH(g_skinny_short_k, 1024);   // longest K
 DS_SWITCH(g_skinny_short_kb, 8500);  // most weights (KB)
-constexpr int kShortNormRows = 16;
 static bool short_product(int M, int N, int K) {
   return M <= 64 && K >= kShortWaves * kWrKS && K % kWrKS == 0 && K <= g_skinny_short_k && 2e-3 * N * K <= g_skinny_short_kb;
 }
+// Whether each 16 rows of a short product have workgroups of their own, which read the weights again: as long as that is no
+// more than a short product may have of them.  Many small workgroups start their loads together where one that holds
+// all rows is one load path for 64 rows of X: steps at 64 rows of 256 features 25.1 -> 19.9 us, of 512 31.0 -> 28.6, of 1024
+// 44.2 -> 41.4 (32 rows 35.4 -> 34.4; its QKV and FFN-in, 25 and 34 MB that way for 6.3 and 8.4, apart too: 45.0 and 36.2).
+static bool short_rows_apart(int M, int N, int K) { return 2e-3 * N * K * ((M + 15) / 16) <= g_skinny_short_kb; }
+// Rows are normalised where they lie apart, every workgroup of theirs for itself (all 64 rows' statistics in each
+// workgroup cost more than the launch that is saved): 19.9 -> 17.5 us at 64 rows of 256, 28.6 -> 27.2 of 512.
 bool skinny_norms_input(int M, int N, int K) {
-  return M <= kShortNormRows && K <= kShortNormK && short_product(M, N, K);
+  return K <= kShortNormK && short_product(M, N, K) && short_rows_apart(M, N, K);
+}
+static hipError_t launch_short(const SkinnyParams& p, hipStream_t stream) {
+  if (p.M <= 16 || short_rows_apart(p.M, p.N, p.K)) return launch_short_rows<1>(p, stream);
+  if (p.M <= 32) return launch_short_rows<2>(p, stream);
+  return launch_short_rows<4>(p, stream);
 }
 
 // Column-tile width (in 16-row tiles) for the wave-private-ring kernel, or 0 if the shape is not one it

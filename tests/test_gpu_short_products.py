@@ -1,5 +1,5 @@
-"""Layers whose products are short (16 columns a workgroup, operands straight into registers, up to 16 rows normalised on
-the way in): against the oracle at the edges of its row tiles and of K, and one sequence's bits whatever shares its step."""
+"""Layers whose products are short (16 columns a workgroup, operands straight into registers, rows normalised on the way
+in): against the oracle at the edges of its row tiles and of K, and one sequence's bits whatever shares its step."""
 import numpy as np
 import pytest
 import torch
@@ -44,7 +44,7 @@ def test_short_products_of_a_step(gpu, heads, head_dim, ffn):
     want = orc.layer_decode_cached(orc.weights_from_bits(wbits), gu.to_f64(x), [CTX] * most, tables, gu.to_f64(kc0),
                                    gu.to_f64(vc0), heads)
     full, kc, vc = _step(layer, most, list(range(most)))
-    for batch in (1, 2, 15, 16, 17, 32, 33, 63):
+    for batch in (1, 2, 4, 5, 8, 9, 12, 13, 15, 16, 17, 32, 33, 48, 49, 63):
         rows = [(7 * i + 1) % most for i in range(batch)]
         got, kb, vb = _step(layer, batch, rows)
         assert torch.equal(got, full[rows]), batch
