@@ -258,8 +258,8 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
     }
   };
 
-  // The loop of a wave that issues G loads a slab: load j is row group g = j*8 + wave of the stage (8 rows), X rows first,
-  // then W rows.
+  // The loop of a wave that issues G loads a slab: load j is row group g = j*8 + wave of the stage (8 rows), X rows
+  // first, then W rows.
   auto run = [&](auto loads) __attribute__((always_inline)) {
     constexpr int G = decltype(loads)::value;
     const int lr = lane >> 3;
@@ -425,8 +425,8 @@ __global__ __launch_bounds__(kSkThreads) void skinny_gemm_kernel(const SkinnyPar
 // streaming kernel needs is not many bytes in flight per CU but several streams per CU that do not
 // stall together - two independent 16 KB streams per CU reach 5.7 TB/s, one 64 KB stream 5.3.
 //
-// So: a workgroup (4 waves; 3 for batches above 64 rows) owns 64 or 80 output columns over the whole K; its waves split K between them
-// 64-wide slab by slab (wave w takes slabs w, w+4, ...) and each wave runs its OWN two- or three-stage
+// So: a workgroup (4 waves; 3 for batches above 64 rows) owns 64 or 80 output columns over the whole K; its waves split
+// K between them 64-wide slab by slab (wave w takes slabs w, w+4, ...) and each wave runs its OWN two- or three-stage
 // direct-to-LDS ring [16, 32 or 64 activation rows | 64 or 80 weight rows] x 128 bytes, waiting on nothing but its
 // own loads - no barrier in the loop, four desynchronised streams per CU.  The four waves' 64 x 64
 // fp32 tiles are added through LDS at the end (fixed order) and wave w finishes column tile w.
@@ -620,7 +620,7 @@ __global__ __launch_bounds__(64 * kShortWaves) void short_wring_gemm_kernel(cons
         const bool live = lane < K / 8;
 #pragma unroll
         for (int i = 0; i < ROWS; ++i) {
-          if (i > 0 && m0 + NW * i >= p.M) break;  // four rows that are not there (step of 1 row of 256 features 16.0 -> 14.4)
+          if (i > 0 && m0 + NW * i >= p.M) break;  // no such rows (256 features, step of 1 row 16.0 -> 14.4 us)
           float v[8], sum = 0.f, sq = 0.f;
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
@@ -995,8 +995,7 @@ static hipError_t launch_wring(int nt, const SkinnyParams& p, hipStream_t stream
   }
   if (M <= 16) return launch_wring_cfg<4, 1, 3, 4>(p, stream);    // 120 KB
   if (M <= 32) return launch_wring_cfg<4, 2, 3, 4>(p, stream);    // 144 KB
-  if (M <= 64) return launch_wring_cfg<4, 4, 2, 4>(p, stream);    // 128 KB
-  return launch_wring_cfg<4, 8, 2, 3>(p, stream);                 // 144 KB
+  return launch_wring_cfg<4, 4, 2, 4>(p, stream);                 // 128 KB (wring_tiles: at most 64 rows)
 }
 
 template <int MT, int C>
@@ -1031,10 +1030,11 @@ DS_SWITCH(g_skinny_short_kb, 8500);  // most weights (KB)
 static bool short_product(int M, int N, int K) {
   return M <= 64 && K >= kShortWaves * kWrKS && K % kWrKS == 0 && K <= g_skinny_short_k && 2e-3 * N * K <= g_skinny_short_kb;
 }
-// Whether each 16 rows of a short product have workgroups of their own, which read the weights again: as long as that is no
-// more than a short product may have of them.  Many small workgroups start their loads together where one that holds
-// all rows is one load path for 64 rows of X: steps at 64 rows of 256 features 25.1 -> 19.9 us, of 512 31.0 -> 28.6, of 1024
-// 44.2 -> 41.4 (32 rows 35.4 -> 34.4; its QKV and FFN-in, 25 and 34 MB that way for 6.3 and 8.4, apart too: 45.0 and 36.2).
+// Whether each 16 rows of a short product have workgroups of their own, which read the weights again: as long as that
+// is no more than a short product may have of them.  Many small workgroups start their loads together where one that
+// holds all rows is one load path for 64 rows of X: steps at 64 rows of 256 features 25.1 -> 19.9 us, of 512 31.0 ->
+// 28.6, of 1024 44.2 -> 41.4 (32 rows 35.4 -> 34.4; its QKV and FFN-in, 25 and 34 MB that way for 6.3 and 8.4, apart
+// too: 45.0 and 36.2).
 static bool short_rows_apart(int M, int N, int K) { return 2e-3 * N * K * ((M + 15) / 16) <= g_skinny_short_kb; }
 // Rows are normalised where they lie apart, every workgroup of theirs for itself (all 64 rows' statistics in each
 // workgroup cost more than the launch that is saved): 19.9 -> 17.5 us at 64 rows of 256, 28.6 -> 27.2 of 512.

@@ -111,8 +111,9 @@ hipError_t launch_splitk_reduce(const float* partial, int splits, int M, int N, 
 // launch less, and a short one goes to the kernel for those.
 size_t skinny_workspace_bytes(int M, int N, int K);
 double skinny_us(int M, int N, int K);  // time launch_skinny_gemm takes for 65 to 128 rows, to be held against layer_plan's
-// What launch_skinny_gemm does: columns per workgroup and splits over K (1 split and 64 or 80 columns = the unsplit kernel
-// with wave-private rings, or the ring kernel unsplit).  own_epilogue = false: with a LayerNorm in its reduce pass.
+// What launch_skinny_gemm does: columns per workgroup and splits over K (1 split and 16 columns = the kernel of short
+// products, 64 or 80 = the unsplit kernel with wave-private rings, or the ring kernel unsplit).  own_epilogue = false: with
+// a LayerNorm in its reduce pass.
 void skinny_describe(int M, int N, int K, int* tile_cols, int* splits, bool own_epilogue = true,
                      bool weigh_reduce = false);
 // With `norm` (only where skinny_norms_input says so, and with weigh_reduce) X is LayerNorm'd on the way in.
