@@ -47,6 +47,28 @@ def test_embed(h, vocab, n_pos, rows, with_pos):
         assert np.array_equal(got, ref)
 
 
+@pytest.mark.parametrize("h", [64, 2048, 2112, 8192, 8256, 12288, 16384])
+@pytest.mark.parametrize("with_pos", [True, False])
+def test_embed_rows_of_every_number_of_pieces(h, with_pos):
+    """Rows that end with a turn of 256 pieces or of 1024, and one piece or more behind it; a copy keeps -0 and NaN."""
+    vocab, n_pos, rows = 40, 12, 9
+    ctx = _ctx(h, h // 64, 64, 4 * h)
+    te, pe = gu.dev_normal_bits((vocab, h), 1.0, 4), gu.dev_normal_bits((n_pos, h), 1.0, 5)
+    te[3, ::2], te[3, 1::5] = -0.0, float("nan")
+    ids, pos = [3, 0, 39, 7, 3, 8, 21, 22, 23], [0, 11, 5, 5, 1, 2, 3, 4, 6]
+    x = torch.full((rows + 1, h), 7.0, dtype=torch.bfloat16, device="cuda")
+    ctx.ds_embed(gu.i32_dev(ids), gu.i32_dev(pos) if with_pos else None, te, vocab, pe if with_pos else None,
+                 n_pos if with_pos else 0, rows, x)
+    torch.cuda.synchronize()
+    want = te[ids]
+    if with_pos:
+        want = (want.float() + pe[pos].float()).to(torch.bfloat16)
+        assert torch.equal(x[:rows].nan_to_num(9.0), want.nan_to_num(9.0))
+    else:
+        assert torch.equal(x[:rows].view(torch.int16), want.view(torch.int16))
+    assert bool((x[rows] == 7.0).all())
+
+
 def test_embed_clamps_out_of_range_ids():
     h, vocab, n_pos = 256, 100, 10
     ctx = _ctx(h, 4, 64, 1024)
