@@ -468,48 +468,64 @@ static bool gqa_kernel_serves(int n_heads, int n_kv_heads, int head_dim) {
 }
 
 // Splits of the KV axis where (sequence, head) pairs - (sequence, key/value head) in the grouped-query kernel - are too few
-// to cover the chip: 768 workgroups, three per compute unit; in the grouped-query kernel, of which two fit a compute unit,
-// one round of 512 as long as a workgroup has little to do (fewer than 128 pairs).  512 and 768 (us): 40 heads, 8 sequences
-// of 2048 58.2 and 55.7, 6 of 1024 to 4096 54.1 and 48.7; 96 heads, 2 of 2048 38.8 and 34.7 (the other way: 40 heads, 4 of
-// 2048 31.1 and 32.2); 8 key/value heads, 32 of 1024 to 4096 78 and 71, 16 ragged ones 20.3 and 16.1, but 8 of 2048 18.5
-// and 22.6.  (1024: 12 sequences of 40 heads 99.9 -> 93.6, 4 of 96 heads 84.6 -> 87.6.)  No split has fewer than 8 pages, and
-// more than 8 splits, which the combining launch takes in one go, are made only of 16 pages and more: 8 key/value heads, 2
-// sequences up to 3400 tokens 18.3 -> 14.6, one of 2048 with 40 heads 14.2 -> 12.5.
-int decode_attention_splits(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len) {
+// to cover the chip.  The least number, for which every caller has a workspace, makes 512 workgroups, two per compute
+// unit, of fewer than 512 pairs (more stay whole).  A split has about 8 pages or more, and where there are more than 8 of
+// them, which the combining launch takes in one go, about 16: 8 key/value heads, 2 sequences up to 3400 tokens 18.3 ->
+// 14.6 us, one of 2048 with 40 heads 14.2 -> 12.5.  (The number is rounded up, so 9 pages make 2 splits; the last split
+// has what is left.)
+static long attention_pairs(int B, int n_heads, int n_kv_heads, int head_dim) {
+  return (long)B * (gqa_kernel_serves(n_heads, n_kv_heads, head_dim) ? n_kv_heads : n_heads);
+}
+static int splits_for(long workgroups, long pairs, int max_kv_len) {
   const int pages = (max_kv_len + kDecPage - 1) / kDecPage;
-  const bool grouped = gqa_kernel_serves(n_heads, n_kv_heads, head_dim);
-  const long items = (long)B * (grouped ? n_kv_heads : n_heads);
-  if (items >= 512) return 1;
-  const int wanted = (int)(((grouped && items < 128 ? 512 : 768) + items - 1) / items);
+  const int wanted = (int)((workgroups + pairs - 1) / pairs);
   const int most = std::max(std::min((pages + 7) / 8, kCombined), pages / 16);
   return std::max(1, std::min(wanted, most));
+}
+static int least_splits(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len) {
+  const long pairs = attention_pairs(B, n_heads, n_kv_heads, head_dim);
+  return pairs >= 512 ? 1 : splits_for(512, pairs, max_kv_len);
+}
+static size_t states_bytes(int B, int n_heads, int head_dim, int splits) {
+  return (size_t)B * n_heads * splits * (head_dim + 2) * sizeof(float);
+}
+
+// More than the least, for 768 workgroups, as far as `room` for their states goes; in the grouped-query kernel, of which
+// two fit a compute unit, only where a workgroup has more to do (128 pairs or more).  512 and 768 (us): 40 heads, 8
+// sequences of 2048 58.0 and 55.0, 7 of them 56.4 and 51.4; 96 heads, 2 of 2048 40.7 and 36.1; 8 key/value heads, 32 ragged
+// (lognormal) sequences 34.7 and 27.6, 40 of 700 30.2 and 28.2, but 8 of 2048 18.5 and 22.6 (and 40 heads, 4 of 2048 32.6
+// and 32.7).
+int decode_attention_splits(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len, size_t room) {
+  const int least = least_splits(B, n_heads, n_kv_heads, head_dim, max_kv_len);
+  const long pairs = attention_pairs(B, n_heads, n_kv_heads, head_dim);
+  const bool grouped = gqa_kernel_serves(n_heads, n_kv_heads, head_dim);
+  if (least == 1 || (grouped && pairs < 128)) return least;
+  const long fit = (long)(room / states_bytes(B, n_heads, head_dim, 1));
+  return std::max(least, (int)std::min<long>(splits_for(768, pairs, max_kv_len), fit));
 }
 
 // The order in which sequences start matters where workgroups queue for a place (two per compute unit): a long sequence
 // that starts among the last ends the launch by itself.  Longest first, a decoding step of ragged (lognormal) sequences
 // takes 1 to 7 % less (OPT-13B at 64 sequences 255 -> 244 us, at 128 437 -> 422; 256 of 8 key/value heads 502 -> 469), of
 // equal ones the same.  From some 32 rounds on it is a draw (256 sequences of OPT-175B: 1864 -> 1846, 2324 -> 2352).
-bool decode_attention_wants_order(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len) {
-  const long items = (long)B * (gqa_kernel_serves(n_heads, n_kv_heads, head_dim) ? n_kv_heads : n_heads);
-  const long wgs = items * decode_attention_splits(B, n_heads, n_kv_heads, head_dim, max_kv_len);
+bool decode_attention_wants_order(int B, int n_heads, int n_kv_heads, int head_dim, int splits) {
+  const long wgs = attention_pairs(B, n_heads, n_kv_heads, head_dim) * splits;
   return B > 1 && B <= kMaxSorted && wgs > 2 * 256 && wgs <= 32 * 2 * 256;
 }
 
 size_t decode_attention_workspace_bytes(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len) {
-  const int splits = decode_attention_splits(B, n_heads, n_kv_heads, head_dim, max_kv_len);
-  if (splits == 1) return 0;
-  return (size_t)B * n_heads * splits * (head_dim + 2) * sizeof(float);
+  const int splits = least_splits(B, n_heads, n_kv_heads, head_dim, max_kv_len);
+  return splits == 1 ? 0 : states_bytes(B, n_heads, head_dim, splits);
 }
 
 hipError_t launch_decode_attention(const void* q, int q_stride, const int32_t* kv_lens, int kv_len_add,
                                    const int32_t* block_tables, int B, int max_blocks, int max_kv_len,
                                    const void* k_cache, const void* v_cache, int n_heads, int n_kv_heads,
-                                   int head_dim, void* o, void* workspace, hipStream_t stream,
+                                   int head_dim, int splits, void* o, void* workspace, hipStream_t stream,
                                    const int32_t* order) {
   if (B <= 0) return hipSuccess;
   if (n_kv_heads <= 0 || n_heads % n_kv_heads != 0) return hipErrorInvalidValue;
-  if (B > 65535) return hipErrorInvalidValue;
-  const int splits = decode_attention_splits(B, n_heads, n_kv_heads, head_dim, max_kv_len);
+  if (B > 65535 || splits < 1 || (splits > 1 && !workspace)) return hipErrorInvalidValue;
   const int pages = (max_kv_len + kDecPage - 1) / kDecPage;
   const int pps = (pages + splits - 1) / splits;
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)head_dim);

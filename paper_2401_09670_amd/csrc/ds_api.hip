@@ -480,6 +480,21 @@ ds_ctx::Least decode_least(const ds_ctx* ctx, int max_batch, int max_ctx) {
   return need;
 }
 
+// Bytes for the partial states of a decode step's attention: those of the least number of splits lie between the FFN
+// intermediate and the partial sums of the products.  Neither of these is live while the attention runs, so the states
+// of more splits may take the place of all three.  A matter of B and max_ctx, not of the workspace that a call brings:
+// ds_decode_step's bits must not depend on it.
+struct AttentionRoom {
+  size_t least, all;
+};
+AttentionRoom attention_room(const ds_ctx* ctx, int B, int max_ctx) {
+  const ds_model_cfg& c = ctx->cfg;
+  const size_t least = ds::decode_attention_workspace_bytes(B, c.n_heads, c.n_kv_heads, c.head_dim, max_ctx);
+  if (least == 0) return {0, 0};
+  const size_t u = align_up((size_t)B * c.ffn * 2, 256);
+  return {least, u + align_up(least, 256) + decode_least(ctx, B, max_ctx).partials};
+}
+
 }  // namespace
 
 extern "C" {
@@ -834,9 +849,12 @@ ds_status ds_decode_attention(ds_ctx* ctx, const void* q, const int32_t* kv_lens
                                        lens, s))
       return st;
   }
+  // as many splits as a decode step takes, with the workspace of one
+  const size_t room = std::min(workspace_bytes, attention_room(ctx, B, max_kv_len).all);
+  const int splits = ds::decode_attention_splits(B, c.n_heads, c.n_kv_heads, c.head_dim, max_kv_len, room);
   DS_LAUNCH(ctx, s, DS_K_DECODE_ATTN,
             ds::launch_decode_attention(q, c.hidden, kv_lens, 0, block_tables, B, max_blocks_per_seq, max_kv_len,
-                                        k_cache, v_cache, c.n_heads, c.n_kv_heads, c.head_dim, o, workspace, s));
+                                        k_cache, v_cache, c.n_heads, c.n_kv_heads, c.head_dim, splits, o, workspace, s));
   return DS_OK;
 }
 
@@ -895,13 +913,15 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
   const int hkv = kv_width(c), wqkv = qkv_width(c);
   void* qkv = ws.take((size_t)B * wqkv * 2);
   void* u = ws.take((size_t)B * m * 2);
-  void* att = ws.take(ds::decode_attention_workspace_bytes(B, c.n_heads, c.n_kv_heads, c.head_dim, max_ctx));
+  const AttentionRoom att = attention_room(ctx, B, max_ctx);
+  ws.take(att.least);
   void* sk = ws.take(0);
+  const int splits = ds::decode_attention_splits(B, c.n_heads, c.n_kv_heads, c.head_dim, max_ctx, att.all);
   const size_t sk_bytes = workspace_bytes - ws.off;
 
   // The attention starts its longest sequences first; their order lies in x1 until the out-projection writes there.
   ds::LengthOrder by_length;
-  if (ds::decode_attention_wants_order(B, c.n_heads, c.n_kv_heads, c.head_dim, max_ctx))
+  if (ds::decode_attention_wants_order(B, c.n_heads, c.n_kv_heads, c.head_dim, splits))
     by_length = ds::LengthOrder{ctx_lens, static_cast<int32_t*>(x1), B};
   const uint16_t* qkv16 = static_cast<const uint16_t*>(qkv);
   {
@@ -925,7 +945,7 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
   }
   DS_LAUNCH(ctx, s, DS_K_DECODE_ATTN,
             ds::launch_decode_attention(qkv, wqkv, ctx_lens, 1, block_tables, B, max_blocks_per_seq, max_ctx,
-                                        k_cache, v_cache, c.n_heads, c.n_kv_heads, c.head_dim, o, att, s,
+                                        k_cache, v_cache, c.n_heads, c.n_kv_heads, c.head_dim, splits, o, u, s,
                                         by_length.order));
   const bool fc1_norms = norms_input(B, h, m);
   {

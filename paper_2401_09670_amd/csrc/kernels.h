@@ -158,15 +158,17 @@ hipError_t launch_kv_append(const void* k_new, const void* v_new, int src_stride
                             int n_heads, int head_dim, hipStream_t stream);
 
 // One query per (sequence, head) over the paged cache.  kv_len_add is added to
-// kv_lens[i] (1 when kv_lens holds the lengths before this step's append).  `order` (device, B entries, or null): which
-// sequence to start first, second, ...; decode_attention_wants_order tells whether one is worth having.
+// kv_lens[i] (1 when kv_lens holds the lengths before this step's append).  `splits` of the KV axis: what
+// decode_attention_splits says for `room` bytes of workspace; decode_attention_workspace_bytes of them are enough, more
+// may mean more splits.  `order` (device, B entries, or null): which sequence to start first, second, ...;
+// decode_attention_wants_order tells whether one is worth having.
 size_t decode_attention_workspace_bytes(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len);
-int decode_attention_splits(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len);
-bool decode_attention_wants_order(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len);
+int decode_attention_splits(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len, size_t room);
+bool decode_attention_wants_order(int B, int n_heads, int n_kv_heads, int head_dim, int splits);
 hipError_t launch_decode_attention(const void* q, int q_stride, const int32_t* kv_lens, int kv_len_add,
                                    const int32_t* block_tables, int B, int max_blocks, int max_kv_len,
                                    const void* k_cache, const void* v_cache, int n_heads, int n_kv_heads,
-                                   int head_dim, void* o, void* workspace, hipStream_t stream,
+                                   int head_dim, int splits, void* o, void* workspace, hipStream_t stream,
                                    const int32_t* order = nullptr);
 
 }  // namespace ds
