@@ -490,18 +490,23 @@ static size_t states_bytes(int B, int n_heads, int head_dim, int splits) {
   return (size_t)B * n_heads * splits * (head_dim + 2) * sizeof(float);
 }
 
-// More than the least, for 768 workgroups, as far as `room` for their states goes; in the grouped-query kernel, of which
-// two fit a compute unit, only where a workgroup has more to do (128 pairs or more).  512 and 768 (us): 40 heads, 8
+// More than the least, for 768 workgroups, as far as `room` for their states goes.  512 and 768 (us): 40 heads, 8
 // sequences of 2048 58.0 and 55.0, 7 of them 56.4 and 51.4; 96 heads, 2 of 2048 40.7 and 36.1; 8 key/value heads, 32 ragged
-// (lognormal) sequences 34.7 and 27.6, 40 of 700 30.2 and 28.2, but 8 of 2048 18.5 and 22.6 (and 40 heads, 4 of 2048 32.6
-// and 32.7).
+// (lognormal) sequences 34.7 and 27.6, 40 of 700 30.2 and 28.2 (the other way: 40 heads, 4 of 2048 32.6 and 32.7).
+//   Not beyond 1024 workgroups, which is 3 splits of more than 341 pairs: 40 heads, 9 of 2048 62.0 and 65.2; 8 key/value
+// heads, 47 of 2048 72.0 and 76.8, of 700 31.5 and 32.9 (ragged ones of them gain, 34.7 and 32.8).
+//   Not in the grouped-query kernel, of which two workgroups fit a compute unit, where a workgroup has little to do: with
+// fewer than 128 pairs (8 key/value heads, 8 of 2048 18.5 and 22.6), or up to 1280 tokens where more than 8 heads share a
+// key, whose states are many (steps of 4096 features on 2 key/value heads: 100 sequences of 700 77.7 and 79.9, 126 of 1200
+// 97.2 and 98.8; of 8192 on 4: 63 of 1200 138.6 and 139.5, of 1500 145.1 and 143.4, 64 ragged ones up to 3072 149 and 137).
 int decode_attention_splits(int B, int n_heads, int n_kv_heads, int head_dim, int max_kv_len, size_t room) {
   const int least = least_splits(B, n_heads, n_kv_heads, head_dim, max_kv_len);
   const long pairs = attention_pairs(B, n_heads, n_kv_heads, head_dim);
   const bool grouped = gqa_kernel_serves(n_heads, n_kv_heads, head_dim);
-  if (least == 1 || (grouped && pairs < 128)) return least;
-  const long fit = (long)(room / states_bytes(B, n_heads, head_dim, 1));
-  return std::max(least, (int)std::min<long>(splits_for(768, pairs, max_kv_len), fit));
+  if (least == 1 || (grouped && (pairs < 128 || (n_heads > 8 * n_kv_heads && max_kv_len <= 1280)))) return least;
+  const int wanted = splits_for(768, pairs, max_kv_len);
+  const long fit = std::min((long)(room / states_bytes(B, n_heads, head_dim, 1)), 1024 / pairs);
+  return std::max(least, (int)std::min<long>(wanted, fit));
 }
 
 // The order in which sequences start matters where workgroups queue for a place (two per compute unit): a long sequence

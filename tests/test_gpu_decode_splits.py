@@ -27,6 +27,14 @@ def _problem(heads, n_kv, head_dim, ffn, batch, longest):
     return shape, gu.make_ctx(shape), lens, tables, nblk, kc, vc
 
 
+def _least_workspace(ctx, q, lens, tables, longest, kc, vc, nblk):
+    """Bytes below which ds_decode_attention refuses the call."""
+    with pytest.raises(binding.DsError) as refused:
+        ctx.ds_decode_attention(q, gu.i32_dev(lens), gu.i32_dev(tables), len(lens), tables.shape[1], longest, kc, vc,
+                                nblk, torch.empty_like(q), gu.workspace(256)[:256])
+    return int(re.search(r"workspace 256 < (\d+)", str(refused.value)).group(1))
+
+
 @pytest.mark.parametrize("heads,n_kv,head_dim,ffn,batch,longest", STEPS)
 def test_a_step_stays_within_the_workspace_it_asks_for(gpu, heads, n_kv, head_dim, ffn, batch, longest):
     """The oracle's values and the static step's bits, also from a larger workspace, and nothing written behind it."""
@@ -73,9 +81,7 @@ def test_attention_with_more_and_with_the_least_workspace(gpu, heads, n_kv, head
         assert bool((ws[size:] == 0xff).all()), "wrote past the workspace"
         return o
 
-    with pytest.raises(binding.DsError) as refused:
-        attend(256)
-    least = int(re.search(r"workspace 256 < (\d+)", str(refused.value)).group(1))
+    least = _least_workspace(ctx, q, lens, tables, longest, kc, vc, nblk)
     asked = ctx.ds_decode_workspace_bytes(batch, longest)
     assert least <= asked
     full = attend(asked)
@@ -87,3 +93,25 @@ def test_attention_with_more_and_with_the_least_workspace(gpu, heads, n_kv, head
             k, v = (orc.kv_gather(c, tables[i], lens[i]) for c in (kd, vd))
             want = orc.attention_rows(gu.to_f64(q[i:i + 1]).reshape(1, heads, head_dim), [lens[i] - 1], k, v)[0]
             assert gu.rel_err(got[i], want) < TOL, i
+
+
+# Heads, key/value heads, sequences, longest context, whether more splits than the least are taken: on both sides of 1024
+# workgroups (3 splits of 341 and 342 pairs and more), of 128 grouped pairs, of 8 heads that share a key, of 1280 tokens.
+@pytest.mark.parametrize("heads,n_kv,batch,longest,more", [
+    (64, 8, 42, 700, True), (64, 8, 43, 700, False), (64, 8, 47, 2048, False), (40, 40, 8, 700, True),
+    (40, 40, 9, 700, False), (31, 31, 11, 700, True), (18, 18, 19, 700, False), (64, 8, 16, 700, True),
+    (64, 8, 15, 700, False), (32, 2, 100, 1280, False), (32, 2, 100, 1281, True), (16, 2, 100, 700, True),
+])
+def test_where_more_splits_than_the_least_are_taken(gpu, heads, n_kv, batch, longest, more):
+    """Other splits, other sums: the bits of a call with the least workspace tell."""
+    _, _, lens, tables, nblk, kc, vc = _problem(heads, n_kv, 128, 1024, batch, longest)
+    ctx = binding.Context(heads * 128, heads, 128, 4 * heads * 128, n_kv_heads=n_kv)
+    q = gu.dev_normal_bits((batch, heads * 128), 1.0, 5)
+    asked = ctx.ds_decode_workspace_bytes(batch, longest)
+    outs = []
+    for size in (_least_workspace(ctx, q, lens, tables, longest, kc, vc, nblk), asked):
+        o = torch.empty_like(q)
+        ctx.ds_decode_attention(q, gu.i32_dev(lens), gu.i32_dev(tables), batch, tables.shape[1], longest, kc, vc, nblk,
+                                o, gu.workspace(size)[:size])
+        outs.append(o)
+    assert torch.equal(*outs) != more
