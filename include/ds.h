@@ -238,7 +238,8 @@ ds_status ds_embed(ds_ctx *ctx, const int32_t *token_ids, const int32_t *positio
  * after a packed prefill the last position of each prompt, cu_seqlens[i+1]-1;
  * w_vocab device bf16 [vocab,h] (OPT ties it to tok_emb); vocab % 8 == 0;
  * next_token device int32 [rows]; best_logit device fp32 [rows] or NULL.
- * Entries of row_index are not validated. */
+ * Entries of row_index are not validated.  A workspace without room for the candidates of the fastest
+ * column blocks still serves if it has room for those of wider ones: the same result. */
 size_t ds_next_token_workspace_bytes(const ds_ctx *ctx, int32_t rows, int32_t vocab);
 ds_status ds_next_token(ds_ctx *ctx, const void *x, const int32_t *row_index, int32_t rows,
                         const void *ln_g, const void *ln_b, const void *w_vocab, int32_t vocab,

@@ -674,18 +674,21 @@ ds_status ds_next_token(ds_ctx* ctx, const void* x, const int32_t* row_index, in
     return fail(ctx, DS_ERR_UNSUPPORTED, "ds_next_token: vocab must be a multiple of 8 and hidden of 128");
   if (!aligned16(x) || !aligned16(ln_g) || !aligned16(ln_b) || !aligned16(w_vocab) || !aligned16(workspace))
     return fail(ctx, DS_ERR_INVALID_ARG, "ds_next_token: pointers must be 16-byte aligned");
-  const size_t need = ds_next_token_workspace_bytes(ctx, rows, vocab);
+  const size_t need = align_up((size_t)rows * ctx->cfg.hidden * 2, 256) +
+                      align_up(ds::skinny_argmax_least_bytes(rows, vocab, ctx->cfg.hidden), 256);
   if (!workspace || workspace_bytes < need)
     return fail(ctx, DS_ERR_WORKSPACE, "ds_next_token: workspace %zu < %zu", workspace_bytes, need);
   if (ds_status st = ensure_device(ctx)) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   Carver cv(workspace);
   void* a = cv.take((size_t)rows * ctx->cfg.hidden * 2);
-  void* cand = cv.take(ds::skinny_argmax_workspace_bytes(rows, vocab, ctx->cfg.hidden));
+  void* cand = cv.take(0);
+  const size_t cand_bytes = workspace_bytes - cv.off;
   DS_LAUNCH(ctx, s, DS_K_LAYERNORM,
             ds::launch_layernorm(x, ln_g, ln_b, a, rows, ctx->cfg.hidden, ctx->cfg.ln_eps, s, row_index));
   DS_LAUNCH(ctx, s, DS_K_TOKEN_IO,
-            ds::launch_skinny_argmax(a, w_vocab, rows, vocab, ctx->cfg.hidden, cand, next_token, best_logit, s));
+            ds::launch_skinny_argmax(a, w_vocab, rows, vocab, ctx->cfg.hidden, cand, cand_bytes, next_token, best_logit,
+                                     s));
   return DS_OK;
 }
 

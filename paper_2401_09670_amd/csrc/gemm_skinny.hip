@@ -30,6 +30,7 @@
 // as MFMA row operand), so a lane ends up with 4 consecutive output columns
 // of one row.  With KSPLIT > 1 each split writes fp32 partial sums and a
 // second kernel adds them in a fixed order and applies the epilogue.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -1123,17 +1124,29 @@ static int greedy_tiles(int M, int N, int K) {
   return best;
 }
 
-size_t skinny_argmax_workspace_bytes(int M, int N, int K) {
-  if (K % kSkPlanK != 0 || M > 256 || M <= 0 || N <= 0) return 0;
-  const int cols = 16 * greedy_tiles(M, N, K);
-  const size_t blocks = (size_t)(N + cols - 1) / cols;
+static size_t candidate_bytes(int M, int N, int tiles) {
+  const size_t blocks = (size_t)(N + 16 * tiles - 1) / (16 * tiles);
   return blocks * M * (sizeof(float) + sizeof(int32_t));
 }
+size_t skinny_argmax_workspace_bytes(int M, int N, int K) {
+  if (K % kSkPlanK != 0 || M > 256 || M <= 0 || N <= 0) return 0;
+  return candidate_bytes(M, N, greedy_tiles(M, N, K));
+}
+// With the 64, 128 or 256 columns of the product's own plan, taken where a workspace has no room for the candidates of
+// the tiles above (the same values in either).
+size_t skinny_argmax_least_bytes(int M, int N, int K) {
+  if (K % kSkPlanK != 0 || M > 256 || M <= 0 || N <= 0) return 0;
+  return std::min(skinny_argmax_workspace_bytes(M, N, K), candidate_bytes(M, N, 4 * skinny_plan(M, N, K, false).ntw));
+}
 
-hipError_t launch_skinny_argmax(const void* X, const void* W, int M, int N, int K, void* workspace,
+hipError_t launch_skinny_argmax(const void* X, const void* W, int M, int N, int K, void* workspace, size_t workspace_bytes,
                                 int32_t* next_token, float* best_logit, hipStream_t stream) {
-  if (M <= 0 || M > 256 || N <= 0 || K % kSkPlanK != 0 || !workspace || !next_token) return hipErrorInvalidValue;
-  const int tiles = greedy_tiles(M, N, K), blocks = (N + 16 * tiles - 1) / (16 * tiles);
+  if (M <= 0 || M > 256 || N <= 0 || K % kSkPlanK != 0 || !workspace || !next_token ||
+      workspace_bytes < skinny_argmax_least_bytes(M, N, K))
+    return hipErrorInvalidValue;
+  const bool fits = workspace_bytes >= skinny_argmax_workspace_bytes(M, N, K);
+  const int tiles = fits ? greedy_tiles(M, N, K) : 4 * skinny_plan(M, N, K, false).ntw;
+  const int blocks = (N + 16 * tiles - 1) / (16 * tiles);
   SkinnyParams p;
   p.X = (const uint16_t*)X;
   p.W = (const uint16_t*)W;

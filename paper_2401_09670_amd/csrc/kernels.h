@@ -130,9 +130,11 @@ hipError_t launch_skinny_gemm(const void* X, const void* W, int M, int N, int K,
 // Greedy token choice over logits = X[M,K] W[N,K]^T (M <= 256, fp32 accumulation, never written out):
 // the weight-streaming kernel keeps, per row and column block, the largest logit and its column; a
 // second kernel merges the blocks (ties -> lowest column).  next_token [M] int32, best_logit [M]
-// fp32 or null.  Workspace: skinny_argmax_workspace_bytes.
+// fp32 or null.  Workspace: skinny_argmax_workspace_bytes, or (other column blocks, the same result) any size from
+// skinny_argmax_least_bytes on.
 size_t skinny_argmax_workspace_bytes(int M, int N, int K);
-hipError_t launch_skinny_argmax(const void* X, const void* W, int M, int N, int K, void* workspace,
+size_t skinny_argmax_least_bytes(int M, int N, int K);
+hipError_t launch_skinny_argmax(const void* X, const void* W, int M, int N, int K, void* workspace, size_t workspace_bytes,
                                 int32_t* next_token, float* best_logit, hipStream_t stream);
 
 // x[r,:] = tok_emb[clamp(token_ids[r]),:] + pos_emb[clamp(positions[r]),:] (fp32 sum, bf16 result);

@@ -212,6 +212,33 @@ def test_next_token_at_the_edges_of_the_column_tiles(vocab, rows):
     assert orc.greedy(logits)[0] == 5 and int(tok[0]) == 5
 
 
+# rows, hidden size, ids, bytes that callers have had reported for them
+@pytest.mark.parametrize("rows,h,vocab,size", [
+    (1, 256, 33560, 1792), (16, 256, 50272, 33536), (64, 256, 50272, 133632), (33, 256, 128256, 149248),
+    (64, 256, 2048, 49152), (1, 5120, 50272, 12032),
+])
+def test_next_token_with_a_workspace_of_fewer_column_blocks(rows, h, vocab, size):
+    ctx = _ctx(h, h // 64, 64, 4 * h)
+    x = gu.dev_normal_bits((rows, h), 1.0, 71)
+    g, b = gu.dev_normal_bits((h,), 0.05, 72, 1.0), gu.dev_normal_bits((h,), 0.05, 73)
+    w = gu.dev_normal_bits((vocab, h), 0.05, 74)
+    w[vocab - 3] = w[5]
+    x[0] = w[5] * 20
+    outs = []
+    for n in (ctx.ds_next_token_workspace_bytes(rows, vocab), size):
+        ws = torch.full((n + 4096,), 0x55, dtype=torch.uint8, device="cuda")
+        tok = torch.full((rows,), -7, dtype=torch.int32, device="cuda")
+        best = torch.zeros(rows, dtype=torch.float32, device="cuda")
+        ctx.ds_next_token(x, None, rows, g, b, w, vocab, tok, best, ws[:n])
+        torch.cuda.synchronize()
+        assert bool((ws[n:] == 0x55).all()), "wrote past the workspace"
+        outs.append((tok, best))
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+    assert int(outs[0][0][0]) == 5
+    with pytest.raises(binding.DsError):
+        ctx.ds_next_token(x, None, rows, g, b, w, vocab, tok, best, gu.workspace(size)[:rows * h * 2])
+
+
 def test_next_token_opt13b_vocab_after_prefill_rows():
     """OPT-13B width and OPT's vocabulary (50272 ids, Sec. 6.1), rows picked like the last positions of a
     packed prefill batch, and a 64-wide decode batch."""
