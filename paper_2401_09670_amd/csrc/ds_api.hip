@@ -922,9 +922,12 @@ static ds_status decode_step(ds_ctx* ctx, const ds_layer_weights* w, const void*
   const int splits = ds::decode_attention_splits(B, c.n_heads, c.n_kv_heads, c.head_dim, max_ctx, att.all);
   const size_t sk_bytes = workspace_bytes - ws.off;
 
-  // The attention starts its longest sequences first; their order lies in x1 until the out-projection writes there.
+  // The attention starts its longest sequences first; their order lies in x1 until the out-projection writes there.  It
+  // is made beside LayerNorm's rows, so not where that is no launch of its own: a step of 64 sequences of 256 features
+  // 25.7 -> 23.4 us at lengths of 300, 35.1 -> 33.0 at ragged ones, 32 of 512 features 37.7 -> 36.0.
   ds::LengthOrder by_length;
-  if (ds::decode_attention_wants_order(B, c.n_heads, c.n_kv_heads, c.head_dim, splits))
+  if (!norms_input(B, h, wqkv) &&
+      ds::decode_attention_wants_order(B, c.n_heads, c.n_kv_heads, c.head_dim, splits))
     by_length = ds::LengthOrder{ctx_lens, static_cast<int32_t*>(x1), B};
   const uint16_t* qkv16 = static_cast<const uint16_t*>(qkv);
   {

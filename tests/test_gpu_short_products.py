@@ -16,14 +16,14 @@ CTX = 21
 LAYERS = [(4, 64, 1024), (6, 64, 264), (8, 64, 512), (10, 64, 1032), (8, 128, 4096)]
 
 
-def _step(layer, batch, rows):
+def _step(layer, batch, rows, context=CTX):
     """y, K and V rows of a step of `batch` sequences, the sequences `rows` of a larger one."""
     shape, ctx, lw, x, kc0, vc0, tables, nblk = layer
     kc, vc = kc0.clone(), vc0.clone()
     y = torch.full((batch + 1, shape.hidden), 7.0, dtype=torch.bfloat16, device="cuda")      # guard row
-    ctx.ds_decode_step(lw, x[rows].contiguous(), gu.i32_dev([CTX] * batch), gu.i32_dev(tables[rows]), batch,
-                       tables.shape[1], CTX + 1, kc, vc, nblk, y,
-                       gu.workspace(ctx.ds_decode_workspace_bytes(batch, CTX + 1)))
+    ctx.ds_decode_step(lw, x[rows].contiguous(), gu.i32_dev([context] * batch), gu.i32_dev(tables[rows]), batch,
+                       tables.shape[1], context + 1, kc, vc, nblk, y,
+                       gu.workspace(ctx.ds_decode_workspace_bytes(batch, context + 1)))
     torch.cuda.synchronize()
     assert bool((y[batch] == 7.0).all()), "wrote past the last row"
     return y[:batch], kc, vc
@@ -54,6 +54,29 @@ def test_short_products_of_a_step(gpu, heads, head_dim, ffn):
             blk = int(tables[rows[i]][CTX // 16])
             assert torch.equal(kb[blk, :, CTX % 16], kc[blk, :, CTX % 16])
             assert torch.equal(vb[blk, :, CTX % 16], vc[blk, :, CTX % 16])
+
+
+@pytest.mark.parametrize("heads,ffn,most", [(4, 1024, 64), (8, 2048, 32)])
+def test_steps_at_longer_contexts_normalise_in_their_products(gpu, heads, ffn, most):
+    """Where the attention would start its sequences in an order of its own, too: no LayerNorm launch, and a sequence's K
+    and V rows are those of a smaller step."""
+    context = 300
+    shape = synth.ModelShape(hidden=heads * 64, n_heads=heads, head_dim=64, ffn=ffn)
+    lw, keep = gu.dev_layer_weights(shape, 93)
+    ctx = gu.make_ctx(shape)
+    tables, nblk = synth.make_block_tables([context + 1] * most, 16, 3)
+    kc0, vc0 = (gu.dev_normal_bits((nblk, heads, 16, 64), 1.0, i) for i in (1, 2))
+    layer = (shape, ctx, lw, gu.dev_normal_bits((most, shape.hidden), 1.0, 5), kc0, vc0, tables, nblk)
+    ctx.ds_profile_enable(True)
+    _, kc, vc = _step(layer, most, list(range(most)), context)
+    assert ctx.ds_profile_collect()["layernorm"][1] == 0
+    ctx.ds_profile_enable(False)
+    rows = [(7 * i + 1) % most for i in range(5)]
+    _, kb, vb = _step(layer, 5, rows, context)
+    for r in rows:
+        blk = int(tables[r][context // 16])
+        assert torch.equal(kb[blk, :, context % 16], kc[blk, :, context % 16])
+        assert torch.equal(vb[blk, :, context % 16], vc[blk, :, context % 16])
 
 
 @pytest.mark.parametrize("t", [1, 16, 17, 50, 64])
