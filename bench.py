@@ -54,7 +54,7 @@ def main():
     if not torch.cuda.is_available():
         print("bench.py: needs a GPU", file=sys.stderr)
         sys.exit(2)
-    if not os.path.exists(binding.LIB_PATH):
+    if not binding.is_built():
         import __graft_entry__
         __graft_entry__.build()
 

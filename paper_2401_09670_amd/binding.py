@@ -18,6 +18,7 @@ from typing import Dict, Optional, Tuple
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG_DIR, "libds.so")
+CALLS_PATH = os.path.join(PKG_DIR, "_calls.so")
 
 DS_OK = 0
 STATIC_SCRATCH_BYTES = 32 << 20   # DS_STATIC_SCRATCH_BYTES of include/ds.h
@@ -59,14 +60,20 @@ TENSOR_CALLS = ("ds_prefill", "ds_kv_migrate", "ds_decode_step", "ds_decode_step
 _lib = None
 
 
+def is_built() -> bool:
+    """Whether the library and the module that calls it are there."""
+    return os.path.exists(LIB_PATH) and os.path.exists(CALLS_PATH)
+
+
 def load_library() -> ctypes.CDLL:
-    """Load libds.so (built in-tree by ``build.build_library``); raises if absent."""
+    """Load libds.so and ``_calls`` (built in-tree by ``build``); raises if either is absent."""
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise RuntimeError(f"{LIB_PATH} is missing: build it with __graft_entry__.build() "
-                           "(there is no fallback path)")
+    for path in (LIB_PATH, CALLS_PATH):
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is missing: build it with __graft_entry__.build() "
+                               "(there is no fallback path)")
     # torch ships a HIP runtime of its own under the same library name: it has to be the one in the process
     # before libds.so asks for it, or torch later finds the system's copy loaded in its place (seen as a
     # segmentation fault at torch's first GPU call when this library was loaded first)

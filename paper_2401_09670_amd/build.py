@@ -30,7 +30,7 @@ def build_calls() -> str:
 
 
 def build_library(verbose: bool = False, jobs: int = 8, dev: bool = False) -> str:
-    """Compile every kernel source and link libds.so, and the module _calls.  Always recompiles.
+    """Compile every kernel source and link libds.so.  Always recompiles.
 
     dev=True builds libds_dev.so instead: the same sources with -DDS_DEV_SWITCHES, in which the planning
     choices (tile shape, split count, column cut, kernel family) can be forced at run time through
@@ -39,7 +39,6 @@ def build_library(verbose: bool = False, jobs: int = 8, dev: bool = False) -> st
     lib_path = DEV_LIB_PATH if dev else LIB_PATH
     flags = FLAGS + (["-DDS_DEV_SWITCHES"] if dev else [])
     os.makedirs(obj_dir, exist_ok=True)
-    build_calls()
     procs = []
     objs = []
     for src in SOURCES:
@@ -68,4 +67,5 @@ def build_library(verbose: bool = False, jobs: int = 8, dev: bool = False) -> st
 
 
 if __name__ == "__main__":
+    print(build_calls())
     print(build_library(verbose=True, dev="--dev" in sys.argv[1:]))

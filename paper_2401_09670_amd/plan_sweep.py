@@ -27,6 +27,8 @@ class Harness:
         from . import binding, build
         if not os.path.exists(build.DEV_LIB_PATH):
             build.build_library(dev=True)
+        if not os.path.exists(build.CALLS_PATH):
+            build.build_calls()
         binding.LIB_PATH = build.DEV_LIB_PATH      # this process only
         self.torch, self.binding = torch, binding
         self.lib = binding.load_library()

@@ -74,8 +74,18 @@ def test_host_argument_checks_return_status():
 def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(binding, "_lib", None)
     monkeypatch.setattr(binding, "LIB_PATH", "/nonexistent/libds.so")
-    with pytest.raises(RuntimeError):
+    assert not binding.is_built()
+    with pytest.raises(RuntimeError, match="build it with"):
         binding.Context(256, 4, 64, 1024)
+
+
+def test_missing_module_fails_with_the_same_instruction(monkeypatch):
+    """A tree whose library is older than the module through which the binding calls it."""
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "CALLS_PATH", "/nonexistent/_calls.so")
+    assert not binding.is_built()
+    with pytest.raises(RuntimeError, match="_calls.so is missing: build it with"):
+        binding.load_library()
 
 
 @pytest.mark.parametrize("hidden,n_heads,head_dim,ffn,n_kv", [

@@ -6,7 +6,10 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2401_09670_amd import _calls, binding
+from paper_2401_09670_amd import binding
+
+binding.load_library()  # (says what to build, if anything)
+from paper_2401_09670_amd import _calls  # noqa: E402
 
 VP, I32, SZ = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
 
