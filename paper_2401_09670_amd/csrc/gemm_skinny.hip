@@ -1110,7 +1110,11 @@ hipError_t launch_argmax_merge(const float* part_val, const int32_t* part_idx, i
 // smallest.  The launch is not split, so with 64, 128 and 256 columns alone 50272 x 5120 left 59 of the 256 CUs idle (197
 // tiles of 256); a CU has only so much in flight, and 242 tiles of 208 bring 515 MB in faster: with the embedding and
 // the LayerNorm 104.1 -> 97.0 us at 64 rows.  Reckoned for 64 rows whatever the batch has, so that a workspace for
-// many rows is enough for fewer.
+// many rows is enough for fewer.  Other vocabularies (5120 features, with the LayerNorm, at 1 and 64 rows, from 64, 128
+// and 256 columns alone): 32000 ids 57.9 -> 54.7 and 65.9 -> 64.7, 65024 107 -> 102 and 113 -> 112, 100352 178 -> 157 and
+// 194 -> 175, 128256 202 -> 194 and level, 152064 270 -> 233 and 290 -> 259; none slower, at 1024 to 12288 features.  Of
+// the widths on offer the rule takes the fastest there, or one within 2 %.  Where rows are a power of two apart it can miss
+// (the channels of the memory count then): 4096 features, 65024 ids at 1 row 123 with its 256 columns, 98 with 64.
 static int greedy_tiles(int M, int N, int K) {
   int best = 4 * skinny_plan(M, N, K, false).ntw;
   if (M > 64 || g_skinny_force_ntw > 0) return best;
