@@ -570,8 +570,9 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
 constexpr int kShortWaves = 4;
 constexpr int kShortNormK = 512;  // one 16-byte piece of a row per lane
 
-template <int MT, int C, bool LN>
+template <int NT, int MT, int C, bool LN>
 __global__ __launch_bounds__(64 * kShortWaves) void short_wring_gemm_kernel(const SkinnyParams p) {
+  static_assert(NT == 1, "16 columns a workgroup");
   constexpr int NW = kShortWaves, BM = 16 * MT, ROWS = LN ? BM / NW : 1;
   __shared__ floatx4 red[NW][MT][64];
   __shared__ float mean_s[BM], rstd_s[BM];
@@ -1003,10 +1004,10 @@ static hipError_t launch_short_cfg(const SkinnyParams& p, hipStream_t stream) {
   const dim3 grid((p.N + 15) / 16, (p.M + 16 * MT - 1) / (16 * MT)), block(64 * kShortWaves);
   if constexpr (MT == 1 && C * kShortWaves * kWrKS <= kShortNormK)
     if (p.norm_gamma) {
-      hipLaunchKernelGGL((short_wring_gemm_kernel<MT, C, true>), grid, block, 0, stream, p);
+      hipLaunchKernelGGL((short_wring_gemm_kernel<1, MT, C, true>), grid, block, 0, stream, p);
       return hipGetLastError();
     }
-  hipLaunchKernelGGL((short_wring_gemm_kernel<MT, C, false>), grid, block, 0, stream, p);
+  hipLaunchKernelGGL((short_wring_gemm_kernel<1, MT, C, false>), grid, block, 0, stream, p);
   return hipGetLastError();
 }
 template <int MT>
