@@ -564,7 +564,8 @@ __global__ __launch_bounds__(64 * NW) void wring_gemm_kernel(const SkinnyParams 
 // variance for itself, as layernorm_kernel does for rows of up to 512 elements, sum by sum in the same order, and
 // each lane normalises the pieces it multiplies, so the bits are those of a launch of its own.
 //
-// MT row tiles a workgroup (blockIdx.y: which); C = slabs of 64 a wave asks for at once, K is a multiple of that many for
+// NT = 1 column tile a workgroup (the first parameter as at wring_gemm_kernel: what ran is read off the kernels' names); MT
+// row tiles (blockIdx.y: which); C = slabs of 64 a wave asks for at once, K is a multiple of that many for
 // every wave, or C = 1.
 // ---------------------------------------------------------------------------------------------
 constexpr int kShortWaves = 4;
