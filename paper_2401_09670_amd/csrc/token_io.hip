@@ -9,11 +9,24 @@
 namespace ds {
 
 // One workgroup per output row, 16-byte pieces.  Ids outside the tables are clamped into them (a
-// wrong id must not become a wild read).  Bound by latency: the pieces of a lane are asked for together, up to kTogether
-// of them (pieces past the end are the last one again, and a table that is absent is the other one, not used: a branch
-// around a load ends in a wait).  With the merge below, which does the same, both ends of the token loop for 50272 x 5120
-// at 1 row 85.8 -> 84.7 us, at 64 rows 97.0 -> 95.3.
-constexpr int kTogether = 4;  // (the asm below names as many)
+// wrong id must not become a wild read).  Up to 512 rows it is bound by latency: the T pieces of a lane are asked for
+// together (past the end the last one again, not used).  5120 features with positions at 64 rows 2.73 -> 2.51 us, 12288
+// 3.57 -> 3.15; with the merge below, which does the same, both ends of the token loop for 50272 x 5120 at 1 row 85.8 ->
+// 84.7, at 64 rows 97.0 -> 95.3.  More rows, a prompt's, are bound by bandwidth: one piece at a time (1024 rows of 9216
+// features without positions 5.8 us, 6.3 together).  A lane has no more pieces than its row, and there is no second table
+// where none is given (4 pieces and two tables always: 8192 rows of 1024 features without positions 5.6 -> 8.0).
+constexpr int kTogether = 4;
+constexpr int kStreamedRows = 512;
+// All of v is there from here on (or the compiler moves each load behind the branch before its use).
+template <int T>
+__device__ __forceinline__ void arrived(u32x4 (&v)[T]) {
+  static_assert(T >= 1 && T <= 4);
+  if constexpr (T == 1) asm volatile("" : "+v"(v[0]));
+  if constexpr (T == 2) asm volatile("" : "+v"(v[0]), "+v"(v[1]));
+  if constexpr (T == 3) asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]));
+  if constexpr (T == 4) asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+}
+template <int T, bool POS>
 __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ token_ids,
                                                     const int32_t* __restrict__ positions,
                                                     const uint16_t* __restrict__ tok_emb, int vocab,
@@ -22,23 +35,23 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
   const size_t row = blockIdx.x;
   const int id = min(max(token_ids[row], 0), vocab - 1);
   const uint16_t* te = tok_emb + (size_t)id * h;
-  const uint16_t* pe = te;
-  if (pos_emb) pe = pos_emb + (size_t)min(max(positions[row], 0), n_pos - 1) * h;
+  const uint16_t* pe = POS ? pos_emb + (size_t)min(max(positions[row], 0), n_pos - 1) * h : nullptr;
   uint16_t* xr = x + row * (size_t)h;
   const int pieces = h >> 3;
-  for (int c0 = threadIdx.x; c0 < pieces; c0 += kTogether * 256) {
-    u32x4 a[kTogether], b[kTogether];
+  for (int c0 = threadIdx.x; c0 < pieces; c0 += T * 256) {
+    u32x4 a[T], b[T];
 #pragma unroll
-    for (int u = 0; u < kTogether; ++u) {
-      const int c = min(c0 + 256 * u, pieces - 1);
+    for (int u = 0; u < T; ++u) {
+      const int c = T == 1 ? c0 : min(c0 + 256 * u, pieces - 1);
       a[u] = ld16(te + c * 8);
-      b[u] = ld16(pe + c * 8);
+      if constexpr (POS) b[u] = ld16(pe + c * 8);
     }
-    asm volatile("" : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]));  // (or the loads move behind the branch)
+    if constexpr (POS) arrived(b);
+    arrived(a);
 #pragma unroll
-    for (int u = 0; u < kTogether; ++u) {
+    for (int u = 0; u < T; ++u) {
       if (c0 + 256 * u >= pieces) break;
-      if (pos_emb) {
+      if constexpr (POS) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           a[u][j] = pack_bf16(bf16_lo(a[u][j]) + bf16_lo(b[u][j]), bf16_hi(a[u][j]) + bf16_hi(b[u][j]));
@@ -48,12 +61,23 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
   }
 }
 
+template <int T>
+static void launch_embed_pieces(const int32_t* token_ids, const int32_t* positions, const void* tok_emb, int vocab,
+                                const void* pos_emb, int n_pos, int rows, int h, void* x, hipStream_t stream) {
+  auto* kern = pos_emb ? embed_kernel<T, true> : embed_kernel<T, false>;
+  hipLaunchKernelGGL(kern, dim3(rows), dim3(256), 0, stream, token_ids, positions, (const uint16_t*)tok_emb, vocab,
+                     (const uint16_t*)pos_emb, n_pos, h, (uint16_t*)x);
+}
+
 hipError_t launch_embed(const int32_t* token_ids, const int32_t* positions, const void* tok_emb, int vocab,
                         const void* pos_emb, int n_pos, int rows, int h, void* x, hipStream_t stream) {
   if (rows <= 0) return hipSuccess;
-  if (h % 8 != 0 || vocab <= 0 || (pos_emb && (n_pos <= 0 || !positions))) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(embed_kernel, dim3(rows), dim3(256), 0, stream, token_ids, positions,
-                     (const uint16_t*)tok_emb, vocab, (const uint16_t*)pos_emb, n_pos, h, (uint16_t*)x);
+  if (h % 8 != 0 || vocab <= 0 || (pos_emb && (!positions || n_pos <= 0))) return hipErrorInvalidValue;
+  const int turns = rows > kStreamedRows ? 1 : (h / 8 + 255) / 256;  // pieces of a lane at a time
+  auto* launch = turns <= 1 ? launch_embed_pieces<1>
+                            : (turns == 2 ? launch_embed_pieces<2>
+                                          : (turns == 3 ? launch_embed_pieces<3> : launch_embed_pieces<kTogether>));
+  launch(token_ids, positions, tok_emb, vocab, pos_emb, n_pos, rows, h, x, stream);
   return hipGetLastError();
 }
 

@@ -69,6 +69,22 @@ def test_embed_rows_of_every_number_of_pieces(h, with_pos):
     assert bool((x[rows] == 7.0).all())
 
 
+@pytest.mark.parametrize("rows", [512, 513])
+@pytest.mark.parametrize("h,with_pos", [(512, True), (2112, True), (2112, False), (12288, True), (12288, False)])
+def test_embed_on_both_sides_of_the_rows_taken_piece_by_piece(h, rows, with_pos):
+    vocab, n_pos = 300, 70
+    ctx = _ctx(h, h // 64, 64, 4 * h)
+    te, pe = gu.dev_normal_bits((vocab, h), 1.0, 4), gu.dev_normal_bits((n_pos, h), 1.0, 5)
+    ids, pos = [(7 * i) % vocab for i in range(rows)], [(3 * i) % n_pos for i in range(rows)]
+    x = torch.full((rows + 1, h), 7.0, dtype=torch.bfloat16, device="cuda")
+    ctx.ds_embed(gu.i32_dev(ids), gu.i32_dev(pos) if with_pos else None, te, vocab, pe if with_pos else None,
+                 n_pos if with_pos else 0, rows, x)
+    torch.cuda.synchronize()
+    want = (te[ids].float() + pe[pos].float()).to(torch.bfloat16) if with_pos else te[ids]
+    assert torch.equal(x[:rows], want)
+    assert bool((x[rows] == 7.0).all())
+
+
 def test_embed_clamps_out_of_range_ids():
     h, vocab, n_pos = 256, 100, 10
     ctx = _ctx(h, 4, 64, 1024)
